@@ -8,14 +8,15 @@
 // u_t.  Every variable has degree <= 3, so the z-update is a 2- or 3-term
 // average.  alpha = 1, so the per-edge state is m alone (u = m - z).
 //
-// Mapping to gfx950: one lane per time step.  Instances with T <= 64 run one
-// per wavefront, up to four independent wavefronts per workgroup; longer
-// instances use ceil(T/64) wavefronts of one workgroup in lockstep.  All of
-// an instance's per-edge state and z stay in registers for the whole solve;
-// neighbouring time steps exchange z and m through LDS; the matrices of the
-// projection are read from a per-instance parameter block with wavefront-
-// uniform addresses.  Workgroups take work items from a queue until it is
-// empty.  Each instance stops at the first iteration with
+// Mapping to gfx950: sixteen time steps are the columns of an f32 MFMA tile
+// and the projection's products run on the matrix cores (solve_one).
+// Instances with T <= 32 run one per wavefront and share workgroups;
+// longer ones on the wavefronts of a workgroup in lockstep, one tile each.
+// All of an instance's per-edge state, its z and the
+// matrices stay in registers for the whole solve; neighbouring time steps
+// exchange z and m by lane shifts, and through LDS between wavefronts.
+// Workgroups take work items from a queue until it is empty.  Each instance
+// stops at the first iteration with
 //   r = max_e |x_e - z_b| <= tol  and  s = rho max_b |z_b - z_b(prev)| <= tol.
 #include <hip/hip_ext.h>
 
@@ -29,12 +30,13 @@
 
 namespace {
 
-constexpr int WGT = 256;   // threads per workgroup (batches with an instance of T > 128)
-constexpr int WGS = 128;   // threads per workgroup when every instance has T <= 128
+constexpr int T1 = 32;     // longest horizon that one wavefront solves alone (two tiles)
+constexpr int TS = 128;    // longest horizon on eight wavefronts (one tile each)
+constexpr int MAXW = 16;   // most wavefronts per workgroup
 constexpr int MN = 12;     // largest state dimension
 constexpr int MM = 4;      // largest input dimension
 constexpr int MK = MN + MM;
-constexpr int TMAX = 256;  // longest horizon (four wavefronts)
+constexpr int TMAX = 256;  // longest horizon (sixteen wavefronts)
 
 struct MpcInst {
   int32_t T, n, m, box;
@@ -72,8 +74,6 @@ __host__ __device__ constexpr ParOff par_offsets(int N) {
   return o;
 }
 __host__ __device__ constexpr int pad_n(int n) { return n < 4 ? 4 : n; }
-constexpr int PBLK = par_offsets(MN).size + MN;  // parameter block + c = A x0 (floats)
-static_assert(PBLK % 4 == 0, "parameter slots must stay 16-byte aligned");
 
 struct SolveArgs {
   const MpcInst* inst;
@@ -84,7 +84,7 @@ struct SolveArgs {
   float* zout;
   float* uout;          // nullable: final per-edge duals
   int32_t* iters;
-  const int32_t* items; // [n_items][5]: G, id0..id3 (-1 = none)
+  const int32_t* items; // [n_items][MAXW + 1]: mode, instances (-1 = none)
   int32_t n_items;
   int32_t* counter;
   float tol;
@@ -92,426 +92,402 @@ struct SolveArgs {
   float rho;
 };
 
-template <bool LOCK>
-__device__ __forceinline__ void isync() {
-  if constexpr (LOCK) {
-    __syncthreads();
-  } else {
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-  }
-}
-
-
 typedef float f4v __attribute__((ext_vector_type(4)));
+typedef unsigned int u2v __attribute__((ext_vector_type(2)));
 
-// Whole-wavefront shifts by one lane (DPP wave_shr:1 / wave_shl:1): lane t
-// receives lane t-1's (resp. t+1's) value; lane 0 (resp. 63) receives 0.
-// Every lane of the wavefront must be active.
-__device__ __forceinline__ float lane_prev(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xF, 0xF, false));
+// Within each 16-lane row: row_prev / row_next give lane i the value of
+// lane i - 1 / i + 1, the row's first / last lane `edge`; row_last gives
+// lane 0 lane 15's value and row_first gives lane 15 lane 0's.
+template <int CTRL>
+__device__ __forceinline__ float row_dpp(float edge, float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(edge), __float_as_int(v), CTRL,
+                                                    0xF, 0xF, false));
 }
-__device__ __forceinline__ float lane_next(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xF, 0xF, false));
+__device__ __forceinline__ float row_prev(float edge, float v) { return row_dpp<0x111>(edge, v); }
+__device__ __forceinline__ float row_next(float edge, float v) { return row_dpp<0x101>(edge, v); }
+__device__ __forceinline__ float row_last(float v) { return row_dpp<0x121>(v, v); }
+__device__ __forceinline__ float row_first(float v) { return row_dpp<0x12F>(v, v); }
+
+// 4 x 4 transpose between the four 16-lane rows of a wavefront and the four
+// elements of v: element c of row g becomes element g of row c.
+__device__ __forceinline__ f4v row_transpose(f4v v) {
+  auto bits = [](float x) { return __float_as_uint(x); };
+  const u2v a = __builtin_amdgcn_permlane16_swap(bits(v[0]), bits(v[1]), false, false);
+  const u2v b = __builtin_amdgcn_permlane16_swap(bits(v[2]), bits(v[3]), false, false);
+  const u2v c = __builtin_amdgcn_permlane32_swap(a[0], b[0], false, false);
+  const u2v d = __builtin_amdgcn_permlane32_swap(a[1], b[1], false, false);
+  return f4v{__uint_as_float(c[0]), __uint_as_float(d[0]), __uint_as_float(c[1]),
+             __uint_as_float(d[1])};
 }
 
-// out[i] += sum_c P[i*C + c] x[c] for i < R, P in LDS with 16-byte aligned
-// rows of C floats (C % 4 == 0), terms added in c order.  Row i+1 is read
-// while row i is summed; the scheduling barrier per row keeps the compiler
-// from reading every row ahead (the whole block would not fit in registers).
-template <int R, int C>
-__device__ __forceinline__ void mv_rows(const float* P, const float (&x)[C], float (&out)[R]) {
-  f4v cur[C / 4], nxt[C / 4];
+// One instance on the matrix cores.  The three products of the dynamics
+// projection (w = M a, v = S w, M^T v) have the same small matrix for every
+// time step, so sixteen steps are the columns of a v_mfma_f32_16x16x4_f32:
+// lane l holds step l % 16 of a tile and, as MFMA results do, the four
+// components 4 g .. 4 g + 3 of the step's vector for g = l / 16.  Rows
+// g < GX hold the state (N padded to 4 GX), row g = GX the inputs, later
+// rows zeros.  The A operands (M, S, S0, M^T: one register per four columns)
+// stay in registers for the whole solve; a result becomes the next product's
+// B operand through a 4 x 4 transpose between lane rows (four permlane
+// swaps).  The f32 MFMA adds its products one after another with fused
+// rounding, the bits of a chain of fmaf in k order.
+// Every component has three edges: state x_{t+1}: mA on the dynamics edge of
+// x_t (with zA = z of x_t), mB on that of x_{t+1}, mQ on the cost; input:
+// mA dynamics, mB box, mQ cost.
+// A wavefront holds TPW tiles.  LOCK: the workgroup's wavefronts work on
+// consecutive tiles of one instance with one barrier per iteration; else
+// one wavefront holds the whole instance.  FIRST: this wavefront has step 0.
+// LOCK: the stopping rule of iteration k is evaluated while iteration k + 1
+// waits for its first product and published by that iteration's barrier; an
+// iteration whose predecessor met the rule, and the one after the last, are
+// dropped.
+// What bounds it: the issue of about 190 vector instructions and 4 + 2 * 3
+// MFMA of 32 cycles per tile (f32 MFMA and vector instructions share the
+// SIMD), and with one wavefront per SIMD the chain of one iteration (three
+// products, 48 cycles to a result, a transpose each, and the barrier).
+// Latency of one iteration, one instance alone, against one lane per time
+// step with the matrices read from LDS: T = 64, n = 8: 0.74 us (1.73);
+// T = 100, n = 8: 0.95 (2.15); T = 200, n = 12: 1.93 (3.33).  The uneven
+// batch of 4096: 6.9 ms (12.4).
+template <int WV>
+struct LockBuf {
+  f4v first[2][WV + 1][4];   // mA of each wavefront's first step (last entry: zeros)
+  f4v last[2][WV + 1][4];    // mB + mQ of its last step (entry w + 1; entry 0: zeros)
+  int ok[2][WV];             // every edge of the wavefront met the stopping rule
+};
+
+// Whether every wavefront met the stopping rule at iteration it (whose
+// flags a barrier has published).
+template <int WV>
+__device__ __forceinline__ bool all_ok(const LockBuf<WV>* lb, int it) {
+  return __builtin_amdgcn_ballot_w64(lb->ok[it & 1][threadIdx.x & (WV - 1)] == 0) == 0;
+}
+
+template <int TPW>
+struct TileState {
+  f4v mA[TPW], mB[TPW], mQ[TPW], zA[TPW], zB[TPW];
+};
+
+template <int GX, int TPW, bool LOCK, bool FIRST, int WV>
+__device__ __forceinline__ int solve_tiles(const SolveArgs& a, const MpcInst& I, int w,
+                                           LockBuf<WV>* lb) {
+#pragma clang fp contract(off)
+  constexpr int N4 = 4 * GX, K4 = N4 + MM;
+  const int T = I.T, n = I.n, m = I.m;
+  const int k = n + m;  // unpadded step width of z and of the u layout / 3
+  const bool box = I.box != 0;
+  const int N = pad_n(n);
+  const ParOff o = par_offsets(N);
+  const float* __restrict__ P = a.par + I.par_off;
+  const int lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
+  const int t0 = w * TPW * 16;              // the wavefront's first step
+  const bool isx = g < GX, isu = g == GX;
+
+  // A operands: row lane % 16, columns 4 c + g; M and S negated, so that
+  // the first product starts from b and gives -w
+  float Am[GX + 1], As[GX], As0[GX], At[GX];
+  {
+    const int r = col;
 #pragma unroll
-  for (int q = 0; q < C / 4; ++q) cur[q] = ((const f4v*)P)[q];
+    for (int c = 0; c <= GX; ++c) Am[c] = r < N ? -P[o.M + r * K4 + 4 * c + g] : 0.f;
 #pragma unroll
-  for (int i = 0; i < R; ++i) {
-    if (i + 1 < R) {
-#pragma unroll
-      for (int q = 0; q < C / 4; ++q) nxt[q] = ((const f4v*)(P + (i + 1) * C))[q];
+    for (int c = 0; c < GX; ++c) {
+      As[c] = r < N ? -P[o.S + r * N4 + 4 * c + g] : 0.f;
+      As0[c] = FIRST && r < N ? -P[o.S0 + r * N4 + 4 * c + g] : 0.f;
+      At[c] = r < K4 ? P[o.MT + r * N4 + 4 * c + g] : 0.f;
     }
-    float s = out[i];
+  }
+  // per component: cost factor, box bounds (none for states)
+  f4v cq = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int q = 0; q < C / 4; ++q)
+  for (int q = 0; q < 4; ++q) {
+    const int i = 4 * g + q;
+    if (isx && i < N) cq[q] = P[o.cq + i];
+    if (isu) cq[q] = P[o.cr + q];
+  }
+  const float lo = isu ? P[o.lo] : -__builtin_inff(), hi = isu ? P[o.lo + 1] : __builtin_inff();
+  const bool nobox = isu && !box;
+  constexpr float THIRD = 1.f / 3.f;
+  TileState<TPW> s, d;   // before and after an iteration
+  float cz[TPW], cA[TPW];   // z-averages of the own variable and of x_t
+  f4v cvec = {0.f, 0.f, 0.f, 0.f};   // A x0, time step 0 only
 #pragma unroll
-      for (int e = 0; e < 4; ++e) s = fmaf(cur[q][e], x[4 * q + e], s);
-    out[i] = s;
+  for (int j = 0; j < TPW; ++j) {
+    const int t = t0 + 16 * j + col;
+    const bool act = t < T;
+    cz[j] = isu ? (box ? THIRD : 0.5f) : (t + 1 < T ? THIRD : 0.5f);
+    cA[j] = isu ? cz[j] : (t >= 1 && act ? THIRD : 0.f);
+    const float* zi = a.zinit + I.z_off + (int64_t)t * k;
+    const float* ui = a.uinit + I.u_off + (int64_t)t * 3 * k;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int i = 4 * g + q;
+      const bool on = act && (isx ? i < n : (isu && q < m));
+      float vB = 0.f, vA = 0.f, uA = 0.f, uB = 0.f, uQ = 0.f;
+      if (on && a.zinit) {
+        vB = isx ? zi[m + i] : zi[q];
+        vA = isx ? (t >= 1 ? zi[m + i - k] : 0.f) : vB;
+      }
+      if (on && a.uinit) {
+        uA = isx ? (t >= 1 ? ui[i] : 0.f) : ui[n + q];
+        uB = isx ? ui[n + m + i] : ui[2 * n + 2 * m + q];
+        uQ = isx ? ui[2 * n + 3 * m + i] : ui[2 * n + m + q];
+      }
+      s.zB[j][q] = vB;
+      s.zA[j][q] = vA;
+      s.mA[j][q] = uA + vA;
+      s.mB[j][q] = uB + vB;
+      s.mQ[j][q] = uQ + vB;
+    }
+  }
+  const bool step0 = FIRST && col == 0 && isx;   // the edge on x_0 does not exist
+  if (step0) {
+    const float* x0 = a.x0 + I.x0_off;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int i = 4 * g + q;
+      if (i < N) {
+        float s = 0.f;
+        for (int j = 0; j < n; ++j) s = fmaf(P[o.A + i * N + j], x0[j], s);
+        cvec[q] = s;
+      }
+    }
+  }
+
+  const f4v zero4 = {0.f, 0.f, 0.f, 0.f};
+  // What the stopping rule of the last iteration still needs: its x, the
+  // sums its z were made of and the z before.
+  f4v xa[TPW], xb[TPW], xq[TPW], sB[TPW], sA[TPW], zo[TPW];
+#pragma unroll
+  for (int j = 0; j < TPW; ++j) xa[j] = xb[j] = xq[j] = sB[j] = sA[j] = zo[j] = zero4;
+  // |x - z| and |z - z(prev)|, the averages' products rounded with the
+  // differences.  Maxima drop a NaN operand: a NaN in a new z makes chk
+  // NaN, and the rule is then not met.
+  auto met = [&]() {
+    float rmax = 0.f, rbmax = 0.f, smax = 0.f, chk = 0.f;
+#pragma unroll
+    for (int j = 0; j < TPW; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        smax = fmaxf(smax, fabsf(fmaf(cz[j], sB[j][q], -zo[j][q])));
+        rmax = fmaxf(rmax, fmaxf(fabsf(fmaf(-cA[j], sA[j][q], xa[j][q])),
+                                 fabsf(fmaf(-cz[j], sB[j][q], xq[j][q]))));
+        rbmax = fmaxf(rbmax, fabsf(fmaf(-cz[j], sB[j][q], xb[j][q])));
+        chk += s.zB[j][q];
+      }
+    rmax = fmaxf(rmax, nobox ? 0.f : rbmax);
+    return __builtin_amdgcn_ballot_w64(!((rmax <= a.tol) & (smax * a.rho <= a.tol) &
+                                         (chk == chk))) == 0;
+  };
+  int it = 1;
+  bool stop;
+  for (;; ++it) {
+    f4v na[TPW], nb[TPW], nq[TPW], ta[TPW], acc[TPW], sp[TPW];
+    // ---- x-update.  n = z - u = 2z - m on every edge; dynamics:
+    // -w = b - M a - c (c = 0 after step 0), v = S w (S0 w at step 0),
+    // a -= M^T v, b += v.  The separable operators, the m-updates (m = x + u,
+    // u = m - z) and the stopping rule stand where the products are awaited.
+#pragma unroll
+    for (int j = 0; j < TPW; ++j) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        na[j][q] = fmaf(2.f, s.zA[j][q], -s.mA[j][q]);
+        nb[j][q] = fmaf(2.f, s.zB[j][q], -s.mB[j][q]);
+        acc[j][q] = FIRST && j == 0 ? nb[j][q] - cvec[q] : nb[j][q];
+      }
+      ta[j] = row_transpose(na[j]);
+    }
+#pragma unroll
+    for (int c = 0; c <= GX; ++c)
+#pragma unroll
+      for (int j = 0; j < TPW; ++j)
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(Am[c], ta[j][c], acc[j], 0, 0, 0);
+    if constexpr (LOCK) {
+      const bool prev_ok = met() & (it > 1);
+      if (lane == 0) lb->ok[(it - 1) & 1][w] = prev_ok ? 1 : 0;
+    }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int q = 0; q < C / 4; ++q) cur[q] = nxt[q];
+    for (int j = 0; j < TPW; ++j) ta[j] = row_transpose(acc[j]);
+#pragma unroll
+    for (int c = 0; c < GX; ++c)
+#pragma unroll
+      for (int j = 0; j < TPW; ++j)
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(As[c], ta[j][c], c ? acc[j] : zero4, 0, 0, 0);
+    f4v v0 = zero4;
+    if constexpr (FIRST) {
+#pragma unroll
+      for (int c = 0; c < GX; ++c)
+        v0 = __builtin_amdgcn_mfma_f32_16x16x4f32(As0[c], ta[0][c], v0, 0, 0, 0);
+    }
+#pragma unroll
+    for (int j = 0; j < TPW; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float tq = fmaf(2.f, s.zB[j][q], -s.mQ[j][q]);
+        nq[j][q] = cq[q] * tq;
+        d.mQ[j][q] = fmaf(cq[q], tq, s.mQ[j][q] - s.zB[j][q]);
+        d.mB[j][q] = s.mB[j][q] - s.zB[j][q];
+        d.mA[j][q] = s.mA[j][q] - s.zA[j][q];
+      }
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (FIRST) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) acc[0][q] = col == 0 ? v0[q] : acc[0][q];
+    }
+#pragma unroll
+    for (int j = 0; j < TPW; ++j) {
+      // (inputs: v is zero, the box clamps; states: no bounds)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) nb[j][q] = nb[j][q] + acc[j][q];
+      ta[j] = row_transpose(acc[j]);
+    }
+#pragma unroll
+    for (int c = 0; c < GX; ++c)
+#pragma unroll
+      for (int j = 0; j < TPW; ++j)
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(At[c], ta[j][c], c ? acc[j] : zero4, 0, 0, 0);
+#pragma unroll
+    for (int j = 0; j < TPW; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        nb[j][q] = __builtin_amdgcn_fmed3f(nb[j][q], lo, hi);
+        d.mB[j][q] = nb[j][q] + d.mB[j][q];
+      }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < TPW; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        na[j][q] = na[j][q] - acc[j][q];
+        if (FIRST && j == 0) na[j][q] = step0 ? 0.f : na[j][q];
+        d.mA[j][q] = na[j][q] + d.mA[j][q];
+        // first two terms of the own variable's average
+        sp[j][q] = (isu ? d.mA[j][q] : d.mB[j][q]) + d.mQ[j][q];
+      }
+    // ---- neighbours: mA of step t + 1 and the partial sum of step t - 1
+    f4v edge = zero4;
+    if constexpr (LOCK) {
+      if (col == 0) lb->first[it & 1][w][g] = d.mA[0];
+      if (col == 15) lb->last[it & 1][w + 1][g] = sp[TPW - 1];
+      __syncthreads();
+      edge = *(col == 15 ? &lb->first[it & 1][w + 1][g] : &lb->last[it & 1][w][g]);
+      stop = all_ok(lb, it - 1);
+    }
+    // ---- z-update: 3-term averages (x_T and box-free inputs: 2 terms)
+#pragma unroll
+    for (int j = 0; j < TPW; ++j) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float up = row_next(j + 1 < TPW ? row_first(d.mA[j + 1 < TPW ? j + 1 : 0][q]) : edge[q], d.mA[j][q]);
+        const float dn = row_prev(j > 0 ? row_last(sp[j > 0 ? j - 1 : 0][q]) : edge[q], sp[j][q]);
+        sB[j][q] = sp[j][q] + (isu ? (box ? d.mB[j][q] : 0.f) : up);
+        sA[j][q] = isu ? sB[j][q] : dn + d.mA[j][q];
+        d.zB[j][q] = sB[j][q] * cz[j];
+        d.zA[j][q] = sA[j][q] * cA[j];
+      }
+      xa[j] = na[j];
+      xb[j] = nb[j];
+      xq[j] = nq[j];
+      zo[j] = s.zB[j];
+    }
+    if constexpr (LOCK) {
+      if (stop | (it > a.max_iter)) break;
+    }
+    s = d;
+    if constexpr (!LOCK) {
+      stop = met();
+      if (stop | (it >= a.max_iter)) {
+        ++it;
+        break;
+      }
+    }
   }
+#pragma unroll
+  for (int j = 0; j < TPW; ++j) {
+    const int t = t0 + 16 * j + col;
+    if (t >= T) continue;
+    float* zout = a.zout + I.z_off + (int64_t)t * k;
+    // u = m - z with the final z (the state the next solve continues from)
+    float* uo = a.uout + I.u_off + (int64_t)t * 3 * k;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int i = 4 * g + q;
+      if (!(isx ? i < n : (isu && q < m))) continue;
+      zout[isx ? m + i : q] = s.zB[j][q];
+      if (a.uout) {
+        uo[isx ? i : n + q] = isx && t == 0 ? 0.f : s.mA[j][q] - s.zA[j][q];
+        uo[isx ? n + m + i : 2 * n + 2 * m + q] = s.mB[j][q] - s.zB[j][q];
+        uo[isx ? 2 * n + 3 * m + i : 2 * n + m + q] = s.mQ[j][q] - s.zB[j][q];
+      }
+    }
+  }
+  return stop ? it - 1 : -a.max_iter;
 }
 
-// One instance.  LOCK: all four wavefronts of the workgroup work on it in
-// lockstep (t = threadIdx.x); otherwise this wavefront alone (t = lane).
-// xb: first exchange slot of this instance.  red: per-wavefront residuals.
-// N: padded state dimension; inputs are padded to MM = 4.
-template <bool LOCK, int N>
-__device__ __forceinline__ void solve_one(const SolveArgs a, int id, int t, int xb, float* xz,
-                                          float* xm, float* red, float* ps) {
-  constexpr ParOff o = par_offsets(N);
-  const MpcInst I = a.inst[id];
-  const int T = __builtin_amdgcn_readfirstlane(I.T);
-  const int n = __builtin_amdgcn_readfirstlane(I.n);
-  const int m = __builtin_amdgcn_readfirstlane(I.m);
-  const int k = n + m;  // unpadded step width of z and of the u layout / 3
-  const bool box = __builtin_amdgcn_readfirstlane(I.box) != 0;
-  const bool act = t < T;
-  // Stage the parameter block in this instance's LDS slot.
-  {
-    const float* __restrict__ Pg = a.par + __builtin_amdgcn_readfirstlane(I.par_off);
-    const int nthr = LOCK ? (int)blockDim.x : 64;
-    const int tid = LOCK ? (int)threadIdx.x : (int)(threadIdx.x & 63);
-    for (int q = tid; q < o.size; q += nthr) ps[q] = Pg[q];
-  }
-  isync<LOCK>();
-  const float* Pb = ps;
-  const float lo = Pb[o.lo], hi = Pb[o.lo + 1];
-
-  float zu[MM], zx1[N];
-  float mdx[N], mdu[MM], mdx1[N], mqu[MM], mbx[MM], mqx[N];
-  float cvec[N];  // c = A x0, used by time step 0 only
-#pragma unroll
-  for (int i = 0; i < N; ++i) cvec[i] = 0.f;
-#pragma unroll
-  for (int i = 0; i < N; ++i) { zx1[i] = 0.f; mdx[i] = 0.f; mdx1[i] = 0.f; mqx[i] = 0.f; }
-#pragma unroll
-  for (int j = 0; j < MM; ++j) { zu[j] = 0.f; mdu[j] = 0.f; mqu[j] = 0.f; mbx[j] = 0.f; }
-
-  if (act && a.zinit) {
-    const float* zi = a.zinit + I.z_off + (int64_t)t * k;
-#pragma unroll
-    for (int j = 0; j < MM; ++j) if (j < m) zu[j] = zi[j];
-#pragma unroll
-    for (int i = 0; i < N; ++i) if (i < n) zx1[i] = zi[m + i];
-  }
-  // z of x_t, the previous step's x_{t+1} (0 at t = 0).  One wavefront per
-  // instance exchanges neighbours by lane shifts; lockstep wavefronts
-  // through LDS.  The same value is carried across iterations in zxpc.
-  float zxpc[N];
+// One instance; every wavefront of the workgroup takes part when LOCK.
+template <int TPW, bool LOCK, int WV>
+__device__ __forceinline__ void solve_one(const SolveArgs& a, int id, int w, LockBuf<WV>* lb) {
+  MpcInst I = a.inst[id];
+  I.T = __builtin_amdgcn_readfirstlane(I.T);
+  I.n = __builtin_amdgcn_readfirstlane(I.n);
+  I.m = __builtin_amdgcn_readfirstlane(I.m);
+  I.box = __builtin_amdgcn_readfirstlane(I.box);
+  I.par_off = __builtin_amdgcn_readfirstlane(I.par_off);
   if constexpr (LOCK) {
-    if (act) {
-#pragma unroll
-      for (int i = 0; i < N; ++i) xz[(xb + t) * MN + i] = zx1[i];
+    const bool idle = w * 16 >= I.T;
+    if (threadIdx.x < 2 * (WV + 1) * 4) {
+      (&lb->first[0][0][0])[threadIdx.x] = f4v{0.f, 0.f, 0.f, 0.f};
+      (&lb->last[0][0][0])[threadIdx.x] = f4v{0.f, 0.f, 0.f, 0.f};
     }
-    isync<LOCK>();
-#pragma unroll
-    for (int i = 0; i < N; ++i) zxpc[i] = (act && t >= 1) ? xz[(xb + t - 1) * MN + i] : 0.f;
-  } else {
-#pragma unroll
-    for (int i = 0; i < N; ++i) zxpc[i] = lane_prev(zx1[i]);
-  }
-  if (act) {
-    float zxp[N];
-#pragma unroll
-    for (int i = 0; i < N; ++i) zxp[i] = zxpc[i];
-    // m = u + z per edge; u per step laid out [dx n | du m | dx1 n | qu m | bx m | qx n]
-    if (a.uinit) {
-      const float* ui = a.uinit + I.u_off + (int64_t)t * 3 * k;
-#pragma unroll
-      for (int i = 0; i < N; ++i) {
-        if (i < n) {
-          mdx[i] = ui[i];
-          mdx1[i] = ui[n + m + i];
-          mqx[i] = ui[2 * n + 3 * m + i];
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < MM; ++j) {
-        if (j < m) {
-          mdu[j] = ui[n + j];
-          mqu[j] = ui[2 * n + m + j];
-          mbx[j] = ui[2 * n + 2 * m + j];
-        }
+    if ((threadIdx.x & 63) == 0) lb->ok[0][w] = lb->ok[1][w] = idle ? 1 : 0;
+    __syncthreads();
+    if (idle) {
+      // as many barriers as the wavefronts at work
+      for (int it = 1;; ++it) {
+        __syncthreads();
+        if (all_ok(lb, it - 1) | (it > a.max_iter)) return;
       }
     }
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-      mdx[i] += zxp[i];
-      mdx1[i] += zx1[i];
-      mqx[i] += zx1[i];
+    if (w > 0) {
+      if (I.n <= 4) solve_tiles<1, 1, true, false>(a, I, w, lb);
+      else if (I.n <= 8) solve_tiles<2, 1, true, false>(a, I, w, lb);
+      else solve_tiles<3, 1, true, false>(a, I, w, lb);
+      return;
     }
   }
-  if (act) {
-#pragma unroll
-    for (int j = 0; j < MM; ++j) {
-      mdu[j] += zu[j];
-      mqu[j] += zu[j];
-      mbx[j] += zu[j];
-    }
-    if (t == 0) {
-      const float* x0 = a.x0 + I.x0_off;
-      float xv[N];
-#pragma unroll
-      for (int j = 0; j < N; ++j) xv[j] = (j < n) ? x0[j] : 0.f;
-#pragma unroll
-      for (int i = 0; i < N; ++i) {
-        float s = 0.f;
-#pragma unroll
-        for (int j = 0; j < N; ++j) s += Pb[o.A + i * N + j] * xv[j];
-        cvec[i] = s;
-      }
-    }
-  }
-
-  int done_it = -1;
-  const int nw = LOCK ? (T + 63) / 64 : 1;
-  const int w = threadIdx.x >> 6;
-  for (int it = 1; it <= a.max_iter; ++it) {
-    float ax[N], au[MM], bv[N], xqu[MM], xbx[MM], xqx[N];
-    float rloc = 0.f, sloc = 0.f;
-    // The parameter block is re-read from LDS every iteration: an opaque
-    // zero offset keeps the compiler from hoisting several hundred
-    // loop-invariant matrix entries into registers.
-    int zoff;
-    asm volatile("s_mov_b32 %0, 0" : "=s"(zoff));
-    const float* P = Pb + zoff;
-    float zxp[N];
-#pragma unroll
-    for (int i = 0; i < N; ++i) zxp[i] = zxpc[i];
-    if (act) {
-      // ---- x-update.  n = z - u = 2z - m on every edge.
-#pragma unroll
-      for (int i = 0; i < N; ++i) ax[i] = (t >= 1) ? (2.f * zxp[i] - mdx[i]) : 0.f;
-#pragma unroll
-      for (int j = 0; j < MM; ++j) au[j] = 2.f * zu[j] - mdu[j];
-#pragma unroll
-      for (int i = 0; i < N; ++i) bv[i] = 2.f * zx1[i] - mdx1[i];
-      // dynamics: w = M a + c - b; v = S w (S0 at t = 0); a -= M^T v; b += v
-      constexpr int N4 = o.N4, K4 = o.K4;
-      float xa[K4], wv[N], wp[N4], vv[N], vp[N4], sx[N], su[MM];
-#pragma unroll
-      for (int c = 0; c < K4; ++c) xa[c] = c < N ? ax[c < N ? c : 0] : (c >= N4 ? au[c >= N4 ? c - N4 : 0] : 0.f);
-#pragma unroll
-      for (int i = 0; i < N; ++i) wv[i] = cvec[i] - bv[i];
-      mv_rows<N, K4>(P + o.M, xa, wv);
-#pragma unroll
-      for (int c = 0; c < N4; ++c) wp[c] = c < N ? wv[c < N ? c : 0] : 0.f;
-#pragma unroll
-      for (int i = 0; i < N; ++i) vv[i] = 0.f;
-      mv_rows<N, N4>(P + ((t >= 1) ? o.S : o.S0), wp, vv);
-#pragma unroll
-      for (int c = 0; c < N4; ++c) vp[c] = c < N ? vv[c < N ? c : 0] : 0.f;
-#pragma unroll
-      for (int i = 0; i < N; ++i) sx[i] = 0.f;
-#pragma unroll
-      for (int j = 0; j < MM; ++j) su[j] = 0.f;
-      mv_rows<N, N4>(P + o.MT, vp, sx);
-      mv_rows<MM, N4>(P + o.MT + N4 * N4, vp, su);
-#pragma unroll
-      for (int j = 0; j < N; ++j) ax[j] -= sx[j];
-#pragma unroll
-      for (int j = 0; j < MM; ++j) au[j] -= su[j];
-#pragma unroll
-      for (int i = 0; i < N; ++i) bv[i] += vv[i];
-      // separable costs and the box
-#pragma unroll
-      for (int j = 0; j < MM; ++j) {
-        xqu[j] = P[o.cr + j] * (2.f * zu[j] - mqu[j]);
-        const float nb = 2.f * zu[j] - mbx[j];
-        xbx[j] = nb < lo ? lo : (nb > hi ? hi : nb);
-      }
-#pragma unroll
-      for (int i = 0; i < N; ++i) xqx[i] = P[o.cq + i] * (2.f * zx1[i] - mqx[i]);
-      // ---- m-update: m = x + u, u = m_old - z_old
-#pragma unroll
-      for (int i = 0; i < N; ++i) {
-        mdx[i] = ax[i] + (mdx[i] - zxp[i]);
-        mdx1[i] = bv[i] + (mdx1[i] - zx1[i]);
-        mqx[i] = xqx[i] + (mqx[i] - zx1[i]);
-      }
-#pragma unroll
-      for (int j = 0; j < MM; ++j) {
-        mdu[j] = au[j] + (mdu[j] - zu[j]);
-        mqu[j] = xqu[j] + (mqu[j] - zu[j]);
-        mbx[j] = xbx[j] + (mbx[j] - zu[j]);
-      }
-    }
-    // From step t+1 (lane t+1): the m and the x of its dynamics edge on
-    // x_{t+1}.  Lane shifts inside a wavefront; in lockstep mode lane 63
-    // takes them from the next wavefront's lane 0 through LDS.
-    float xmn[N], axn[N];
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-      xmn[i] = lane_next(mdx[i]);
-      axn[i] = lane_next(ax[i]);
-    }
-    if constexpr (LOCK) {
-      if ((t & 63) == 0) {
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-          xm[w * 2 * MN + i] = mdx[i];
-          xm[w * 2 * MN + MN + i] = ax[i];
-        }
-      }
-      __syncthreads();
-      if ((t & 63) == 63 && w + 1 < nw) {
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-          xmn[i] = xm[(w + 1) * 2 * MN + i];
-          axn[i] = xm[(w + 1) * 2 * MN + MN + i];
-        }
-      }
-    }
-    float zx1n[N];
-#pragma unroll
-    for (int i = 0; i < N; ++i) zx1n[i] = 0.f;
-    // residual maxima use v_max (which drops NaN): a NaN in this step's new
-    // z makes chk NaN, and the step then reports an infinite residual
-    float chk = 0.f;
-    if (act) {
-      // ---- z-update: 3-term averages (x_T and box-free inputs: 2 terms).
-      // The residual of step t+1's dynamics edge on x_{t+1} is taken here,
-      // where the new z of x_{t+1} is.
-      const bool nxt = (t + 1 < T);
-#pragma unroll
-      for (int i = 0; i < N; ++i) {
-        float s = mdx1[i] + mqx[i];
-        if (nxt) s += xmn[i];
-        const float zn = s * (nxt ? (1.f / 3.f) : 0.5f);
-        sloc = fmaxf(sloc, fabsf(zn - zx1[i]));
-        rloc = fmaxf(rloc, fmaxf(fabsf(bv[i] - zn), fabsf(xqx[i] - zn)));
-        if (nxt) rloc = fmaxf(rloc, fabsf(axn[i] - zn));
-        zx1n[i] = zn;
-        chk += zn;
-      }
-#pragma unroll
-      for (int j = 0; j < MM; ++j) {
-        const float s = box ? (mdu[j] + mqu[j] + mbx[j]) : (mdu[j] + mqu[j]);
-        const float zn = s * (box ? (1.f / 3.f) : 0.5f);
-        sloc = fmaxf(sloc, fabsf(zn - zu[j]));
-        float r = fmaxf(fabsf(au[j] - zn), fabsf(xqu[j] - zn));
-        if (box) r = fmaxf(r, fabsf(xbx[j] - zn));
-        rloc = fmaxf(rloc, r);
-        chk += zn;
-        zu[j] = zn;
-      }
-#pragma unroll
-      for (int i = 0; i < N; ++i) zx1[i] = zx1n[i];
-    }
-    // next iteration's z of x_t: the new z of step t-1 (lane t-1); in
-    // lockstep mode lane 0 takes it from the previous wavefront's lane 63
-    // through LDS, across the barrier of the stopping-rule reduction
-#pragma unroll
-    for (int i = 0; i < N; ++i) zxpc[i] = lane_prev(zx1n[i]);
-    if constexpr (LOCK) {
-      if ((t & 63) == 63) {
-#pragma unroll
-        for (int i = 0; i < N; ++i) xz[w * MN + i] = zx1n[i];
-      }
-    }
-    if (!(chk == chk)) rloc = __builtin_inff();
-    // ---- stopping rule, reduced over the instance
-    float r = admmi::wave_max_nonneg(rloc), s = admmi::wave_max_nonneg(sloc);
-    if constexpr (LOCK) {
-      if ((threadIdx.x & 63) == 0) { red[2 * w] = r; red[2 * w + 1] = s; }
-      __syncthreads();
-      r = red[0];
-      s = red[1];
-      for (int q = 1; q < nw; ++q) { r = fmaxf(r, red[2 * q]); s = fmaxf(s, red[2 * q + 1]); }
-      if ((t & 63) == 0 && w >= 1) {
-#pragma unroll
-        for (int i = 0; i < N; ++i) zxpc[i] = xz[(w - 1) * MN + i];
-      }
-    }
-    s *= a.rho;
-    if (r <= a.tol && s <= a.tol) {
-      done_it = it;
-      break;
-    }
-  }
-  if (act) {
-    float* zo = a.zout + I.z_off + (int64_t)t * k;
-#pragma unroll
-    for (int j = 0; j < MM; ++j) if (j < m) zo[j] = zu[j];
-#pragma unroll
-    for (int i = 0; i < N; ++i) if (i < n) zo[m + i] = zx1[i];
-    if (a.uout) {
-      // u = m - z with the final z (the state the next solve continues from);
-      // zxpc already holds the final z of x_t
-      float* uo = a.uout + I.u_off + (int64_t)t * 3 * k;
-#pragma unroll
-      for (int i = 0; i < N; ++i) {
-        if (i < n) {
-          uo[i] = t >= 1 ? mdx[i] - zxpc[i] : 0.f;
-          uo[n + m + i] = mdx1[i] - zx1[i];
-          uo[2 * n + 3 * m + i] = mqx[i] - zx1[i];
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < MM; ++j) {
-        if (j < m) {
-          uo[n + j] = mdu[j] - zu[j];
-          uo[2 * n + m + j] = mqu[j] - zu[j];
-          uo[2 * n + 2 * m + j] = mbx[j] - zu[j];
-        }
-      }
-    }
-  }
-  if (t == 0) a.iters[id] = done_it > 0 ? done_it : -a.max_iter;
+  int it;
+  if (I.n <= 4) it = solve_tiles<1, TPW, LOCK, true>(a, I, 0, lb);
+  else if (I.n <= 8) it = solve_tiles<2, TPW, LOCK, true>(a, I, 0, lb);
+  else it = solve_tiles<3, TPW, LOCK, true>(a, I, 0, lb);
+  if ((threadIdx.x & 63) == 0) a.iters[id] = it;
 }
 
-template <bool LOCK>
-__device__ __forceinline__ void solve_dispatch(const SolveArgs a, int id, int t, int xb, float* xz,
-                                               float* xm, float* red, float* ps) {
-  const int N = pad_n(__builtin_amdgcn_readfirstlane(a.inst[id].n));
-  switch (N) {
-    case 4: solve_one<LOCK, 4>(a, id, t, xb, xz, xm, red, ps); break;
-    case 5: solve_one<LOCK, 5>(a, id, t, xb, xz, xm, red, ps); break;
-    case 6: solve_one<LOCK, 6>(a, id, t, xb, xz, xm, red, ps); break;
-    case 7: solve_one<LOCK, 7>(a, id, t, xb, xz, xm, red, ps); break;
-    case 8: solve_one<LOCK, 8>(a, id, t, xb, xz, xm, red, ps); break;
-    case 9: solve_one<LOCK, 9>(a, id, t, xb, xz, xm, red, ps); break;
-    case 10: solve_one<LOCK, 10>(a, id, t, xb, xz, xm, red, ps); break;
-    case 11: solve_one<LOCK, 11>(a, id, t, xb, xz, xm, red, ps); break;
-    default: solve_one<LOCK, 12>(a, id, t, xb, xz, xm, red, ps); break;
-  }
-}
-
-// WG threads per workgroup: WG/64 one-wavefront instances, or one instance
-// of up to WG/64 lockstep wavefronts, per work item.  The register budget
-// is held at two waves per SIMD for both sizes.
-template <int WG>
-__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2, 2))) void mpc_solve_kernel(
-    const MpcInst* __restrict__ inst, const float* __restrict__ par, const float* __restrict__ x0,
-    const float* __restrict__ zinit, const float* __restrict__ uinit, float* __restrict__ zout,
-    float* __restrict__ uout, int32_t* __restrict__ iters, const int32_t* __restrict__ items,
-    int32_t n_items, int32_t* __restrict__ counter, float tol, int32_t max_iter, float rho) {
-  SolveArgs a;
-  a.inst = inst;
-  a.par = par;
-  a.x0 = x0;
-  a.zinit = zinit;
-  a.uinit = uinit;
-  a.zout = zout;
-  a.uout = uout;
-  a.iters = iters;
-  a.items = items;
-  a.n_items = n_items;
-  a.counter = counter;
-  a.tol = tol;
-  a.max_iter = max_iter;
-  a.rho = rho;
-  __shared__ float xz[WG * MN];
-  __shared__ float xm[WG * MN];
-  __shared__ float red[8];
-  __shared__ __align__(16) float ps[(WG / 64) * PBLK];   // rows read as 16-byte vectors
+// Work items (MAXW + 1 numbers): 0 and up to WV instances of T <= T1, one
+// wavefront each; or 1 and an instance for the whole workgroup, one tile per
+// wavefront.  WV = 8 serves batches whose T are all at most TS (two
+// workgroups per CU), WV = 16 the others (one).
+template <int WV>
+__global__ __launch_bounds__(WV * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
+mpc_solve_kernel(SolveArgs a) {
+  __shared__ LockBuf<WV> lb;
   __shared__ int s_item;
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   for (;;) {
     if (threadIdx.x == 0) s_item = atomicAdd(a.counter, 1);
     __syncthreads();
     const int item = __builtin_amdgcn_readfirstlane(s_item);
     __syncthreads();
     if (item >= a.n_items) break;
-    const int G = __builtin_amdgcn_readfirstlane(a.items[5 * item]);
-    if (G == 1) {
-      const int id = __builtin_amdgcn_readfirstlane(a.items[5 * item + 1 + w]);
-      if (id >= 0) solve_dispatch<false>(a, id, lane, w * 64, xz, xm, red, ps + w * PBLK);
+    const int32_t* it = a.items + (int64_t)(MAXW + 1) * item;
+    if (__builtin_amdgcn_readfirstlane(it[0]) == 0) {
+      const int id = __builtin_amdgcn_readfirstlane(it[1 + w]);
+      if (id >= 0) {
+        if (__builtin_amdgcn_readfirstlane(a.inst[id].T) <= 16) solve_one<1, false>(a, id, 0, &lb);
+        else solve_one<2, false>(a, id, 0, &lb);
+      }
     } else {
-      const int id = __builtin_amdgcn_readfirstlane(a.items[5 * item + 1]);
-      solve_dispatch<true>(a, id, threadIdx.x, 0, xz, xm, red, ps);
+      solve_one<1, true>(a, __builtin_amdgcn_readfirstlane(it[1]), w, &lb);
     }
     __syncthreads();
   }
@@ -621,7 +597,7 @@ __global__ __launch_bounds__(64) void mpc_dual_kernel(const MpcInst* inst, int32
 // edge, so that part of step 1 is dropped) and the new last step's duals are
 // zero; the duals around every variable keep their sum.
 // One workgroup per instance, one thread per step (T <= 256).
-__global__ __launch_bounds__(WGT) void mpc_shift_kernel(
+__global__ __launch_bounds__(TMAX) void mpc_shift_kernel(
     const MpcInst* __restrict__ inst, const float* __restrict__ par, const float* __restrict__ x0,
     const float* __restrict__ z, const float* __restrict__ u, const float* __restrict__ w,
     float* __restrict__ x0n, float* __restrict__ zn, float* __restrict__ un) {
@@ -693,7 +669,7 @@ std::vector<double> inv_spd(std::vector<double> a, int n) {
 }
 
 struct Plan {
-  int pack1 = 4;  // instances per workgroup when T <= 64
+  int pack1 = 4;  // instances of T <= T1 per four wavefronts (1: per workgroup)
   int order = 1;  // 0 as given, 1 longest first, 2 by (n, m) then longest first,
                   // 3 longest measured solve first (iterations of the last tuning solve)
   int grid = 0;   // persistent workgroups; 0: resident capacity
@@ -715,7 +691,8 @@ struct admm_mpc_batch {
   int32_t* d_counter = nullptr;
   Plan plan;
   int resident = 0;          // workgroups resident per device at full occupancy
-  int wg = WGT;              // threads per workgroup of the persistent launch
+  bool short_h = false;      // every T <= TS
+  int cus = 1;
   std::vector<int32_t> measured;  // iterations per instance from the last tuning solve
   std::vector<void*> allocs;
   ~admm_mpc_batch() {
@@ -734,9 +711,12 @@ admm_status mpc_alloc(admm_mpc_batch* b, void** p, size_t bytes) {
   return ADMM_OK;
 }
 
-// Work items for a plan: instances of more than 64 steps get a workgroup of
-// their own; shorter ones are packed pack1 to a workgroup (one wavefront
-// each).  Items are ordered by the plan's order key.
+// Work items for a plan: instances of more than T1 steps get a workgroup of
+// their own; shorter ones take one wavefront each, pack1 to every four
+// wavefronts of a workgroup, but no more than it takes to give every CU a
+// workgroup (a lone wavefront has a SIMD to itself).  One instance per
+// workgroup and more than one tile: in lockstep (0.75 against 1.0 us per
+// iteration at T = 20).  Items are ordered by the plan's order key.
 admm_status build_items(admm_mpc_batch* b, const Plan& pl) {
   std::vector<int32_t> ids(b->n_inst);
   std::iota(ids.begin(), ids.end(), 0);
@@ -745,14 +725,14 @@ admm_status build_items(admm_mpc_batch* b, const Plan& pl) {
     return (double)I.T * (2.0 * I.n * (I.n + I.m) + I.n * I.n + 8.0 * (I.n + I.m));
   };
   // expected duration of a solve: measured iterations x the latency of one
-  // iteration, which grows with the padded state size and with the number
-  // of lockstep wavefronts (fitted to single-instance timings)
+  // iteration, which grows with the products' size and with the wavefronts
+  // per SIMD (fitted to single-instance timings: 0.74 us at T = 64, n = 8,
+  // 1.24 at T = 114, n = 9, 1.93 at T = 200, n = 12)
   auto duration = [&](int i) {
     const MpcInst& I = b->h_inst[i];
-    const double Np = I.n < 4 ? 4.0 : (double)I.n;
-    const int G = (I.T + 63) / 64;
+    const double gx = (I.n + 3) / 4, wps = (I.T + 63) / 64;
     const double it = std::max<int32_t>(1, std::abs(b->measured[i]));
-    return it * (0.6 + 0.016 * Np * Np + 0.3 * (G - 1));
+    return it * (0.45 + 0.05 * gx + wps * (0.1 + 0.08 * gx));
   };
   if (pl.order == 3 && (int)b->measured.size() == b->n_inst) {
     std::stable_sort(ids.begin(), ids.end(),
@@ -771,27 +751,26 @@ admm_status build_items(admm_mpc_batch* b, const Plan& pl) {
   std::vector<int32_t> pend;
   auto flush = [&]() {
     if (pend.empty()) return;
-    items.push_back(1);
-    for (int q = 0; q < 4; ++q) items.push_back(q < (int)pend.size() ? pend[q] : -1);
+    items.push_back(0);
+    for (int q = 0; q < MAXW; ++q) items.push_back(q < (int)pend.size() ? pend[q] : -1);
     pend.clear();
   };
-  // a workgroup holds at most wg/64 one-wavefront instances
-  const int pack = std::min(pl.pack1, b->wg / 64);
+  int n_short = 0;
+  for (const MpcInst& I : b->h_inst) n_short += I.T <= T1;
+  const int share = pl.pack1 == 1 ? 1 : pl.pack1 * (b->short_h ? TS / 16 : MAXW) / 4;
+  const int pack = std::max(1, std::min(share, (n_short + b->cus - 1) / b->cus));
   for (int32_t i : ids) {
-    const int G = (b->h_inst[i].T + 63) / 64;
-    if (G == 1) {
+    if (b->h_inst[i].T <= (pack > 1 ? T1 : 16)) {
       pend.push_back(i);
       if ((int)pend.size() == pack) flush();
     } else {
-      items.push_back(G);
+      items.push_back(1);
       items.push_back(i);
-      items.push_back(-1);
-      items.push_back(-1);
-      items.push_back(-1);
+      for (int q = 1; q < MAXW; ++q) items.push_back(-1);
     }
   }
   flush();
-  b->n_items = (int32_t)(items.size() / 5);
+  b->n_items = (int32_t)(items.size() / (MAXW + 1));
   ADMM_HIP(hipMemcpy(b->d_items, items.data(), items.size() * sizeof(int32_t), hipMemcpyHostToDevice));
   b->plan = pl;
   return ADMM_OK;
@@ -818,10 +797,8 @@ admm_status launch_solve(admm_mpc_batch* b, const float* x0, const float* zinit,
   a.rho = (float)b->rho;
   int grid = b->plan.grid > 0 ? b->plan.grid : b->resident;
   grid = std::max(1, std::min(grid, b->n_items));
-  hipExtLaunchKernelGGL(b->wg == WGS ? mpc_solve_kernel<WGS> : mpc_solve_kernel<WGT>, dim3(grid),
-                        dim3(b->wg), 0, st, e0, e1, 0,
-                        (const MpcInst*)a.inst, a.par, a.x0, a.zinit, a.uinit, a.zout, a.uout,
-                        a.iters, a.items, a.n_items, a.counter, a.tol, a.max_iter, a.rho);
+  hipExtLaunchKernelGGL(b->short_h ? mpc_solve_kernel<TS / 16> : mpc_solve_kernel<MAXW>, dim3(grid),
+                        dim3(b->short_h ? TS * 4 : MAXW * 64), 0, st, e0, e1, 0, a);
   ADMM_HIP(hipGetLastError());
   return ADMM_OK;
 }
@@ -929,20 +906,20 @@ admm_status admm_mpc_batch_create(int32_t n_inst, const int32_t* T, const int32_
   if ((s = mpc_alloc(b.get(), (void**)&b->d_inst, sizeof(MpcInst) * n_inst))) return s;
   if ((s = mpc_alloc(b.get(), (void**)&b->d_par, sizeof(float) * par.size()))) return s;
   if ((s = mpc_alloc(b.get(), (void**)&b->d_u, sizeof(float) * b->u_total))) return s;
-  if ((s = mpc_alloc(b.get(), (void**)&b->d_items, sizeof(int32_t) * 5 * (size_t)n_inst))) return s;
+  if ((s = mpc_alloc(b.get(), (void**)&b->d_items, sizeof(int32_t) * (MAXW + 1) * (size_t)n_inst))) return s;
   if ((s = mpc_alloc(b.get(), (void**)&b->d_counter, sizeof(int32_t)))) return s;
   ADMM_HIP(hipMemcpy(b->d_inst, b->h_inst.data(), sizeof(MpcInst) * n_inst, hipMemcpyHostToDevice));
   ADMM_HIP(hipMemcpy(b->d_par, par.data(), sizeof(float) * par.size(), hipMemcpyHostToDevice));
-  int per_cu = 0, cus = 0;
+  int per_cu = 0;
   int maxT = 0;
   for (int32_t i = 0; i < n_inst; ++i) maxT = std::max(maxT, (int)T[i]);
-  b->wg = maxT <= WGS ? WGS : WGT;
-  if (b->wg == WGS)
-    ADMM_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, mpc_solve_kernel<WGS>, WGS, 0));
+  b->short_h = maxT <= TS;
+  if (b->short_h)
+    ADMM_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, mpc_solve_kernel<TS / 16>, TS * 4, 0));
   else
-    ADMM_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, mpc_solve_kernel<WGT>, WGT, 0));
-  ADMM_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device));
-  b->resident = std::max(1, per_cu) * std::max(1, cus);
+    ADMM_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, mpc_solve_kernel<MAXW>, MAXW * 64, 0));
+  ADMM_HIP(hipDeviceGetAttribute(&b->cus, hipDeviceAttributeMultiprocessorCount, device));
+  b->resident = std::max(1, per_cu) * std::max(1, b->cus);
   if ((s = build_items(b.get(), Plan()))) return s;
   *out = b.release();
   return ADMM_OK;
@@ -1013,7 +990,7 @@ admm_status admm_mpc_batch_shift(admm_mpc_batch* b, const float* x0, const float
   if (x0_next == x0 || (z_next && z_next == z) || (u_next && u_next == u))
     return admmi::set_err(ADMM_E_ARG, "outputs must not overlap the inputs");
   ADMM_HIP(hipSetDevice(b->device));
-  mpc_shift_kernel<<<b->n_inst, WGT, 0, (hipStream_t)stream>>>(b->d_inst, b->d_par, x0, z, u, w,
+  mpc_shift_kernel<<<b->n_inst, TMAX, 0, (hipStream_t)stream>>>(b->d_inst, b->d_par, x0, z, u, w,
                                                               x0_next, z_next, u_next);
   ADMM_HIP(hipGetLastError());
   return ADMM_OK;

@@ -1,0 +1,54 @@
+"""The batched MPC solver at the edges of its sixteen-step tiles: horizons
+around multiples of 16 and of the wavefronts of a workgroup, state sizes
+around multiples of four, against the FP64 oracle after 50 iterations (FP32
+rounding of 50 contracting iterations: 1e-4, as for the other shapes); and
+instances that share a workgroup, one wavefront each, against the same
+instances on workgroups of their own (the same arithmetic: equal bits)."""
+import numpy as np
+import pytest
+
+import oracle as O
+import workloads as W
+from tests.helpers import rel
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def _solve(insts, tol, max_iter, pack=None):
+    from paper_1603_02526_amd import mpc as M
+    b = M.MPCBatch(insts)
+    if pack is not None:
+        b.set_plan(pack, 0, 0)
+    x0 = torch.tensor(b.pack_x0([i.x0 for i in insts]), device="cuda")
+    z = torch.zeros(b.z_total, dtype=torch.float32, device="cuda")
+    u = torch.zeros(b.u_total, dtype=torch.float32, device="cuda")
+    it = torch.zeros(b.n_inst, dtype=torch.int32, device="cuda")
+    b.solve_state(x0, z, it, u_out=u, tol=tol, max_iter=max_iter)
+    torch.cuda.synchronize()
+    return b, z.cpu().numpy(), u.cpu().numpy(), it.cpu().numpy()
+
+
+@pytest.mark.parametrize("n,m,box", [(1, 1, 1.0), (4, 2, 0.0), (5, 3, 1.0), (8, 4, 1.0), (9, 1, 0.5), (12, 4, 1.0)])
+@pytest.mark.parametrize("long_batch", [False, True])
+def test_tile_edges_match_oracle(n, m, box, long_batch):
+    rng = np.random.default_rng(100 + n)
+    insts = []
+    for T in (1, 15, 16, 17, 31, 32, 33, 48, 127, 128) + ((129, 144, 255, 256) if long_batch else ()):
+        A, B = W.mpc_system(rng, n, m)
+        insts.append(W.MPCInstance(T, n, m, A, B, rng.standard_normal(n), np.ones(n), np.full(m, 0.1), box))
+    b, z, _, it = _solve(insts, 1e-30, 50)
+    assert np.all(it == -50)
+    for inst, zi in zip(insts, b.split_z(z)):
+        g = O.OracleGraph(W.mpc_graph(inst, box=box > 0))
+        g.run(50)
+        assert rel(zi.astype(np.float64), g.z) < 1e-4, (inst.T, rel(zi.astype(np.float64), g.z))
+
+
+@pytest.mark.parametrize("t_range", [(1, 16), (10, 32)])
+def test_shared_workgroups_change_nothing(t_range):
+    insts = W.mpc_batch(700, seed=71, T_range=t_range)
+    _, z, u, it = _solve(insts, 1e-4, 400, pack=4)
+    _, z1, u1, it1 = _solve(insts, 1e-4, 400, pack=1)
+    assert np.array_equal(it, it1) and np.array_equal(z, z1) and np.array_equal(u, u1)

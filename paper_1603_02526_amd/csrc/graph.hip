@@ -245,11 +245,34 @@ bool detect_complete_pairs(const admm_graph& g, const Group& gr, std::vector<int
   return true;
 }
 
-// Hinge and margin factors take up to NT - 1 weight components: one
-// register per component up to 64 (dmax 32 or 64), two sweeps over memory
-// above that (dmax 0).
+// Hinge and margin factors take up to NT - 1 weight components; factors
+// without a shared variable list keep one register per component up to 64
+// (dmax 32 or 64) and make two sweeps over memory above that (dmax 0).
 constexpr int HINGE_DMAX = NT - 1;
 int hinge_dmax(int d) { return d <= 32 ? 32 : d <= 64 ? 64 : 0; }
+
+// Lanes per row of factors of the shared-variable hinge (xpass_hinge_tile;
+// v factors per 16 bytes).  NT / fl lanes share a factor's d + 1 edges, at
+// most eight each; of the shapes that allow that, the one with the most
+// factors per workgroup (fewest partial sums) that still gives every CU a
+// workgroup; buckets under MIN_SLOTS edge slots keep the fewest workgroups
+// (1500 x 3: 4.6 us per iteration, split 4.9; at 4000 x 15 the split gives
+// 5.4 against 5.6).  Iterations with at least 256 / 512 / 1024 workgroups where
+// there are that many, FP32: 30,000 x 50 7.1 / 7.9 / 8.0 us, 100,000 x 8
+// 6.0 / 6.6 / 8.3, 100,000 x 20 8.2 / 7.9 / 10.0, 10,000 x 200 9.2 / 9.5 /
+// 9.3.  In a plan for the resident driver (one workgroup, its LDS image) the
+// rows must not need more padding than to 64 factors.
+int hinge_lanes(int64_t n, int d, int v, bool resident) {
+  constexpr int64_t MIN_BLOCKS = 256, MIN_SLOTS = 40000;
+  int fl = 64;
+  while (fl > 8 && (d + NT / fl) / (NT / fl) > 8) fl /= 2;
+  if (resident) {
+    while (fl > 8 && round_up(n, fl * v) > round_up(n, 64)) fl /= 2;
+  } else if (n * (d + 1) >= MIN_SLOTS) {
+    while (fl > 8 && (n + fl * v - 1) / (fl * v) < MIN_BLOCKS) fl /= 2;
+  }
+  return fl;
+}
 
 constexpr int32_t DEFAULT_T_LPB = 32;   // transposed lists per z-pass block (measured best of 16, 32, 64)
 
@@ -456,38 +479,33 @@ admm_status build_plan(admm_graph& g, Plan& P, bool no_tiles) {
       // ---------------- hinge, shared variable list ----------------
       b.mode = BM_UNIF_HINGE;
       b.d = gr.arity - 1;
-      b.dmax = hinge_dmax(b.d);
       b.n = gr.n;
-      // d < 32: four lanes per four factors in FP32 with alpha = 1 (NT
-      // factors per workgroup, rows padded to whole workgroups so that every
-      // 16-byte access stays in its row), else two lanes per factor (NT / 2)
-      // (not in a plan built for the resident driver, whose LDS image keeps
-      // the rows at their 64-factor padding)
-      b.quad = (b.dmax == 32 && b.d < 32 && g.precision == ADMM_FP32 && P.alpha_one &&
-                !P.no_tiles) ? 1 : 0;
-      b.nfp = round_up(gr.n, b.quad ? NT : 64);
+      const int d = b.d, v = g.precision == ADMM_FP64 ? 2 : 4;
+      b.fl = hinge_lanes(gr.n, d, v, P.no_tiles);
+      const int64_t FB = (int64_t)b.fl * v;   // factors per workgroup
+      const int64_t tiles = (gr.n + FB - 1) / FB;
+      b.nfp = tiles * FB;
       b.nslot = gr.arity;
-      for (int e = 0; e < gr.arity; ++e) P.idx.push_back((int32_t)zof(0, e));
-      const int d = b.d;
-      if (b.quad) {
-        // 16-byte aligned parameter rows
-        P.par.resize((size_t)round_up((int64_t)P.par.size(), 4), 0.0);
-        b.par_off = (int64_t)P.par.size();
+      b.zaff = (int32_t)zof(0, 0);
+      for (int e = 0; e < gr.arity; ++e) {
+        P.idx.push_back((int32_t)zof(0, e));
+        if (zof(0, e) != zof(0, 0) + e) b.zaff = -1;
       }
+      // state and parameters per workgroup: [edge][FB], 16-byte aligned
+      P.par.resize((size_t)round_up((int64_t)P.par.size(), 4), 0.0);
+      b.par_off = (int64_t)P.par.size();
       P.par.resize(P.par.size() + (size_t)(d + 3) * b.nfp, 0.0);
-      double* par = P.par.data() + b.par_off;
       for (int64_t f = 0; f < gr.n; ++f) {
+        double* par = P.par.data() + b.par_off + f / FB * (d + 3) * FB + f % FB;
         const double* p = gr.prm(f);
         const double y = p[d], C = p[d + 1];
         double aa = 0.0;
-        for (int k = 0; k < d; ++k) { par[k * b.nfp + f] = y * p[k]; aa += p[k] * p[k]; }
-        par[d * b.nfp + f] = y;
-        par[(d + 1) * b.nfp + f] = C;
-        par[(d + 2) * b.nfp + f] = rg / (aa + 1.0);
+        for (int k = 0; k < d; ++k) { par[k * FB] = y * p[k]; aa += p[k] * p[k]; }
+        par[d * FB] = y;
+        par[(d + 1) * FB] = C;
+        par[(d + 2) * FB] = rg / (aa + 1.0);
       }
       P.n_m += (int64_t)gr.arity * b.nfp;
-      const int64_t fpb = b.quad ? NT : (b.dmax == 32 ? NT / 2 : NT);
-      const int64_t tiles = (gr.n + fpb - 1) / fpb;
       b.dst_off = (int64_t)P.idx.size();
       P.idx.resize(P.idx.size() + tiles * gr.arity, -1);
       b.blk0 = (int32_t)blocks;
@@ -497,7 +515,7 @@ admm_status build_plan(admm_graph& g, Plan& P, bool no_tiles) {
         for (int e = 0; e < gr.arity; ++e) em.push_back({zof(0, e), b.dst_off + t * gr.arity + e});
       for (int64_t f = 0; f < gr.n; ++f)
         for (int e = 0; e < gr.arity; ++e) {
-          P.upos[us] = b.m_off + (int64_t)e * b.nfp + f;
+          P.upos[us] = b.m_off + (f / FB * gr.arity + e) * FB + f % FB;
           P.uz[us] = (int32_t)zof(f, e);
           deg[zof(f, e)] += rw; rmz[zof(f, e)] = std::max(rmz[zof(f, e)], rg);
           ++us;

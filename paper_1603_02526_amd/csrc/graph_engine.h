@@ -173,11 +173,9 @@ struct Engine : EngineBase {
       int need = 0;
       for (const BucketDesc& b : P.bt) {
         if (b.mode == BM_PAIR) need |= b.sparse ? FT_PAIRSP : FT_PAIR;
+        else if (b.mode == BM_UNIF_HINGE) need |= FT_UHINGE;
         else if ((b.kind == KD_HINGE || b.kind == KD_MARGIN) && b.dmax == 0) need |= FT_XWIDE;
-        else if (b.mode == BM_UNIF_HINGE && b.dmax == 32) need |= FT_UHINGE;
-        else if ((b.mode == BM_UNIF_HINGE || b.kind == KD_HINGE || b.kind == KD_MARGIN) &&
-                 b.dmax == 64)
-          need |= FT_W64;
+        else if ((b.kind == KD_HINGE || b.kind == KD_MARGIN) && b.dmax == 64) need |= FT_W64;
         else if (b.mode == BM_GEN_SLOT || b.kind == KD_NONOVERLAP || b.kind == KD_WALL ||
                  b.kind == KD_EQUAL)
           need |= FT_GEN;

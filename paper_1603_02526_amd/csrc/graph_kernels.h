@@ -62,8 +62,8 @@ struct BucketDesc {
                         // of the bucket, which takes one partial sum per workgroup
   int32_t tri;          // pair layout: 64-row tiles in row-major order of the whole
                         // upper triangle (J >= I), so (I, J) follows from the tile index
-  int32_t quad;         // shared-variable hinge: four factors per lane (FP32, alpha = 1)
-  int32_t quad_pad;
+  int32_t fl;           // shared-variable hinge: lanes per row of factors (FL)
+  int32_t zaff;         // shared-variable hinge: z offset of edge k is zaff + k (-1: a list)
   int64_t m_off, x_off;  // element offsets of the state regions in the pool
   int64_t twb_off;      // three-weight variant: first byte of this bucket's active flags
   int64_t dst_off;      // index-buffer offset of the contribution destinations
@@ -917,16 +917,15 @@ __device__ __forceinline__ void xpass_pair_sparse(const XArgs<float>& a, const B
 // ---------------------------------------------------------------------------
 // Hinge factor C max(0, 1 - y(w.a + b)) over scalar edges (w_1..w_d, b).
 // Parameters SoA [d+3][nfp]: y*a_1..y*a_d, y, C, rho/(|a|^2+1).
-// UNIF: every factor shares the variable list (z offsets [d+1]); each
-// workgroup of 256 factors emits column partials [tile][d+1].
-// Otherwise z offsets are per edge [d+1][nfp] and m itself is summed.
+// z offsets are per edge [d+1][nfp] and m itself is summed (factors that all
+// share one variable list: xpass_hinge_tile).
 // MARGIN (App. C, one-point margin, sign-corrected): the same projection
 // onto y(w.x + b) + xi >= 1 with the slack xi as slot d+1, no upper bound
 // (C = +inf) and rho/(|x|^2+2) as the last parameter.
 // ---------------------------------------------------------------------------
-template <typename T, bool A1, int MODE, bool UNIF, int DM>
+template <typename T, bool A1, int MODE, int DM>
 __device__ __forceinline__ void xpass_hinge(const XArgs<T>& a, const BucketDesc& b, int blk) {
-  __shared__ T wsum[NT / 64][DM + 1];
+  __shared__ T wsum[NT / 64];
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int d = b.d;
   const int64_t f = (int64_t)blk * NT + t;
@@ -943,7 +942,7 @@ __device__ __forceinline__ void xpass_hinge(const XArgs<T>& a, const BucketDesc&
 #pragma unroll
   for (int k = 0; k < DM; ++k) {
     if (k < d) {
-      const T zk = UNIF ? a.z[zo[k]] : a.z[zo[k * nfp + ff]];
+      const T zk = a.z[zo[k * nfp + ff]];
       const T mk = M[k * nfp + ff];
       T xo = T(0);
       if constexpr (!A1 || MODE == PM_RESID) xo = X[k * nfp + ff];
@@ -956,11 +955,11 @@ __device__ __forceinline__ void xpass_hinge(const XArgs<T>& a, const BucketDesc&
       }
     }
   }
-  const T zb = UNIF ? a.z[zo[d]] : a.z[zo[d * nfp + ff]];
+  const T zb = a.z[zo[d * nfp + ff]];
   const T mb = M[d * nfp + ff];
   T xob = T(0);
   if constexpr (!A1 || MODE == PM_RESID) xob = X[d * nfp + ff];
-  const bool margin = !UNIF && b.kind == KD_MARGIN;
+  const bool margin = b.kind == KD_MARGIN;
   T zs = T(0), ms = T(0), xos = T(0);
   if (margin) {
     zs = a.z[zo[(d + 1) * nfp + ff]];
@@ -986,13 +985,11 @@ __device__ __forceinline__ void xpass_hinge(const XArgs<T>& a, const BucketDesc&
     const T st = tau * (T)b.irho;
     const T xb = nb + st * y;
     const T mnb = xb + ub;
-    const bool shared_b = !UNIF && b.ub;
+    const bool shared_b = b.ub;
     if (valid) {
       M[d * nfp + ff] = mnb;
       if constexpr (!A1 || MODE == PM_SAVE) X[d * nfp + ff] = xb;
-      if constexpr (!UNIF) {
-        if (!shared_b) a.pool[a.idx[b.dst_off + d * nfp + ff]] = mnb;
-      }
+      if (!shared_b) a.pool[a.idx[b.dst_off + d * nfp + ff]] = mnb;
       if (margin) {
         const T xs = ns + st;
         M[(d + 1) * nfp + ff] = xs + us;
@@ -1008,304 +1005,186 @@ __device__ __forceinline__ void xpass_hinge(const XArgs<T>& a, const BucketDesc&
         if (valid) {
           M[k * nfp + ff] = mk;
           if constexpr (!A1 || MODE == PM_SAVE) X[k * nfp + ff] = xk;
-          if constexpr (!UNIF) a.pool[a.idx[b.dst_off + k * nfp + ff]] = mk;
-        }
-        if constexpr (UNIF) {
-          const T s = admmi::wave_sum(valid ? mk : T(0));
-          if (lane == 0) wsum[w][k] = s;
+          a.pool[a.idx[b.dst_off + k * nfp + ff]] = mk;
         }
       }
     }
     if (shared_b) {
       // the shared b edge: this workgroup's sum of m in a fixed order
       const T sb = admmi::wave_sum(valid ? mnb : T(0));
-      if (lane == 0) wsum[w][0] = sb;
+      if (lane == 0) wsum[w] = sb;
       __syncthreads();
       if (t == 0) {
-        T acc = wsum[0][0];
+        T acc = wsum[0];
 #pragma unroll
-        for (int q = 1; q < NT / 64; ++q) acc += wsum[q][0];
+        for (int q = 1; q < NT / 64; ++q) acc += wsum[q];
         a.pool[a.idx[b.dst_off + d * nfp + blk]] = acc;
       }
     }
-    if constexpr (UNIF) {
-      const T s = admmi::wave_sum(valid ? mnb : T(0));
-      if (lane == 0) wsum[w][d] = s;
-      __syncthreads();
-      if (t <= d) {
-        T acc = wsum[0][t];
-#pragma unroll
-        for (int q = 1; q < NT / 64; ++q) acc += wsum[q][t];
-        a.pool[a.idx[b.dst_off + (int64_t)blk * (d + 1) + t]] = acc;
-      }
-    }
   }
 }
 
-// Hinge factors sharing one variable list with d <= 32 (the SVM): two lanes
-// per factor, NT / 2 factors per workgroup, so twice as many wavefronts
-// keep loads in flight.  Lane h of a pair takes components [h dh, (h+1) dh)
-// (dh = ceil(d / 2)) and lane 1 also the b edge; both lanes form the same
-// dot product (partial sums exchanged, added in the same order) and step.
-// Every component's m is summed over the workgroup's factors: over the
-// lanes of one parity of a wavefront (xor butterfly over lane bits 1..5),
-// then over the four wavefronts in order.
-template <typename T>
-__device__ __forceinline__ T sum_parity_row(T v);
-
-// Sum over the lanes of one parity within each 16-lane row (lane bits 1..3),
-// DPP only; every lane returns its row's sum for its parity.
-template <>
-__device__ __forceinline__ float sum_parity_row<float>(float v) {
-  v += ADMM_DPP(v, 0x4E, 0xF);    // quad_perm [2,3,0,1]: lanes i, i ^ 2
-  v += ADMM_DPP(v, 0x124, 0xF);   // row_ror:4
-  v += ADMM_DPP(v, 0x128, 0xF);   // row_ror:8
-  return v;
+// Lane exchanges for sums over lane groups.  dpp: a DPP permutation within
+// 16-lane rows; pair16 / pair32: v plus the value 16 / 32 lanes away (the
+// same order of addends in both lanes).
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) { return ADMM_DPP(v, CTRL, 0xF); }
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, false);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+typedef unsigned int u2v __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ float pair16(float v) {
+  const u2v r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float pair32(float v) {
+  const u2v r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ double pair16(double v) {
+  const long long b = __double_as_longlong(v);
+  const u2v l = __builtin_amdgcn_permlane16_swap((unsigned)b, (unsigned)b, false, false);
+  const u2v h = __builtin_amdgcn_permlane16_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
+  return __longlong_as_double(((long long)h[0] << 32) | l[0]) +
+         __longlong_as_double(((long long)h[1] << 32) | l[1]);
+}
+__device__ __forceinline__ double pair32(double v) {
+  const long long b = __double_as_longlong(v);
+  const u2v l = __builtin_amdgcn_permlane32_swap((unsigned)b, (unsigned)b, false, false);
+  const u2v h = __builtin_amdgcn_permlane32_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
+  return __longlong_as_double(((long long)h[0] << 32) | l[0]) +
+         __longlong_as_double(((long long)h[1] << 32) | l[1]);
 }
 
-template <>
-__device__ __forceinline__ double sum_parity_row<double>(double v) {
-#pragma unroll
-  for (int o = 2; o < 16; o <<= 1) v += __shfl_xor(v, o, 16);
-  return v;
-}
-
-// LDS of the shared-variable hinge paths, one allocation per precision
-// whatever the register width they are instantiated for.
+// Hinge factors that all list the same variables (the SVM).  A workgroup
+// takes FB = FL V consecutive factors (V of them fill 16 bytes) and their
+// d + 1 edges, the b edge last (its parameter is y): lane (r, fl) = (t / FL,
+// t % FL) holds the factors V fl .. V fl + V - 1 on the edges r, r + RL, ...
+// (RL = NT / FL, at most EM = 8 of them).  State and parameters are stored per
+// workgroup as [edge][FB], so that every access of a wavefront is 1 KB in a
+// row.  The dot products are added over a lane's edges, over the lanes of
+// its factors in the wavefront, then over the four wavefronts in order; an
+// edge's m over a lane's factors, then over the FL lanes of its row.
+// What bounds it: memory (2 (d + 1) + d + 3 numbers per factor) for large
+// buckets and a dependent launch for small ones; so FL is the largest that
+// keeps to EM and leaves every CU a workgroup (hinge_lanes in graph.hip).
+// x-pass of 10,000 factors, against one thread per factor: FP32 d = 200 6.4
+// us (104.6), d = 50 4.3 (24.5); FP64 d = 50 4.7 (36.9), d = 200 9.0 (198);
+// of 100,000 FP32 factors, d = 20: 6.5 us, 26 MB = 4.0 TB/s (8.6 with four
+// lanes per four factors and each edge a row of all factors).
+// dsh: one allocation per precision whatever the shape.
 template <typename T>
-struct HingeSmem {
-  T wsum[NT / 16][33];   // per 16-lane row (or per wavefront), per component
-  T zsh[33];             // z of the bucket's d + 1 variables
-};
-template <typename T>
-__device__ __forceinline__ HingeSmem<T>& hinge_smem() {
-  __shared__ HingeSmem<T> sm;
+__device__ __forceinline__ T (&hinge_smem())[NT / 64][64 * (16 / sizeof(T))] {
+  __shared__ T sm[NT / 64][64 * (16 / sizeof(T))];
   return sm;
 }
 
-template <typename T, bool A1, int MODE, int DH>
-__device__ __forceinline__ void xpass_hinge2(const XArgs<T>& a, const BucketDesc& b, int blk) {
-  constexpr int FPB = NT / 2;
-  auto& wsum2 = hinge_smem<T>().wsum;
-  auto& zsh = hinge_smem<T>().zsh;
-  const int t = threadIdx.x, lane = t & 63, h = t & 1, row = t >> 4;
-  const int d = b.d, dh = (d + 1) / 2;
-  const int64_t f = (int64_t)blk * FPB + (t >> 1);
-  const bool valid = f < b.n;
-  const int64_t ff = valid ? f : 0;
-  const int64_t nfp = b.nfp;
+template <typename T, bool A1, int MODE, int FL>
+__device__ __forceinline__ void xpass_hinge_tile(const XArgs<T>& a, const BucketDesc& b, int blk) {
+  constexpr int V = 16 / (int)sizeof(T), FB = FL * V, RL = NT / FL, EM = 8;
+  typedef T vec __attribute__((ext_vector_type(V)));
+  constexpr bool READX = !A1 || MODE == PM_RESID, WRITEX = !A1 || MODE == PM_SAVE;
+  const int t = threadIdx.x, w = t >> 6, fl = t % FL, r = t / FL;
+  const int d = b.d;
+  const int64_t row0 = (int64_t)blk * (d + 1) * FB + fl * V;
+  T* M = a.pool + b.m_off + row0;
+  T* X = a.pool + b.x_off + row0;
+  const T* P = a.par + b.par_off + (int64_t)blk * (d + 3) * FB + fl * V;
   const int32_t* zo = a.idx + b.idx_off;
-  const T* P = a.par + b.par_off;
-  T* M = a.pool + b.m_off;
-  T* X = a.pool + b.x_off;
+  const int32_t* dst = a.idx + b.dst_off + (int64_t)blk * (d + 1);
   const T alpha = (T)b.alpha;
-  const int k0 = h ? dh : 0, k1 = h ? d : dh;
-  if (t <= d) zsh[t] = a.z[zo[t]];
-  // every load of the factor first (a valid component index everywhere,
-  // k0 <= d, so no load sits behind a branch), then the arithmetic
-  T mv[DH], pv[DH], xv[DH];
+  // every load first: an edge past d reads edge d and is left out below
+  vec mv[EM], pv[EM], xv[EM];
+  T zv[EM];
+  int dk[EM];
 #pragma unroll
-  for (int i = 0; i < DH; ++i) {
-    const int kc = k0 + i < k1 ? k0 + i : k0;
-    mv[i] = M[kc * nfp + ff];
-    pv[i] = MODE == PM_RESID ? T(0) : P[kc * nfp + ff];
-    xv[i] = (!A1 || MODE == PM_RESID) ? X[kc * nfp + ff] : T(0);
+  for (int i = 0; i < EM; ++i) {
+    if (RL * i > d) break;   // uniform
+    const int k = r + RL * i <= d ? r + RL * i : d;
+    if constexpr (MODE != PM_RESID) {
+      mv[i] = *(const vec*)(M + k * FB);
+      pv[i] = *(const vec*)(P + k * FB);
+      dk[i] = dst[k];
+    }
+    if constexpr (READX) xv[i] = *(const vec*)(X + k * FB);
+    zv[i] = a.z[b.zaff >= 0 ? b.zaff + k : zo[k]];
   }
-  const T mb = M[d * nfp + ff];
-  const T xob = (!A1 || MODE == PM_RESID) ? X[d * nfp + ff] : T(0);
-  T y = T(0), C = T(0), iD = T(0);
-  if constexpr (MODE != PM_RESID) {
-    y = P[d * nfp + ff];
-    C = P[(d + 1) * nfp + ff];
-    iD = P[(d + 2) * nfp + ff];
-  }
-  __syncthreads();
-  const T zb = zsh[d];
+  const int left = (int)(b.n - ((int64_t)blk * FB + fl * V));   // factors from the lane's first
   if constexpr (MODE == PM_RESID) {
     T rmax = T(0);
 #pragma unroll
-    for (int i = 0; i < DH; ++i) {
-      const int k = k0 + i;
-      if (valid && k < k1) rmax = tmax(rmax, tabs(xv[i] - zsh[k]));
+    for (int i = 0; i < EM; ++i) {
+      if (RL * i > d) break;
+#pragma unroll
+      for (int v = 0; v < V; ++v)
+        if (r + RL * i <= d && v < left) rmax = tmax(rmax, tabs(xv[i][v] - zv[i]));
     }
-    if (valid && h) rmax = tmax(rmax, tabs(xob - zb));
     block_max_store(rmax, a.blockmax);
-    return;
   } else {
-    T uv[DH], nv[DH];
-    T dot = T(0);
+    auto& dsh = hinge_smem<T>();
+    const vec C = *(const vec*)(P + (d + 1) * FB), iD = *(const vec*)(P + (d + 2) * FB);
+    // u and n; the lane's part of the dot products
+    vec dot;
 #pragma unroll
-    for (int i = 0; i < DH; ++i) {
-      const int k = k0 + i;
-      const bool on = k < k1;
-      state_un<T, A1>(mv[i], xv[i], zsh[on ? k : k0], alpha, uv[i], nv[i]);
-      if (on) dot += nv[i] * pv[i];
-    }
-    T ub = T(0), nb = T(0);
-    state_un<T, A1>(mb, xob, zb, alpha, ub, nb);
-    if (!h) ub = nb = T(0);
-    // both lanes: (even partial + odd partial) + y nb, the same bits in each
-    const T other = __shfl_xor(dot, 1, 64);
-    const T nbb = __shfl_xor(nb, 1, 64);
-    const T full = (h ? other + dot : dot + other) + y * (h ? nb : nbb);
-    const T tau = tmin(C, tmax(T(0), (T(1) - full) * iD));
-    const T st = tau * (T)b.irho;
-    T mnb = T(0);
-    if (h) {
-      const T xb = nb + st * y;
-      mnb = xb + ub;
-      if (valid) {
-        M[d * nfp + ff] = mnb;
-        if constexpr (!A1 || MODE == PM_SAVE) X[d * nfp + ff] = xb;
+    for (int v = 0; v < V; ++v) dot[v] = T(0);
+#pragma unroll
+    for (int i = 0; i < EM; ++i) {
+      if (RL * i > d) break;
+      const bool on = r + RL * i <= d;
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        T u, n;
+        state_un<T, A1>(mv[i][v], A1 ? T(0) : xv[i][v], zv[i], alpha, u, n);
+        mv[i][v] = u;          // mv holds u from here on
+        pv[i][v] = on ? pv[i][v] : T(0);
+        dot[v] += n * pv[i][v];
       }
     }
 #pragma unroll
-    for (int i = 0; i < DH; ++i) {   // i < dh is uniform: every lane takes part
-      if (i >= dh) break;
-      const int k = k0 + i;
-      const bool on = k < k1;
-      const T xk = nv[i] + st * pv[i];
-      const T mn = xk + uv[i];
-      if (valid && on) {
-        M[k * nfp + ff] = mn;
-        if constexpr (!A1 || MODE == PM_SAVE) X[k * nfp + ff] = xk;
-      }
-      const T s = sum_parity_row<T>((valid && on) ? mn : T(0));
-      if ((lane & 15) < 2 && on) wsum2[row][k] = s;
+    for (int v = 0; v < V; ++v) {
+      if constexpr (FL <= 8) dot[v] += dpp<0x128>(dot[v]);   // row_ror:8
+      if constexpr (FL <= 16) dot[v] = pair16(dot[v]);
+      if constexpr (FL <= 32) dot[v] = pair32(dot[v]);
     }
-    {
-      const T s = sum_parity_row<T>((valid && h) ? mnb : T(0));
-      if ((lane & 15) == 1) wsum2[row][d] = s;
-    }
+    if ((t & 63) < FL) *(vec*)&dsh[w][fl * V] = dot;
     __syncthreads();
-    if (t <= d) {
-      T acc = wsum2[0][t];
+    vec st = *(const vec*)&dsh[0][fl * V];
 #pragma unroll
-      for (int q = 1; q < NT / 16; ++q) acc += wsum2[q][t];
-      a.pool[a.idx[b.dst_off + (int64_t)blk * (d + 1) + t]] = acc;
-    }
-  }
-}
-
-// Shared-variable hinge with d < 32, FP32 and alpha = 1: each group of
-// four lanes takes four consecutive factors, so that every load and store
-// of a lane is 16 bytes (four factors' values of one edge).  Lane q of a
-// group takes the edges [q DQ, (q + 1) DQ) of the d + 1 (the b edge last,
-// its parameter y); its partial dot products of the four factors are added
-// over the group in a fixed order, so all four lanes hold the same bits.
-// The edges' m are summed over the workgroup's factors: over a lane's four
-// factors, over the lanes of the same q in each 16-lane row (DPP), across
-// the rows, then across the wavefronts in order.  NT factors per workgroup.
-__device__ __forceinline__ float quad_sum4(float v) {
-  // (v0 + v1) + (v2 + v3) of the group's four lanes, the same in each
-  const float v0 = ADMM_DPP(v, 0x00, 0xF), v1 = ADMM_DPP(v, 0x55, 0xF);
-  const float v2 = ADMM_DPP(v, 0xAA, 0xF), v3 = ADMM_DPP(v, 0xFF, 0xF);
-  return (v0 + v1) + (v2 + v3);
-}
-
-template <bool A1, int MODE, int DQ>
-__device__ __forceinline__ void xpass_hinge4(const XArgs<float>& a, const BucketDesc& b, int blk) {
-  auto& wsum4 = hinge_smem<float>().wsum;   // rows 0 .. NT / 64 - 1 used
-  auto& zsh4 = hinge_smem<float>().zsh;
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6, q = t & 3;
-  const int d = b.d;
-  const int64_t f0 = (int64_t)blk * NT + 4 * (t >> 2);   // the group's first factor
-  const int64_t nfp = b.nfp;
-  const int32_t* zo = a.idx + b.idx_off;
-  const float* P = a.par + b.par_off;
-  float* M = a.pool + b.m_off;
-  float* X = a.pool + b.x_off;
-  const int k0 = q * DQ;
-  if (t <= d) zsh4[t] = a.z[zo[t]];
-  // loads first: the lane's edges (an edge index past d reads edge d) and
-  // the four factors' y, C and rho / (|a|^2 + 1)
-  f4v mv[DQ], pv[DQ];
+    for (int q = 1; q < NT / 64; ++q) st += *(const vec*)&dsh[q][fl * V];
 #pragma unroll
-  for (int i = 0; i < DQ; ++i) {
-    const int k = k0 + i <= d ? k0 + i : d;
-    if constexpr (MODE == PM_RESID) {
-      mv[i] = *(const f4v*)(X + k * nfp + f0);
-    } else {
-      mv[i] = *(const f4v*)(M + k * nfp + f0);
-      pv[i] = *(const f4v*)(P + k * nfp + f0);
-    }
-  }
-  f4v C4 = {0.f, 0.f, 0.f, 0.f}, iD4 = C4;
-  if constexpr (MODE != PM_RESID) {
-    C4 = *(const f4v*)(P + (d + 1) * nfp + f0);
-    iD4 = *(const f4v*)(P + (d + 2) * nfp + f0);
-  }
-  __syncthreads();
-  bool valid[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) valid[j] = f0 + j < b.n;
-  if constexpr (MODE == PM_RESID) {
-    float rmax = 0.f;
-#pragma unroll
-    for (int i = 0; i < DQ; ++i) {
-      const int k = k0 + i;
-      if (k <= d) {
-        const float zk = zsh4[k];
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          if (valid[j]) rmax = tmax(rmax, tabs(mv[i][j] - zk));
-      }
-    }
-    block_max_store(rmax, a.blockmax);
-    return;
-  } else {
-    // u = m - z, n = z - u; partial dot products of the lane's edges
-    f4v dot = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int i = 0; i < DQ; ++i) {
-      const int k = k0 + i;
-      const float zk = zsh4[k <= d ? k : d];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float u = mv[i][j] - zk;
-        const float n = zk - u;
-        mv[i][j] = u;          // mv holds u from here on
-        pv[i][j] = k <= d ? pv[i][j] : 0.f;
-        dot[j] += n * pv[i][j];
-      }
-    }
-    f4v st;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const float full = quad_sum4(dot[j]);
-      const float tau = tmin(C4[j], tmax(0.f, (1.f - full) * iD4[j]));
-      st[j] = tau * (float)b.irho;
+    for (int v = 0; v < V; ++v) {
+      const T tau = tmin((T)C[v], tmax(T(0), (T(1) - st[v]) * iD[v]));
+      st[v] = tau * (T)b.irho;
     }
     // x = n + st p, m = x + u; the edges' sums over the workgroup's factors
 #pragma unroll
-    for (int i = 0; i < DQ; ++i) {
-      const int k = k0 + i;
-      const float zk = zsh4[k <= d ? k : d];
-      f4v mn, xk;
+    for (int i = 0; i < EM; ++i) {
+      if (RL * i > d) break;
+      const int k = r + RL * i;
+      vec mn, xk;
+      T s = T(0);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float u = mv[i][j];
-        xk[j] = (zk - u) + st[j] * pv[i][j];
-        mn[j] = xk[j] + u;
+      for (int v = 0; v < V; ++v) {
+        const T u = mv[i][v];
+        xk[v] = (zv[i] - u) + st[v] * pv[i][v];
+        mn[v] = xk[v] + u;
+        s += v < left ? mn[v] : T(0);
       }
       if (k <= d) {
-        *(f4v*)(M + k * nfp + f0) = mn;
-        if constexpr (MODE == PM_SAVE) *(f4v*)(X + k * nfp + f0) = xk;
+        *(vec*)(M + k * FB) = mn;
+        if constexpr (WRITEX) *(vec*)(X + k * FB) = xk;
       }
-      float sv = ((valid[0] ? mn[0] : 0.f) + (valid[1] ? mn[1] : 0.f)) +
-                 ((valid[2] ? mn[2] : 0.f) + (valid[3] ? mn[3] : 0.f));
-      sv += ADMM_DPP(sv, 0x124, 0xF);   // row_ror:4
-      sv += ADMM_DPP(sv, 0x128, 0xF);   // row_ror:8
-      sv += __shfl_xor(sv, 16, 64);
-      sv += __shfl_xor(sv, 32, 64);
-      if (lane < 4 && k <= d) wsum4[w][k] = sv;
-    }
-    __syncthreads();
-    if (t <= d) {
-      float acc = wsum4[0][t];
-#pragma unroll
-      for (int r = 1; r < NT / 64; ++r) acc += wsum4[r][t];
-      a.pool[a.idx[b.dst_off + (int64_t)blk * (d + 1) + t]] = acc;
+      s += dpp<0xB1>(s);    // quad_perm [1,0,3,2]
+      s += dpp<0x4E>(s);    // quad_perm [2,3,0,1]
+      s += dpp<0x141>(s);   // row_half_mirror: the other quad
+      if constexpr (FL >= 16) s += dpp<0x140>(s);   // row_mirror: the other eight lanes
+      if constexpr (FL >= 32) s = pair16(s);
+      if constexpr (FL >= 64) s = pair32(s);
+      if (fl == 0 && k <= d) a.pool[dk[i]] = s;
     }
   }
 }
@@ -1315,10 +1194,10 @@ __device__ __forceinline__ void xpass_hinge4(const XArgs<float>& a, const Bucket
 // over the components forms the dot product s = y(n_w.a + n_b) (+ n_xi);
 // once tau is known a second sweep reads each component's m, z and y a
 // again and writes its outputs, in the same order as xpass_hinge.
-template <typename T, bool A1, int MODE, bool UNIF>
+template <typename T, bool A1, int MODE>
 __device__ __forceinline__ void xpass_hinge_wide(const XArgs<T>& a, const BucketDesc& b,
                                                  int blk) {
-  __shared__ T wsw[NT / 64][NT];
+  __shared__ T wsw[NT / 64];
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int d = b.d;
   const int64_t f = (int64_t)blk * NT + t;
@@ -1332,7 +1211,7 @@ __device__ __forceinline__ void xpass_hinge_wide(const XArgs<T>& a, const Bucket
   const T alpha = (T)b.alpha;
   T dot = T(0), rmax = T(0);
   for (int k = 0; k < d; ++k) {
-    const T zk = UNIF ? a.z[zo[k]] : a.z[zo[k * nfp + ff]];
+    const T zk = a.z[zo[k * nfp + ff]];
     const T mk = M[k * nfp + ff];
     T xo = T(0);
     if constexpr (!A1 || MODE == PM_RESID) xo = X[k * nfp + ff];
@@ -1344,11 +1223,11 @@ __device__ __forceinline__ void xpass_hinge_wide(const XArgs<T>& a, const Bucket
       dot += nk * P[k * nfp + ff];
     }
   }
-  const T zb = UNIF ? a.z[zo[d]] : a.z[zo[d * nfp + ff]];
+  const T zb = a.z[zo[d * nfp + ff]];
   const T mb = M[d * nfp + ff];
   T xob = T(0);
   if constexpr (!A1 || MODE == PM_RESID) xob = X[d * nfp + ff];
-  const bool margin = !UNIF && b.kind == KD_MARGIN;
+  const bool margin = b.kind == KD_MARGIN;
   T zs = T(0), ms = T(0), xos = T(0);
   if (margin) {
     zs = a.z[zo[(d + 1) * nfp + ff]];
@@ -1374,13 +1253,11 @@ __device__ __forceinline__ void xpass_hinge_wide(const XArgs<T>& a, const Bucket
     const T st = tau * (T)b.irho;
     const T xb = nb + st * y;
     const T mnb = xb + ub;
-    const bool shared_b = !UNIF && b.ub;
+    const bool shared_b = b.ub;
     if (valid) {
       M[d * nfp + ff] = mnb;
       if constexpr (!A1 || MODE == PM_SAVE) X[d * nfp + ff] = xb;
-      if constexpr (!UNIF) {
-        if (!shared_b) a.pool[a.idx[b.dst_off + d * nfp + ff]] = mnb;
-      }
+      if (!shared_b) a.pool[a.idx[b.dst_off + d * nfp + ff]] = mnb;
       if (margin) {
         const T xs = ns + st;
         M[(d + 1) * nfp + ff] = xs + us;
@@ -1389,7 +1266,7 @@ __device__ __forceinline__ void xpass_hinge_wide(const XArgs<T>& a, const Bucket
       }
     }
     for (int k = 0; k < d; ++k) {
-      const T zk = UNIF ? a.z[zo[k]] : a.z[zo[k * nfp + ff]];
+      const T zk = a.z[zo[k * nfp + ff]];
       const T mk = M[k * nfp + ff];
       T xo = T(0);
       if constexpr (!A1) xo = X[k * nfp + ff];
@@ -1400,33 +1277,18 @@ __device__ __forceinline__ void xpass_hinge_wide(const XArgs<T>& a, const Bucket
       if (valid) {
         M[k * nfp + ff] = mn;
         if constexpr (!A1 || MODE == PM_SAVE) X[k * nfp + ff] = xk;
-        if constexpr (!UNIF) a.pool[a.idx[b.dst_off + k * nfp + ff]] = mn;
-      }
-      if constexpr (UNIF) {
-        const T s = admmi::wave_sum(valid ? mn : T(0));
-        if (lane == 0) wsw[w][k] = s;
+        a.pool[a.idx[b.dst_off + k * nfp + ff]] = mn;
       }
     }
     if (shared_b) {
       const T sb = admmi::wave_sum(valid ? mnb : T(0));
-      if (lane == 0) wsw[w][0] = sb;
+      if (lane == 0) wsw[w] = sb;
       __syncthreads();
       if (t == 0) {
-        T acc = wsw[0][0];
+        T acc = wsw[0];
 #pragma unroll
-        for (int q = 1; q < NT / 64; ++q) acc += wsw[q][0];
+        for (int q = 1; q < NT / 64; ++q) acc += wsw[q];
         a.pool[a.idx[b.dst_off + d * nfp + blk]] = acc;
-      }
-    }
-    if constexpr (UNIF) {
-      const T s = admmi::wave_sum(valid ? mnb : T(0));
-      if (lane == 0) wsw[w][d] = s;
-      __syncthreads();
-      if (t <= d) {
-        T acc = wsw[0][t];
-#pragma unroll
-        for (int q = 1; q < NT / 64; ++q) acc += wsw[q][t];
-        a.pool[a.idx[b.dst_off + (int64_t)blk * (d + 1) + t]] = acc;
       }
     }
   }
@@ -1761,13 +1623,13 @@ __device__ __forceinline__ void xpass_lindyn(const XArgs<T>& a, const BucketDesc
 // launch is that of the paths it can take.
 enum Features : int {
   FT_PAIR = 1,     // dense pair tiles
-  FT_UHINGE = 2,   // shared-variable hinge, d <= 32
+  FT_UHINGE = 2,   // shared-variable hinge
   FT_GEN = 4,      // non-overlap/wall on arbitrary variables, separable slots
   FT_WIDE = 8,     // general hinge and margin with d <= 32
   FT_PAIRSP = 16,  // dense pair tiles with sparse pair state
-  FT_XWIDE = 32,   // hinge and margin with 64 < d < NT (two sweeps, no register arrays)
+  FT_XWIDE = 32,   // general hinge and margin with 64 < d < NT (two sweeps, no register arrays)
   FT_TWA = 64,     // three-weight variant (packing graphs: pair tiles, constraints, slots)
-  FT_W64 = 128,    // hinge (shared-variable or general) with 32 < d <= 64
+  FT_W64 = 128,    // general hinge and margin with 32 < d <= 64
   FT_LINDYN = 256, // linear-dynamics projections
 };
 constexpr int FS_PAIR = FT_PAIR | FT_GEN;
@@ -1834,47 +1696,21 @@ __device__ __forceinline__ void xpass_block(XArgs<T> a, int blk, const BucketDes
       else
         xpass_pair<T, A1, MODE, 64>(a, b, local);
     }
-  } else if ((FS & (FT_UHINGE | FT_W64 | FT_XWIDE)) && b.mode == BM_UNIF_HINGE) {
-    if ((FS & FT_UHINGE) && b.dmax == 32 && b.quad) {
-      if constexpr (sizeof(T) == 4 && A1) {
-        // four lanes per four factors, ceil((d + 1) / 4) <= 8 edges per lane
-        const int dq = (b.d + 4) / 4;
-        if (dq <= 2)
-          xpass_hinge4<A1, MODE, 2>(a, b, local);
-        else if (dq <= 4)
-          xpass_hinge4<A1, MODE, 4>(a, b, local);
-        else if (dq <= 6)
-          xpass_hinge4<A1, MODE, 6>(a, b, local);
-        else
-          xpass_hinge4<A1, MODE, 8>(a, b, local);
-      }
-    } else if ((FS & FT_UHINGE) && b.dmax == 32) {
-      // per lane ceil(d / 2) components, register arrays sized to the next
-      // multiple of 4 (no loads of unused components)
-      const int dh = (b.d + 1) / 2;
-      if (dh <= 4)
-        xpass_hinge2<T, A1, MODE, 4>(a, b, local);
-      else if (dh <= 8)
-        xpass_hinge2<T, A1, MODE, 8>(a, b, local);
-      else if (dh <= 12)
-        xpass_hinge2<T, A1, MODE, 12>(a, b, local);
-      else
-        xpass_hinge2<T, A1, MODE, 16>(a, b, local);
-    }
-    else if ((FS & FT_W64) && b.dmax == 64)
-      xpass_hinge<T, A1, MODE, true, 64>(a, b, local);
-    else if ((FS & FT_XWIDE) && b.dmax == 0)
-      xpass_hinge_wide<T, A1, MODE, true>(a, b, local);
+  } else if ((FS & FT_UHINGE) && b.mode == BM_UNIF_HINGE) {
+    if (b.fl == 8) xpass_hinge_tile<T, A1, MODE, 8>(a, b, local);
+    else if (b.fl == 16) xpass_hinge_tile<T, A1, MODE, 16>(a, b, local);
+    else if (b.fl == 32) xpass_hinge_tile<T, A1, MODE, 32>(a, b, local);
+    else xpass_hinge_tile<T, A1, MODE, 64>(a, b, local);
   } else if ((FS & FT_GEN) && b.mode == BM_GEN_SLOT) {
     xpass_slot<T, A1, MODE>(a, b, local);
   } else if ((FS & FT_GEN) && (b.kind == KD_NONOVERLAP || b.kind == KD_WALL || b.kind == KD_EQUAL)) {
     xpass_geom<T, A1, MODE, TW>(a, b, local);
   } else if ((FS & FT_XWIDE) && (b.kind == KD_HINGE || b.kind == KD_MARGIN) && b.dmax == 0) {
-    xpass_hinge_wide<T, A1, MODE, false>(a, b, local);
+    xpass_hinge_wide<T, A1, MODE>(a, b, local);
   } else if ((FS & FT_W64) && (b.kind == KD_HINGE || b.kind == KD_MARGIN) && b.dmax == 64) {
-    xpass_hinge<T, A1, MODE, false, 64>(a, b, local);
+    xpass_hinge<T, A1, MODE, 64>(a, b, local);
   } else if ((FS & FT_WIDE) && (b.kind == KD_HINGE || b.kind == KD_MARGIN)) {
-    xpass_hinge<T, A1, MODE, false, 32>(a, b, local);
+    xpass_hinge<T, A1, MODE, 32>(a, b, local);
   } else if (FS & FT_LINDYN) {
     xpass_lindyn<T, A1, MODE>(a, b, local);
   }

@@ -1,11 +1,12 @@
 // Small MLP for the learned MPC warm start: y = W3 relu(W2 relu(W1 x + b1) +
 // b2) + b3, mean-squared-error loss, Adam.  Every matrix product runs on the
 // gfx950 matrix cores (v_mfma_f32_16x16x32_bf16): operands rounded to
-// bf16 (round to nearest even) while staged through LDS, products
+// bf16 (round to nearest even) on their way into registers, products
 // accumulated in fp32.  Master weights, activations and gradients are fp32
-// in device memory.  Bias, ReLU and the ReLU mask of the backward pass are
-// fused into the product epilogues; reductions (loss, bias gradients) use a
-// fixed order, so results are deterministic.
+// in device memory.  Bias, ReLU, the loss and its gradient, the ReLU mask of
+// the backward pass and the Adam step are fused into the products; a
+// training step is seven launches.  Reductions (split products, loss, bias
+// gradients) use a fixed order, so results are deterministic.
 #include <hip/hip_ext.h>
 
 #include <algorithm>
@@ -18,197 +19,429 @@
 
 namespace {
 
-typedef short v8s __attribute__((ext_vector_type(8)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef float v8f __attribute__((ext_vector_type(8)));
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef __bf16 v4bf __attribute__((ext_vector_type(4)));
 
-constexpr int GT = 256;  // threads per GEMM workgroup (4 wavefronts)
-constexpr int BM = 64, BN = 64, BK = 32;
+// Products C = A B^T by groups of four wavefronts, a 64 x BN tile of C
+// each (BN = 64: 2 x 2 wavefronts of 32 x 32; BN = 32: 4 wavefronts of
+// 16 x 32), K in chunks of KC through LDS.
+constexpr int BM = 64, KC = 128, GT = 256;
+constexpr int LROW = KC + 8;   // LDS row: 16-byte aligned, rows four banks apart
+constexpr int BSPLIT = 4;      // groups of a backward workgroup, which share K
 
-__device__ __forceinline__ unsigned short f2bf(float f) {
-  unsigned int u = __float_as_uint(f);
-  if ((u & 0x7f800000u) == 0x7f800000u) return (unsigned short)((u >> 16) | ((u & 0xffff) ? 0x40 : 0));
-  u += 0x7fffu + ((u >> 16) & 1u);  // round to nearest even
-  return (unsigned short)(u >> 16);
+__host__ __device__ constexpr int tiles(int n, int t) { return n / t + (n % t != 0); }
+
+// A matrix operand in memory: element (i, k) at p[i ld + k], or, K-strided,
+// at p[k ld + i].  vec: rows of k are 16-byte aligned.
+struct Operand {
+  const float* p;
+  int ld;
+  bool vec;
+};
+Operand operand(const float* p, int ld) {
+  return Operand{p, ld, (reinterpret_cast<uintptr_t>(p) & 15) == 0 && ld % 4 == 0};
 }
 
-enum Epi : int { EPI_PLAIN = 0, EPI_BIAS = 1, EPI_BIAS_RELU = 2, EPI_MASK = 3, EPI_BIAS_AFFINE = 4 };
+// One group's part of a chunk of R rows in flight: thread t holds R / 8
+// groups of four k.  K in memory order: of the rows t / 32 + 8 j at
+// k = 4 (t % 32), so that 32 lanes read 512 bytes in a row.  K-strided: of
+// row t % R at the k of its GT / R-th of the chunk, a row of R elements per k.
+template <int R>
+struct Chunk {
+  v4f v[R / 8];
+};
 
-// C[M x N] = sum_k A(m,k) B(k,n); A(m,k) = TA ? A[k*lda+m] : A[m*lda+k],
-// B(k,n) = TB ? B[n*ldb+k] : B[k*ldb+n].  Epilogue per EPI.
-// Workgroup tile 64 x 64, each wavefront a 32 x 32 quarter as 2 x 2 MFMA
-// tiles of 16 x 16, K consumed 32 at a time through LDS: one gfx950
-// v_mfma_f32_16x16x32_bf16 per tile and barrier (lane l holds row or
-// column l % 16 and the eight k = 8 (l / 16) .. + 7 of the step).  Split K: workgroup z covers K range [z*kc, (z+1)*kc) and
-// writes its partial product to C + z*M*N (plain epilogue only).
-template <bool TA, bool TB, int EPI>
-__global__ __launch_bounds__(GT) void gemm_kernel(int M, int N, int K, int kc,
-                                                 const float* __restrict__ A, int lda,
-                                                 const float* __restrict__ B, int ldb,
-                                                 float* __restrict__ C, int ldc,
-                                                 const float* __restrict__ bias,
-                                                 const float* __restrict__ mask, int ldm,
-                                                 const float* __restrict__ mu,
-                                                 const float* __restrict__ sd) {
-  __shared__ unsigned short As[BM][BK + 4];
-  __shared__ unsigned short Bs[BK][BN + 4];
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-  const int kbeg = blockIdx.z * kc;
-  const int kend = min(K, kbeg + kc);
-  C += (int64_t)blockIdx.z * M * N;
-  const int wm = (w >> 1) * 32, wn = (w & 1) * 32;
-  v4f acc[2][2];
+// Rows past the end repeat the last one (they only make results that nobody
+// stores); k past k1 (at least 1) read in range and become zero.
+template <bool KS, int R>
+__device__ __forceinline__ void load_chunk(Chunk<R>& c, const Operand& o, int rows, int r0, int kb,
+                                           int k1, int t) {
+  if constexpr (KS) {
+    const int i = min(r0 + t % R, rows - 1), k = kb + t / R * (R / 2);
+    if (kb + KC <= k1) {   // uniform
+      const float* q = o.p + (int64_t)k * o.ld + i;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+      for (int j = 0; j < R / 8; ++j)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
-  // The next K tile is read from global memory into registers while the
-  // current one is multiplied from LDS.
-  float ra[8], rb[8];
-  auto load_tile = [&](int k0) {
+        for (int e = 0; e < 4; ++e, q += o.ld) c.v[j][e] = *q;
+    } else {
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int e = t + q * GT;
-      int r, c;
-      if (TA) { c = e / BM; r = e % BM; } else { r = e / BK; c = e % BK; }
-      const int gm = m0 + r, gk = k0 + c;
-      ra[q] = (gm < M && gk < kend) ? (TA ? A[(int64_t)gk * lda + gm] : A[(int64_t)gm * lda + gk]) : 0.f;
+      for (int j = 0; j < R / 8; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int kk = k + 4 * j + e;
+          const float x = o.p[(int64_t)min(kk, k1 - 1) * o.ld + i];
+          c.v[j][e] = kk < k1 ? x : 0.f;
+        }
     }
+  } else {
+    const int k = kb + 4 * (t % 32);
+    if (o.vec && kb + KC <= k1) {   // uniform
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int e = t + q * GT;
-      int r, c;
-      if (TB) { c = e / BK; r = e % BK; } else { r = e / BN; c = e % BN; }
-      const int gk = k0 + r, gn = n0 + c;
-      rb[q] = (gk < kend && gn < N) ? (TB ? B[(int64_t)gn * ldb + gk] : B[(int64_t)gk * ldb + gn]) : 0.f;
-    }
-  };
-  if (kbeg < kend) load_tile(kbeg);
-  for (int k0 = kbeg; k0 < kend; k0 += BK) {
-    // A tile 64 x 32 and B tile 32 x 64: 2048 elements each, 8 per thread
+      for (int j = 0; j < R / 8; ++j)
+        c.v[j] = *(const v4f*)(o.p + (int64_t)min(r0 + t / 32 + 8 * j, rows - 1) * o.ld + k);
+    } else if (o.vec && k1 % 4 == 0) {
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int e = t + q * GT;
-      int r, c;
-      if (TA) { c = e / BM; r = e % BM; } else { r = e / BK; c = e % BK; }
-      As[r][c] = f2bf(ra[q]);
-    }
+      for (int j = 0; j < R / 8; ++j) {
+        const int64_t row = (int64_t)min(r0 + t / 32 + 8 * j, rows - 1) * o.ld;
+        const v4f x = *(const v4f*)(o.p + row + min(k, k1 - 4));
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int e = t + q * GT;
-      int r, c;
-      if (TB) { c = e / BK; r = e % BK; } else { r = e / BN; c = e % BN; }
-      Bs[r][c] = f2bf(rb[q]);
-    }
-    __syncthreads();
-    if (k0 + BK < kend) load_tile(k0 + BK);
-#pragma unroll
-    for (int kk = 0; kk < BK; kk += 32) {
-      const int kq = kk + (lane >> 4) * 8;
-      v8s af[2], bf[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int row = wm + i * 16 + (lane & 15);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) af[i][j] = (short)As[row][kq + j];
+        for (int e = 0; e < 4; ++e) c.v[j][e] = k < k1 ? x[e] : 0.f;
       }
+    } else {
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int col = wn + i * 16 + (lane & 15);
+      for (int j = 0; j < R / 8; ++j) {
+        const int64_t row = (int64_t)min(r0 + t / 32 + 8 * j, rows - 1) * o.ld;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) bf[i][j] = (short)Bs[kq + j][col];
-      }
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-              __builtin_bit_cast(v8bf, af[i]), __builtin_bit_cast(v8bf, bf[j]), acc[i][j], 0, 0, 0);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int col = n0 + wn + j * 16 + (lane & 15);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int row = m0 + wm + i * 16 + (lane >> 4) * 4 + q;
-        if (row < M && col < N) {
-          float v = acc[i][j][q];
-          if (EPI == EPI_BIAS || EPI == EPI_BIAS_RELU || EPI == EPI_BIAS_AFFINE) v += bias[col];
-          if (EPI == EPI_BIAS_AFFINE) v = mu[col] + sd[col] * v;
-          if (EPI == EPI_BIAS_RELU) v = v > 0.f ? v : 0.f;
-          if (EPI == EPI_MASK) v = mask[(int64_t)row * ldm + col] > 0.f ? v : 0.f;
-          C[(int64_t)row * ldc + col] = v;
+        for (int e = 0; e < 4; ++e) {
+          const float x = o.p[row + min(k + e, k1 - 1)];
+          c.v[j][e] = k + e < k1 ? x : 0.f;
         }
       }
     }
-}
-
-// out[i] = sum_{z < nz} ws[z*n + i], z in order (split-K reduction).
-__global__ void splitk_sum_kernel(int64_t n, int nz, const float* __restrict__ ws,
-                                  float* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  float s = 0.f;
-  for (int z = 0; z < nz; ++z) s += ws[(int64_t)z * n + i];
-  out[i] = s;
-}
-
-// The same reduction of a [M][N] product followed by the ReLU-mask
-// epilogue: out[r][c] = mask[r][c] > 0 ? sum : 0.
-__global__ void splitk_sum_mask_kernel(int64_t n, int N, int nz, const float* __restrict__ ws,
-                                       const float* __restrict__ mask, int ldm,
-                                       float* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  float s = 0.f;
-  for (int z = 0; z < nz; ++z) s += ws[(int64_t)z * n + i];
-  const int64_t r = i / N, c = i % N;
-  out[i] = mask[r * ldm + c] > 0.f ? s : 0.f;
-}
-
-// Loss on normalised outputs: with yh the network's raw output and
-// th = (target - mu) / sd per column, dY = 2 (yh - th) / (rows * cols);
-// per-block partial sums of (yh - th)^2.
-__global__ __launch_bounds__(256) void mse_grad_kernel(int64_t n, int cols, const float* y,
-                                                       const float* tg, const float* mu,
-                                                       const float* sd, float scale, float* dy,
-                                                       float* part) {
-  __shared__ float red[256];
-  float s = 0.f;
-  // n < 2^31 (checked on the host): 32-bit index arithmetic
-  const int nn = (int)n;
-  for (int i = blockIdx.x * 256 + threadIdx.x; i < nn; i += gridDim.x * 256) {
-    const int c = i % cols;
-    const float d = y[i] - (tg[i] - mu[c]) / sd[c];
-    dy[i] = 2.f * d * scale;
-    s += d * d;
   }
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int k = 128; k > 0; k >>= 1) {
-    if ((int)threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
+}
+
+// Rounded to bf16 (to nearest even) into the rows [row][k] of LDS.
+template <bool KS, int R>
+__device__ __forceinline__ void store_chunk(const Chunk<R>& c, __bf16 (*s)[LROW], int t) {
+  if constexpr (KS) {
+#pragma unroll
+    for (int j = 0; j < R / 16; ++j) {
+      v8f v;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = c.v[2 * j + e / 4][e % 4];
+      *(v8bf*)&s[t % R][t / R * (R / 2) + 8 * j] = __builtin_convertvector(v, v8bf);
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < R / 8; ++j)
+      *(v4bf*)&s[t / 32 + 8 * j][4 * (t % 32)] = __builtin_convertvector(c.v[j], v4bf);
+  }
+}
+
+template <int BN>
+struct GroupSmem {
+  __bf16 a[BM][LROW];
+  __bf16 b[BN][LROW];
+};
+
+template <int BN>
+struct Tile {
+  static constexpr int MI = BN / 32;   // MFMA tiles of a wavefront: MI x 2
+  v4f acc[MI][2];
+  // row and column in the 64 x BN tile of element q of MFMA tile (i, j)
+  static __device__ __forceinline__ int row0() {
+    const int w = (threadIdx.x >> 6) & 3;
+    return BN == 64 ? (w >> 1) * 32 : w * 16;
+  }
+  static __device__ __forceinline__ int col0() {
+    const int w = (threadIdx.x >> 6) & 3;
+    return BN == 64 ? (w & 1) * 32 : 0;
+  }
+  static __device__ __forceinline__ int row(int i, int q) {
+    return row0() + 16 * i + ((threadIdx.x >> 4) & 3) * 4 + q;
+  }
+  static __device__ __forceinline__ int col(int j) { return col0() + 16 * j + (threadIdx.x & 15); }
+};
+
+// The group's tile over k in [k0, k1), k ascending in steps of 32 (one
+// v_mfma_f32_16x16x32_bf16 per 16 x 16 tile and step, fp32 accumulation).
+// Every group of the workgroup calls this with the same number of chunks.
+// The next chunk is on its way while the current one is multiplied.  asum
+// (if SUM, A K-strided): this thread's part of its row's sum over k of A
+// before rounding.
+template <bool AKS, bool BKS, bool SUM, int BN>
+__device__ __forceinline__ void group_product(const Operand& A, int M, const Operand& B, int N,
+                                              int m0, int n0, int k0, int k1, int chunks,
+                                              GroupSmem<BN>& sm, Tile<BN>& tile, float& asum) {
+  const int t = threadIdx.x % GT, lane = t & 63;
+#pragma unroll
+  for (int i = 0; i < Tile<BN>::MI; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) tile.acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+  asum = 0.f;
+  Chunk<BM> ca;
+  Chunk<BN> cb;
+  load_chunk<AKS>(ca, A, M, m0, k0, k1, t);
+  load_chunk<BKS>(cb, B, N, n0, k0, k1, t);
+  for (int c = 0; c < chunks; ++c) {
+    const int kb = k0 + c * KC;
+    if (c > 0) __syncthreads();
+    if constexpr (SUM) {
+#pragma unroll
+      for (int j = 0; j < BM / 8; ++j) asum += (ca.v[j][0] + ca.v[j][1]) + (ca.v[j][2] + ca.v[j][3]);
+    }
+    store_chunk<AKS>(ca, sm.a, t);
+    store_chunk<BKS>(cb, sm.b, t);
     __syncthreads();
+    if (c + 1 < chunks) {
+      load_chunk<AKS>(ca, A, M, m0, kb + KC, k1, t);
+      load_chunk<BKS>(cb, B, N, n0, kb + KC, k1, t);
+    }
+    const int steps = min(KC, k1 - kb);
+#pragma unroll
+    for (int kk = 0; kk < KC; kk += 32) {
+      if (kk >= steps) break;   // uniform over the group
+      v8bf fa[Tile<BN>::MI], fb[2];
+#pragma unroll
+      for (int i = 0; i < Tile<BN>::MI; ++i)
+        fa[i] = *(const v8bf*)&sm.a[Tile<BN>::row0() + 16 * i + (lane & 15)][kk + 8 * (lane >> 4)];
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        fb[j] = *(const v8bf*)&sm.b[Tile<BN>::col0() + 16 * j + (lane & 15)][kk + 8 * (lane >> 4)];
+#pragma unroll
+      for (int i = 0; i < Tile<BN>::MI; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          tile.acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fb[j], tile.acc[i][j], 0, 0, 0);
+    }
   }
-  if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
 
-// Sum of the per-block partials in a fixed order: 64 lanes sum strided
-// subsets in order, then lane 0 adds the 64 results in lane order.
-__global__ void finish_loss_kernel(int nb, const float* part, float scale, float* loss) {
-  __shared__ float r64[64];
-  float s = 0.f;
-  for (int i = threadIdx.x; i < nb; i += 64) s += part[i];
-  r64[threadIdx.x] = s;
+// Layers of the forward pass: C = A B^T + bias, A [M][K], B [N][K], then
+//   RELU    C = max(C, 0)
+//   AFFINE  C = mu + sd C
+//   LOSS    on normalised outputs: with th = (target - mu) / sd per column,
+//           C = 2 (yh - th) scale, and per workgroup the sum of (yh - th)^2
+// One group per tile with all of K (the order of its sums decides how the
+// next layer's operands round).  What bounds it: a chunk's memory round trip
+// (the operands are what other XCDs have just written) and the launch; a
+// 64-wide tile, with half as many wavefronts, took 16.2 us for the loss
+// layer.  Batch 2048: 256 -> 256 5.1 us (10.7 with 16-bit LDS accesses and
+// the same tile in one wavefront each), 256 -> 1100 with the loss 13.4 us
+// (31.9 in three launches).
+enum Epi : int { EPI_RELU = 0, EPI_AFFINE = 1, EPI_LOSS = 2 };
+
+constexpr int LN = 32;
+template <int EPI>
+__global__ __launch_bounds__(GT) void layer_kernel(int M, int N, int K, Operand A, Operand B,
+                                                   const float* __restrict__ bias,
+                                                   float* __restrict__ C,
+                                                   const float* __restrict__ mu,
+                                                   const float* __restrict__ sd,
+                                                   const float* __restrict__ target, float scale,
+                                                   float* __restrict__ part) {
+  __shared__ GroupSmem<LN> sm;
+  using TL = Tile<LN>;
+  const int gm = tiles(M, BM);
+  const int m0 = (int)blockIdx.x % gm * BM, n0 = (int)blockIdx.x / gm * LN;
+  v4f tg[TL::MI][2];
+  if constexpr (EPI == EPI_LOSS) {
+    // read ahead of the product (clamped; what lies outside is not used)
+#pragma unroll
+    for (int i = 0; i < TL::MI; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          tg[i][j][q] = target[(int64_t)min(m0 + TL::row(i, q), M - 1) * N + min(n0 + TL::col(j), N - 1)];
+  }
+  TL tile;
+  float asum, loss = 0.f;
+  group_product<false, false, false>(A, M, B, N, m0, n0, 0, K, tiles(K, KC), sm, tile, asum);
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int col = n0 + TL::col(j);
+    if (col >= N) continue;
+    const float bc = bias[col];
+    float mc = 0.f, sc = 1.f;
+    if (EPI != EPI_RELU) {
+      mc = mu[col];
+      sc = sd[col];
+    }
+#pragma unroll
+    for (int i = 0; i < TL::MI; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int row = m0 + TL::row(i, q);
+        if (row >= M) continue;
+        const int64_t at = (int64_t)row * N + col;
+        float v = tile.acc[i][j][q] + bc;
+        if (EPI == EPI_RELU) v = v > 0.f ? v : 0.f;
+        if (EPI == EPI_AFFINE) v = mc + sc * v;
+        if (EPI == EPI_LOSS) {
+          const float d = v - (tg[i][j][q] - mc) / sc;
+          loss += d * d;
+          v = 2.f * d * scale;
+        }
+        C[at] = v;
+      }
+  }
+  if constexpr (EPI == EPI_LOSS) {
+    __shared__ float red[GT / 64];
+    const float s = admmi::wave_sum(loss);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      float t = red[0];
+#pragma unroll
+      for (int q = 1; q < GT / 64; ++q) t += red[q];
+      part[blockIdx.x] = t;
+    }
+  }
+}
+
+// Part of [0, K) of sharer w of n: whole steps of 32; its chunks are as many
+// as the first one's.
+__host__ __device__ inline int k_share(int K, int n) { return tiles(tiles(K, n), 32) * 32; }
+
+// The tiles of a workgroup's groups meet in LDS (over the operands' space)
+// and are added in group order.
+template <int BN, int KW>
+union SplitSmem {
+  GroupSmem<BN> g[KW];
+  float t[KW][BM][BN + 1];
+};
+
+template <int BN, int KW>
+__device__ __forceinline__ void split_store(SplitSmem<BN, KW>& sm, const Tile<BN>& tile) {
+  const int g = threadIdx.x / GT;
+#pragma unroll
+  for (int i = 0; i < Tile<BN>::MI; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        sm.t[g][Tile<BN>::row(i, q)][Tile<BN>::col(j)] = tile.acc[i][j][q];
+}
+
+template <int BN, int KW>
+__device__ __forceinline__ float split_sum(const SplitSmem<BN, KW>& sm, int e) {
+  float s = sm.t[0][e / BN][e % BN];
+#pragma unroll
+  for (int q = 1; q < KW; ++q) s += sm.t[q][e / BN][e % BN];
+  return s;
+}
+
+// Backward through a layer: D [M][N] = (G W) where the layer's input was
+// positive, else 0; G [M][K] the gradient of its outputs, W [K][N] its
+// weights.  One 64 x 32 tile per workgroup, K shared by its groups.  What
+// bounds it: as above.  Batch 2048: K = 1100 and 256 10.9 us on average (17.9
+// with split products in memory and their sum in a second launch; 15.5 with
+// a 64-wide tile, 12.3 with one group).
+constexpr int BW = 32;
+__global__ __launch_bounds__(BSPLIT * GT) void back_kernel(int M, int N, int K, Operand G,
+                                                          Operand W, const float* __restrict__ h,
+                                                          float* __restrict__ D) {
+  __shared__ SplitSmem<BW, BSPLIT> sm;
+  const int gm = tiles(M, BM), g = threadIdx.x / GT;
+  const int m0 = (int)blockIdx.x % gm * BM, n0 = (int)blockIdx.x / gm * BW;
+  const int ks = k_share(K, BSPLIT), k0 = min(K, g * ks);
+  Tile<BW> tile;
+  float asum;
+  group_product<false, true, false>(G, M, W, N, m0, n0, k0, min(K, k0 + ks), tiles(ks, KC),
+                                    sm.g[g], tile, asum);
   __syncthreads();
-  if (threadIdx.x == 0) {
-    float t = 0.f;
-    for (int i = 0; i < 64; ++i) t += r64[i];
-    *loss = t * scale;
+  split_store(sm, tile);
+  __syncthreads();
+#pragma unroll
+  for (int x = 0; x < BM * BW / (BSPLIT * GT); ++x) {
+    const int e = threadIdx.x + x * BSPLIT * GT, row = m0 + e / BW, col = n0 + e % BW;
+    if (row < M && col < N) {
+      const int64_t at = (int64_t)row * N + col;
+      D[at] = h[at] > 0.f ? split_sum(sm, e) : 0.f;
+    }
+  }
+}
+
+// Gradients of every layer's weights and biases in one launch: for layer l,
+// dW [M][N] = G^T H summed over the batch, G [batch][M] the gradient of its
+// outputs and H [batch][N] its inputs, and db [M] = G summed over the batch
+// (by the workgroups of the first column of tiles, from the operands before
+// rounding).  One 64 x 64 tile per workgroup; the batch is shared by
+// `splits` workgroups, whose results go to consecutive parameter-sized rows
+// of ws.  The last workgroup adds the loss partials.  What bounds it: the
+// traffic of the operands, each read by 4 to 18 tiles, and a chunk's round
+// trip.  Batch 2048, hidden 256, n_out 1100: 12.2 us (19.0 with two groups
+// per workgroup; twelve launches and some 75 us as separate products, sums and
+// column sums).
+struct GradLayer {
+  Operand G, H;
+  int M, N, tn, blk0;   // tiles per row of tiles, first workgroup of a split
+  int64_t oW, ob;       // offsets in the parameter vector
+};
+struct GradArgs {
+  GradLayer l[3];
+  int batch, blocks, splits;   // blocks: workgroups per split
+  float* ws;
+  int64_t n_params;
+  const float* part;
+  int64_t n_part;
+  float scale;
+  float* loss;
+};
+
+__global__ __launch_bounds__(GT) void grad_kernel(GradArgs a) {
+  constexpr int BN = 64;
+  __shared__ GroupSmem<BN> sm;
+  __shared__ float rs[GT / 64][BM];
+  const int t = threadIdx.x, w = t >> 6;
+  if ((int)blockIdx.x == a.blocks * a.splits) {
+    // strided sums, then the wavefronts' in order
+    float s = 0.f;
+    for (int64_t i = t; i < a.n_part; i += GT) s += a.part[i];
+    s = admmi::wave_sum(s);
+    if ((t & 63) == 0) rs[0][w] = s;
+    __syncthreads();
+    if (t == 0) {
+      float r = rs[0][0];
+#pragma unroll
+      for (int q = 1; q < GT / 64; ++q) r += rs[0][q];
+      *a.loss = r * a.scale;
+    }
+    return;
+  }
+  const int split = (int)blockIdx.x % a.splits, blk = (int)blockIdx.x / a.splits;
+  const GradLayer L = a.l[blk >= a.l[2].blk0 ? 2 : (blk >= a.l[1].blk0 ? 1 : 0)];
+  const int m0 = (blk - L.blk0) / L.tn * BM, n0 = (blk - L.blk0) % L.tn * BN;
+  const int ks = k_share(a.batch, a.splits);
+  const int k0 = min(a.batch, split * ks), k1 = min(a.batch, k0 + ks);
+  float* out = a.ws + split * a.n_params;
+  Tile<BN> tile;
+  float asum;
+  if (n0 == 0)
+    group_product<true, true, true>(L.G, L.M, L.H, L.N, m0, n0, k0, k1, tiles(ks, KC), sm, tile, asum);
+  else
+    group_product<true, true, false>(L.G, L.M, L.H, L.N, m0, n0, k0, k1, tiles(ks, KC), sm, tile, asum);
+#pragma unroll
+  for (int i = 0; i < Tile<BN>::MI; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int row = m0 + Tile<BN>::row(i, q), col = n0 + Tile<BN>::col(j);
+        if (row < L.M && col < L.N) out[L.oW + (int64_t)row * L.N + col] = tile.acc[i][j][q];
+      }
+  if (n0 == 0) {   // uniform
+    rs[w][t & 63] = asum;
+    __syncthreads();
+    if (t < BM && m0 + t < L.M) out[L.ob + m0 + t] = (rs[0][t] + rs[1][t]) + (rs[2][t] + rs[3][t]);
+  }
+}
+
+// The splits' gradients in order, and what becomes of them: stored in g, or
+// (ADAM) the step they give (Kingma and Ba, bias-corrected) on the flat
+// parameter vector.
+template <bool ADAM>
+__global__ __launch_bounds__(256) void step_kernel(int64_t n, int splits,
+                                                   const float* __restrict__ ws, float* g, float* p,
+                                                   float* m, float* v, float lr, float b1, float b2,
+                                                   float eps, float c1, float c2) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  float gi = ws[i];
+  for (int s = 1; s < splits; ++s) gi += ws[s * n + i];
+  if constexpr (ADAM) {
+    const float mi = b1 * m[i] + (1.f - b1) * gi;
+    const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
+    m[i] = mi;
+    v[i] = vi;
+    p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+  } else {
+    g[i] = gi;
   }
 }
 
@@ -255,35 +488,6 @@ __global__ void fill_kernel(int n, float v, float* a) {
   if (i < n) a[i] = v;
 }
 
-// Bias gradients db[c] = sum_r dY[r][c] in two deterministic stages:
-// colsum_part sums chunks of CS_ROWS rows in order into ws[k][c], and
-// splitk_sum_kernel adds the chunks in order.
-constexpr int CS_ROWS = 128;
-__global__ void colsum_part_kernel(int rows, int cols, const float* __restrict__ dY,
-                                   float* __restrict__ ws) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= cols) return;
-  const int r0 = blockIdx.y * CS_ROWS;
-  const int r1 = r0 + CS_ROWS < rows ? r0 + CS_ROWS : rows;
-  float s = 0.f;
-#pragma unroll 8
-  for (int r = r0; r < r1; ++r) s += dY[(int64_t)r * cols + c];
-  ws[(int64_t)blockIdx.y * cols + c] = s;
-}
-
-// Adam (Kingma and Ba), bias-corrected, on the flat parameter vector.
-__global__ void adam_kernel(int64_t n, float* p, const float* g, float* m, float* v, float lr,
-                            float b1, float b2, float eps, float c1, float c2) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const float gi = g[i];
-  const float mi = b1 * m[i] + (1.f - b1) * gi;
-  const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-  m[i] = mi;
-  v[i] = vi;
-  p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-}
-
 }  // namespace
 
 // Workspace of admm_mlp_fit_output_scaling_noalloc: a fixed array in device
@@ -320,13 +524,11 @@ struct admm_mlp {
   int n_in = 0, hid = 0, n_out = 0, max_batch = 0;
   int64_t n_params = 0;
   int64_t oW1, ob1, oW2, ob2, oW3, ob3;
-  float *p = nullptr, *g = nullptr, *am = nullptr, *av = nullptr;
-  float *h1 = nullptr, *h2 = nullptr, *y = nullptr, *dy = nullptr, *dh1 = nullptr, *dh2 = nullptr;
-  float* part = nullptr;
+  float *p = nullptr, *am = nullptr, *av = nullptr;
+  float* ws = nullptr;                 // gradients of each split of the batch
+  float *h1 = nullptr, *h2 = nullptr, *dy = nullptr, *dh1 = nullptr, *dh2 = nullptr;
+  float* part = nullptr;               // loss partials, one per workgroup
   float *mu = nullptr, *sd = nullptr;  // fixed output affine y = mu + sd * yhat
-  float* ws = nullptr;                 // split-K partial products
-  int64_t ws_n = 0;                    // its size in floats
-  float* cs = nullptr;                 // bias-gradient chunk sums
   int64_t step = 0;
   std::vector<void*> allocs;
   ~admm_mlp() {
@@ -339,94 +541,83 @@ struct admm_mlp {
 
 namespace {
 
-constexpr int LOSS_BLOCKS = 1024;
-
 admm_status mlp_alloc(admm_mlp* n, float** q, int64_t count) {
   ADMM_HIP(hipMalloc((void**)q, (size_t)std::max<int64_t>(count, 1) * sizeof(float)));
   n->allocs.push_back(*q);
   return ADMM_OK;
 }
 
-constexpr int MAX_SPLITS = 32;
+template <int EPI>
+void layer(int M, int N, int K, const float* A, const float* B, const float* bias, float* C,
+           hipStream_t st, const float* mu = nullptr, const float* sd = nullptr,
+           const float* target = nullptr, float scale = 0.f, float* part = nullptr) {
+  layer_kernel<EPI><<<tiles(M, BM) * tiles(N, LN), GT, 0, st>>>(
+      M, N, K, operand(A, K), operand(B, K), bias, C, mu, sd, target, scale, part);
+}
 
-template <bool TA, bool TB, int EPI>
-void gemm(int M, int N, int K, const float* A, int lda, const float* B, int ldb, float* C, int ldc,
-          const float* bias, const float* mask, int ldm, hipStream_t st,
-          const float* mu = nullptr, const float* sd = nullptr, float* ws = nullptr,
-          int64_t ws_n = 0) {
-  const int gm = (M + BM - 1) / BM, gn = (N + BN - 1) / BN;
-  int splits = 1;
-  if ((EPI == EPI_PLAIN || EPI == EPI_MASK) && ws != nullptr && ldc == N) {
-    // enough workgroups to fill the device, at least 128 of K per split
-    splits = std::max(1, std::min(MAX_SPLITS, std::min((1024 + gm * gn - 1) / (gm * gn), K / 128)));
-    splits = (int)std::max<int64_t>(1, std::min<int64_t>(splits, ws_n / ((int64_t)M * N)));
+// h1 = relu(x W1^T + b1), h2 = relu(h1 W2^T + b2)
+void hidden_layers(admm_mlp* n, const float* x, int batch, hipStream_t st) {
+  layer<EPI_RELU>(batch, n->hid, n->n_in, x, n->p + n->oW1, n->p + n->ob1, n->h1, st);
+  layer<EPI_RELU>(batch, n->hid, n->hid, n->h1, n->p + n->oW2, n->p + n->ob2, n->h2, st);
+}
+
+// y = mu + sd * (h2 W3^T + b3)
+void forward(admm_mlp* n, const float* x, int batch, float* y, hipStream_t st) {
+  hidden_layers(n, x, batch, st);
+  layer<EPI_AFFINE>(batch, n->n_out, n->hid, n->h2, n->p + n->oW3, n->p + n->ob3, y, st, n->mu,
+                    n->sd);
+}
+
+// Workgroups that share the batch in the gradient launch, at least 32 rows
+// each.  Consecutive workgroups go to different XCDs, so with eight each XCD
+// reads its own eighth of the activations and gradients (19.0 us against 23.4 with
+// five and the splits in order, measured with two groups per workgroup).
+constexpr int MAX_SPLITS = 8;
+int grad_splits(int batch) { return std::max(1, std::min(MAX_SPLITS, batch / 32)); }
+
+// gradients of mean((y - t)^2) into g, or, with lr > 0, the Adam step they
+// give; loss (device scalar) when non-null
+void backward(admm_mlp* n, const float* x, const float* tg, int batch, float* loss, float* g,
+              float lr, hipStream_t st) {
+  hidden_layers(n, x, batch, st);
+  const float scale = 1.f / (float)((int64_t)batch * n->n_out);
+  layer<EPI_LOSS>(batch, n->n_out, n->hid, n->h2, n->p + n->oW3, n->p + n->ob3, n->dy, st, n->mu,
+                  n->sd, tg, scale, n->part);
+  const int gh = tiles(batch, BM) * tiles(n->hid, BW);
+  back_kernel<<<gh, BSPLIT * GT, 0, st>>>(batch, n->hid, n->n_out, operand(n->dy, n->n_out),
+                                          operand(n->p + n->oW3, n->hid), n->h2, n->dh2);
+  back_kernel<<<gh, BSPLIT * GT, 0, st>>>(batch, n->hid, n->hid, operand(n->dh2, n->hid),
+                                          operand(n->p + n->oW2, n->hid), n->h1, n->dh1);
+  GradArgs a{};
+  const float* G[3] = {n->dy, n->dh2, n->dh1};
+  const float* H[3] = {n->h2, n->h1, x};
+  const int M[3] = {n->n_out, n->hid, n->hid}, N[3] = {n->hid, n->hid, n->n_in};
+  const int64_t oW[3] = {n->oW3, n->oW2, n->oW1}, ob[3] = {n->ob3, n->ob2, n->ob1};
+  for (int l = 0; l < 3; ++l) {
+    a.l[l] = GradLayer{operand(G[l], M[l]), operand(H[l], N[l]), M[l], N[l], tiles(N[l], 64),
+                       a.blocks, oW[l], ob[l]};
+    a.blocks += tiles(M[l], BM) * tiles(N[l], 64);
   }
-  const int kc = ((K + splits - 1) / splits + BK - 1) / BK * BK;
-  splits = (K + kc - 1) / kc;
-  dim3 grid(gn, gm, splits);
-  if (splits > 1) {
-    // plain partial products; the reduction applies the mask
-    gemm_kernel<TA, TB, EPI_PLAIN><<<grid, GT, 0, st>>>(M, N, K, kc, A, lda, B, ldb, ws, ldc,
-                                                         nullptr, nullptr, 0, nullptr, nullptr);
-    const int64_t n = (int64_t)M * N;
-    if (EPI == EPI_MASK)
-      splitk_sum_mask_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(n, N, splits, ws, mask,
-                                                                          ldm, C);
-    else
-      splitk_sum_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(n, splits, ws, C);
-  } else {
-    gemm_kernel<TA, TB, EPI><<<grid, GT, 0, st>>>(M, N, K, kc, A, lda, B, ldb, C, ldc, bias, mask,
-                                                   ldm, mu, sd);
+  a.batch = batch;
+  a.splits = grad_splits(batch);
+  a.ws = n->ws;
+  a.n_params = n->n_params;
+  a.part = n->part;
+  a.n_part = (int64_t)tiles(batch, BM) * tiles(n->n_out, LN);
+  a.scale = scale;
+  a.loss = loss;
+  grad_kernel<<<a.blocks * a.splits + (loss ? 1 : 0), GT, 0, st>>>(a);
+  const unsigned gp = (unsigned)((n->n_params + 255) / 256);
+  if (lr > 0.f) {
+    n->step += 1;
+    const float c1 = 1.f - (float)std::pow(0.9, (double)n->step);
+    const float c2 = 1.f - (float)std::pow(0.999, (double)n->step);
+    step_kernel<true><<<gp, 256, 0, st>>>(n->n_params, a.splits, n->ws, nullptr, n->p, n->am, n->av,
+                                          lr, 0.9f, 0.999f, 1e-8f, c1, c2);
+  } else if (g) {
+    step_kernel<false><<<gp, 256, 0, st>>>(n->n_params, a.splits, n->ws, g, nullptr, nullptr, nullptr,
+                                           0.f, 0.f, 0.f, 0.f, 1.f, 1.f);
   }
-}
-
-void colsum(int rows, int cols, const float* dY, float* db, float* cs, hipStream_t st) {
-  const int nk = (rows + CS_ROWS - 1) / CS_ROWS;
-  colsum_part_kernel<<<dim3((cols + 255) / 256, nk), 256, 0, st>>>(rows, cols, dY, cs);
-  splitk_sum_kernel<<<(cols + 255) / 256, 256, 0, st>>>(cols, nk, cs, db);
-}
-
-// forward: h1 = relu(x W1^T + b1), h2 = relu(h1 W2^T + b2),
-// yhat = h2 W3^T + b3; with denorm, y = mu + sd * yhat.
-void forward(admm_mlp* n, const float* x, int batch, float* y, hipStream_t st, bool denorm) {
-  gemm<false, true, EPI_BIAS_RELU>(batch, n->hid, n->n_in, x, n->n_in, n->p + n->oW1, n->n_in, n->h1,
-                                   n->hid, n->p + n->ob1, nullptr, 0, st);
-  gemm<false, true, EPI_BIAS_RELU>(batch, n->hid, n->hid, n->h1, n->hid, n->p + n->oW2, n->hid, n->h2,
-                                   n->hid, n->p + n->ob2, nullptr, 0, st);
-  if (denorm)
-    gemm<false, true, EPI_BIAS_AFFINE>(batch, n->n_out, n->hid, n->h2, n->hid, n->p + n->oW3,
-                                       n->hid, y, n->n_out, n->p + n->ob3, nullptr, 0, st, n->mu,
-                                       n->sd);
-  else
-    gemm<false, true, EPI_BIAS>(batch, n->n_out, n->hid, n->h2, n->hid, n->p + n->oW3, n->hid, y,
-                                n->n_out, n->p + n->ob3, nullptr, 0, st);
-}
-
-// gradients of mean((y - t)^2) into n->g; loss (device scalar) when non-null
-void backward(admm_mlp* n, const float* x, const float* tg, int batch, float* loss, hipStream_t st) {
-  forward(n, x, batch, n->y, st, false);
-  const int64_t ny = (int64_t)batch * n->n_out;
-  const float scale = 1.f / (float)ny;
-  mse_grad_kernel<<<LOSS_BLOCKS, 256, 0, st>>>(ny, n->n_out, n->y, tg, n->mu, n->sd, scale, n->dy,
-                                                n->part);
-  if (loss) finish_loss_kernel<<<1, 64, 0, st>>>(LOSS_BLOCKS, n->part, scale, loss);
-  float* g = n->g;
-  // layer 3
-  gemm<true, false, EPI_PLAIN>(n->n_out, n->hid, batch, n->dy, n->n_out, n->h2, n->hid, g + n->oW3,
-                               n->hid, nullptr, nullptr, 0, st, nullptr, nullptr, n->ws, n->ws_n);
-  colsum(batch, n->n_out, n->dy, g + n->ob3, n->cs, st);
-  gemm<false, false, EPI_MASK>(batch, n->hid, n->n_out, n->dy, n->n_out, n->p + n->oW3, n->hid,
-                               n->dh2, n->hid, nullptr, n->h2, n->hid, st, nullptr, nullptr, n->ws, n->ws_n);
-  // layer 2
-  gemm<true, false, EPI_PLAIN>(n->hid, n->hid, batch, n->dh2, n->hid, n->h1, n->hid, g + n->oW2,
-                               n->hid, nullptr, nullptr, 0, st, nullptr, nullptr, n->ws, n->ws_n);
-  colsum(batch, n->hid, n->dh2, g + n->ob2, n->cs, st);
-  gemm<false, false, EPI_MASK>(batch, n->hid, n->hid, n->dh2, n->hid, n->p + n->oW2, n->hid,
-                               n->dh1, n->hid, nullptr, n->h1, n->hid, st, nullptr, nullptr, n->ws, n->ws_n);
-  // layer 1
-  gemm<true, false, EPI_PLAIN>(n->hid, n->n_in, batch, n->dh1, n->hid, x, n->n_in, g + n->oW1,
-                               n->n_in, nullptr, nullptr, 0, st, nullptr, nullptr, n->ws, n->ws_n);
-  colsum(batch, n->hid, n->dh1, g + n->ob1, n->cs, st);
 }
 
 }  // namespace
@@ -460,25 +651,16 @@ admm_status admm_mlp_create(int32_t n_in, int32_t hidden, int32_t n_out, int32_t
   admm_status s;
   const int64_t B = max_batch;
   if ((s = mlp_alloc(n.get(), &n->p, n->n_params))) return s;
-  if ((s = mlp_alloc(n.get(), &n->g, n->n_params))) return s;
   if ((s = mlp_alloc(n.get(), &n->am, n->n_params))) return s;
   if ((s = mlp_alloc(n.get(), &n->av, n->n_params))) return s;
   if ((s = mlp_alloc(n.get(), &n->h1, B * hidden))) return s;
   if ((s = mlp_alloc(n.get(), &n->h2, B * hidden))) return s;
-  if ((s = mlp_alloc(n.get(), &n->y, B * n_out))) return s;
   if ((s = mlp_alloc(n.get(), &n->dy, B * n_out))) return s;
   if ((s = mlp_alloc(n.get(), &n->dh1, B * hidden))) return s;
   if ((s = mlp_alloc(n.get(), &n->dh2, B * hidden))) return s;
-  if ((s = mlp_alloc(n.get(), &n->part, LOSS_BLOCKS))) return s;
+  if ((s = mlp_alloc(n.get(), &n->part, (int64_t)tiles(max_batch, BM) * tiles(n_out, LN)))) return s;
   if ((s = mlp_alloc(n.get(), &n->mu, n_out))) return s;
-  {
-    const int64_t big = std::max<int64_t>((int64_t)n_out * hidden,
-                                          std::max<int64_t>((int64_t)hidden * hidden, (int64_t)hidden * n_in));
-    n->ws_n = std::max<int64_t>(big, (int64_t)max_batch * hidden) * MAX_SPLITS / 4;
-    if ((s = mlp_alloc(n.get(), &n->ws, n->ws_n))) return s;
-    const int64_t chunks = (max_batch + CS_ROWS - 1) / CS_ROWS;
-    if ((s = mlp_alloc(n.get(), &n->cs, chunks * std::max(n_out, hidden)))) return s;
-  }
+  if ((s = mlp_alloc(n.get(), &n->ws, n->n_params * grad_splits(max_batch)))) return s;
   if ((s = mlp_alloc(n.get(), &n->sd, n_out))) return s;
   fill_kernel<<<(n_out + 255) / 256, 256>>>(n_out, 0.f, n->mu);
   fill_kernel<<<(n_out + 255) / 256, 256>>>(n_out, 1.f, n->sd);
@@ -517,7 +699,7 @@ admm_status admm_mlp_forward(admm_mlp* n, const float* x, int32_t batch, float* 
   if (!n || !x || !y) return admmi::set_err(ADMM_E_ARG, "NULL argument");
   if (batch < 1 || batch > n->max_batch) return admmi::set_err(ADMM_E_ARG, "batch out of [1, max_batch]");
   ADMM_HIP(hipSetDevice(n->device));
-  forward(n, x, batch, y, (hipStream_t)stream, true);
+  forward(n, x, batch, y, (hipStream_t)stream);
   ADMM_HIP(hipGetLastError());
   return ADMM_OK;
 }
@@ -529,8 +711,7 @@ admm_status admm_mlp_grads(admm_mlp* n, const float* x, const float* target, int
   if (batch < 1 || batch > n->max_batch) return admmi::set_err(ADMM_E_ARG, "batch out of [1, max_batch]");
   ADMM_HIP(hipSetDevice(n->device));
   hipStream_t st = (hipStream_t)stream;
-  backward(n, x, target, batch, loss, st);
-  if (grads) ADMM_HIP(hipMemcpyAsync(grads, n->g, n->n_params * sizeof(float), hipMemcpyDeviceToDevice, st));
+  backward(n, x, target, batch, loss, grads, 0.f, st);
   ADMM_HIP(hipGetLastError());
   return ADMM_OK;
 }
@@ -542,14 +723,7 @@ admm_status admm_mlp_train_step(admm_mlp* n, const float* x, const float* target
   if (batch < 1 || batch > n->max_batch) return admmi::set_err(ADMM_E_ARG, "batch out of [1, max_batch]");
   if (!(lr > 0.f)) return admmi::set_err(ADMM_E_ARG, "lr must be > 0");
   ADMM_HIP(hipSetDevice(n->device));
-  hipStream_t st = (hipStream_t)stream;
-  backward(n, x, target, batch, loss, st);
-  n->step += 1;
-  const float b1 = 0.9f, b2 = 0.999f;
-  const float c1 = 1.f - (float)std::pow(0.9, (double)n->step);
-  const float c2 = 1.f - (float)std::pow(0.999, (double)n->step);
-  adam_kernel<<<(unsigned)((n->n_params + 255) / 256), 256, 0, st>>>(n->n_params, n->p, n->g, n->am,
-                                                                     n->av, lr, b1, b2, 1e-8f, c1, c2);
+  backward(n, x, target, batch, loss, nullptr, lr, (hipStream_t)stream);
   ADMM_HIP(hipGetLastError());
   return ADMM_OK;
 }

@@ -96,13 +96,26 @@ struct Engine : EngineBase {
     return put(p, t);
   }
 
+  bool teams = false;   // resident driver: several blocks side by side
   template <bool A1>
-  static const void* resident_fn() {
-    return reinterpret_cast<const void*>(&resident_kernel<T, A1>);
+  const void* resident_fn() const {
+    return teams ? reinterpret_cast<const void*>(&resident_team_kernel<T, A1>)
+                 : reinterpret_cast<const void*>(&resident_kernel<T, A1>);
+  }
+
+  // Whether the team kernel can run this plan: every block of both passes
+  // free of barriers.
+  static bool teams_ok(const Plan& P) {
+    if (!P.var_b.empty() || !P.var_t.empty()) return false;
+    for (const BucketDesc& b : P.bt)
+      if (!(b.mode == BM_GEN_SLOT || (b.mode == BM_GEN_FACTOR && (b.kind == KD_NONOVERLAP || b.kind == KD_WALL || b.kind == KD_EQUAL))))
+        return false;
+    return true;
   }
 
   admm_status resident_check(const Plan& P, int64_t nz_, bool a1) override {
     const int64_t bytes = resident_image_bytes(P, nz_, (int64_t)sizeof(T));
+    teams = teams_ok(P);
     hipFuncAttributes fa;
     ADMM_HIP(hipFuncGetAttributes(&fa, a1 ? resident_fn<true>() : resident_fn<false>()));
     int maxsh = 0;
@@ -449,12 +462,10 @@ struct Engine : EngineBase {
     r.iters = iters;
     const XArgs<T> xa = xargs();
     const ZArgs<T> za = zargs(0);
-    if (alpha1)
-      hipExtLaunchKernelGGL((resident_kernel<T, true>), dim3(1), dim3(NT), res_lds, st, e0, e1, 0,
-                            xa, za, r);
-    else
-      hipExtLaunchKernelGGL((resident_kernel<T, false>), dim3(1), dim3(NT), res_lds, st, e0, e1, 0,
-                            xa, za, r);
+    const dim3 nt = teams ? dim3(NT, TEAMS) : dim3(NT);
+    const auto kern = alpha1 ? (teams ? resident_team_kernel<T, true> : resident_kernel<T, true>)
+                             : (teams ? resident_team_kernel<T, false> : resident_kernel<T, false>);
+    hipExtLaunchKernelGGL(kern, dim3(1), nt, res_lds, st, e0, e1, 0, xa, za, r);
     if (iters & 1) zc ^= 1;
   }
 

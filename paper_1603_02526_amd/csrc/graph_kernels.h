@@ -22,6 +22,7 @@
 namespace admmg {
 
 constexpr int NT = 256;              // threads per workgroup, every pass
+constexpr int TEAMS = 4;             // rows of NT threads of the resident driver's team kernel
 constexpr int PB = 64;               // entity block of dense pair tiles
 constexpr int PR = PB * PB / NT;     // pair rows per thread
 constexpr int MAXN = 16;             // lindyn state dim limit (general path)
@@ -138,7 +139,8 @@ __device__ __forceinline__ T tmin(T a, T b) { return a < b ? a : b; }
 // plain max can drop a NaN operand).
 template <typename T>
 __device__ __forceinline__ void block_max_store(T v, T* out) {
-  __shared__ T red[NT / 64];
+  __shared__ T reds[TEAMS][NT / 64];
+  T* red = reds[threadIdx.y];   // one row of threads, except in resident teams
   if (!(v == v)) v = T(INFINITY);
   v = admmi::wave_max(v);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
@@ -2041,13 +2043,14 @@ struct ResArgs {
   T* z_back[2];     // global z buffers (the final z is copied to z_back[final index])
 };
 
-template <typename T, bool A1>
-__global__ __launch_bounds__(NT) void resident_kernel(XArgs<T> xa, ZArgs<T> za, ResArgs<T> r) {
-  extern __shared__ __align__(16) unsigned char lds_img[];
+// The regions into LDS, thread t of nt.
+template <typename T>
+__device__ __forceinline__ void resident_load(const ResArgs<T>& r, unsigned char* lds_img, int t,
+                                              int nt, XArgs<T>& xa, ZArgs<T>& za) {
   for (int q = 0; q < r.nreg; ++q) {
     const uint32_t* src = (const uint32_t*)r.reg[q].src;
     uint32_t* dst = (uint32_t*)(lds_img + r.reg[q].off);
-    for (int i = threadIdx.x; i < r.reg[q].words; i += NT) dst[i] = src[i];
+    for (int i = t; i < r.reg[q].words; i += nt) dst[i] = src[i];
   }
   __syncthreads();
   xa.pool = (T*)(lds_img + r.o_pool);
@@ -2063,6 +2066,27 @@ __global__ __launch_bounds__(NT) void resident_kernel(XArgs<T> xa, ZArgs<T> za, 
   za.deg_w = (const T*)(lds_img + r.o_deg_w);
   za.var_l = (const int32_t*)(lds_img + r.o_var_l);
   za.deg_l = (const T*)(lds_img + r.o_deg_l);
+}
+
+// What changed, and the final z, back to memory.
+template <typename T>
+__device__ __forceinline__ void resident_store(const ResArgs<T>& r, const unsigned char* lds_img,
+                                               int t, int nt, int zc) {
+  for (int q = 0; q < r.nreg; ++q) {
+    if (!r.reg[q].back) continue;
+    const uint32_t* src = (const uint32_t*)(lds_img + r.reg[q].off);
+    uint32_t* dst = (uint32_t*)r.reg[q].back;
+    for (int i = t; i < r.reg[q].words; i += nt) dst[i] = src[i];
+  }
+  const uint32_t* zs = (const uint32_t*)(lds_img + (zc ? r.o_z1 : r.o_z0));
+  uint32_t* zd = (uint32_t*)r.z_back[zc];
+  for (int i = t; i < r.z_words; i += nt) zd[i] = zs[i];
+}
+
+template <typename T, bool A1>
+__global__ __launch_bounds__(NT) void resident_kernel(XArgs<T> xa, ZArgs<T> za, ResArgs<T> r) {
+  extern __shared__ __align__(16) unsigned char lds_img[];
+  resident_load(r, lds_img, threadIdx.x, NT, xa, za);
   // z buffers are addressed as lds_img + offset each iteration (not through a
   // pointer carried across iterations) so that every z access stays an LDS
   // access.
@@ -2092,15 +2116,62 @@ __global__ __launch_bounds__(NT) void resident_kernel(XArgs<T> xa, ZArgs<T> za, 
     xpass_block<T, A1, PM_RESID, FS_RES>(xa, b, find_bucket(xa, b));
     __syncthreads();
   }
-  for (int q = 0; q < r.nreg; ++q) {
-    if (!r.reg[q].back) continue;
-    const uint32_t* src = (const uint32_t*)(lds_img + r.reg[q].off);
-    uint32_t* dst = (uint32_t*)r.reg[q].back;
-    for (int i = threadIdx.x; i < r.reg[q].words; i += NT) dst[i] = src[i];
+  resident_store(r, lds_img, threadIdx.x, NT, zc);
+}
+
+// The resident driver for graphs whose passes need no barrier inside a block
+// (general non-overlap, wall, equality and separable factors; no long
+// z-list): TEAMS rows of NT threads take the blocks of a pass side by side,
+// so a pass over up to TEAMS blocks costs the latency of one.  The same
+// blocks and the same arithmetic as resident_kernel.  What bounds it: the
+// dependent LDS reads of a pass (index, z, m) and its barrier.  10 disks (3
+// and 2 blocks): a solve of 100 iterations with its transfers 216 us against 534.
+constexpr int FS_TEAM = FT_GEN;
+
+template <typename T, bool A1>
+__global__ __launch_bounds__(NT * TEAMS) void resident_team_kernel(XArgs<T> xa, ZArgs<T> za,
+                                                                   ResArgs<T> r) {
+  extern __shared__ __align__(16) unsigned char lds_img[];
+  const int team = __builtin_amdgcn_readfirstlane((int)threadIdx.y);
+  const int tid = team * NT + (int)threadIdx.x;
+  resident_load(r, lds_img, tid, NT * TEAMS, xa, za);
+  int zc = r.zc;
+  const int32_t zoff[2] = {r.o_z0, r.o_z1};
+  // a team's first block stays the same: its bucket is looked up once
+  const BucketDesc b0 = find_bucket(xa, team < r.xblocks ? team : 0);
+  for (int k = 0; k < r.iters; ++k) {
+    const bool last = (k == r.iters - 1);
+    xa.z = (const T*)(lds_img + zoff[zc]);
+    for (int b = team; b < r.xblocks; b += TEAMS) {
+      const BucketDesc d = b == team ? b0 : find_bucket(xa, b);
+      if (A1 && last)
+        xpass_block<T, A1, PM_SAVE, FS_TEAM>(xa, b, d);
+      else
+        xpass_block<T, A1, PM_NORMAL, FS_TEAM>(xa, b, d);
+    }
+    __syncthreads();
+    za.zin = (const T*)(lds_img + zoff[zc]);
+    za.zout = (T*)(lds_img + zoff[zc ^ 1]);
+    za.check = last ? 1 : 0;
+    // the residual maximum of a checked block holds one barrier: every team
+    // meets it as often
+    for (int b = 0; b < r.zblocks; b += TEAMS) {
+      if (b + team < r.zblocks) zpass_block<T>(za, b + team);
+      else if (last) __syncthreads();
+      if (last) __syncthreads();
+    }
+    __syncthreads();
+    zc ^= 1;
   }
-  const uint32_t* zs = (const uint32_t*)(lds_img + zoff[zc]);
-  uint32_t* zd = (uint32_t*)r.z_back[zc];
-  for (int i = threadIdx.x; i < r.z_words; i += NT) zd[i] = zs[i];
+  xa.z = (const T*)(lds_img + zoff[zc]);
+  for (int b = 0; b < r.xblocks; b += TEAMS) {
+    if (b + team < r.xblocks)
+      xpass_block<T, A1, PM_RESID, FS_TEAM>(xa, b + team, find_bucket(xa, b + team));
+    else
+      __syncthreads();
+    __syncthreads();
+  }
+  resident_store(r, lds_img, tid, NT * TEAMS, zc);
 }
 
 // State import: m = u + z_b (x = z_b) for every user slot.

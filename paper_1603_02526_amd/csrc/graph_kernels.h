@@ -202,6 +202,18 @@ __device__ __forceinline__ bool prox_nonoverlap(T* v) {
   return moved;
 }
 
+// Whether the discs of a non-overlap factor are surely apart (its prox then
+// leaves n unchanged): r1 + r2 against |c2 - c1| without the root, with a
+// relative margin far above its rounding.  A wavefront without contact skips
+// the root and the reciprocal, some 60 FP64 instructions.
+template <typename T>
+__device__ __forceinline__ bool surely_apart(const T* v) {
+  constexpr bool D = sizeof(T) == 8;
+  const T dx = v[3] - v[0], dy = v[4] - v[1], S = v[2] + v[5];
+  const T L2 = dx * dx + dy * dy;
+  return !(S > T(0)) || (S * S < L2 * (T(1) - T(D ? 0x1p-40 : 0x1p-18)) && L2 > T(D ? 1e-280 : 1e-28));
+}
+
 // Wall Q^T(c - V) >= r; p = (Qx, Qy, Q.V, 1/(|Q|^2+1)).  Returns whether
 // the constraint was active (the prox moved its input).
 template <typename T>
@@ -278,6 +290,62 @@ __device__ __forceinline__ void pair_tile(const BucketDesc& b, const int32_t* ti
   }
 }
 
+// Lane exchanges for sums over lane groups.  dpp: a DPP permutation within
+// 16-lane rows.  swap32_add: the sums of a over lanes 32 apart in the lower
+// half, of b in the upper; swap16_add: of a over lanes 16 apart in the even
+// rows, of b in the odd; pair16 / pair32: v plus the value 16 / 32 lanes away
+// (the same order of addends in both lanes).
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) { return ADMM_DPP(v, CTRL, 0xF); }
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, false);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+typedef unsigned int u2v __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ float swap32_add(float a, float b) {
+  const u2v r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float swap16_add(float a, float b) {
+  const u2v r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ double swap32_add(double a, double b) {
+  const long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+  const u2v l = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
+  const u2v h = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+  return __longlong_as_double(((long long)h[0] << 32) | l[0]) +
+         __longlong_as_double(((long long)h[1] << 32) | l[1]);
+}
+__device__ __forceinline__ double swap16_add(double a, double b) {
+  const long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+  const u2v l = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
+  const u2v h = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+  return __longlong_as_double(((long long)h[0] << 32) | l[0]) +
+         __longlong_as_double(((long long)h[1] << 32) | l[1]);
+}
+template <typename T>
+__device__ __forceinline__ T pair16(T v) { return swap16_add(v, v); }
+template <typename T>
+__device__ __forceinline__ T pair32(T v) { return swap32_add(v, v); }
+
+// Four rows' values at once: v[q] holds row q's value of every lane; the
+// result in lane l is the sum of row l / 16 over the wavefront.  Two swaps
+// scatter the rows over the lane rows while adding (three exchanges for four
+// rows), then each 16-lane row adds up; a fixed order.
+template <typename T>
+__device__ __forceinline__ T four_row_sums(const T (&v)[4]) {
+  T s = swap16_add(swap32_add(v[0], v[2]), swap32_add(v[1], v[3]));
+  s += dpp<0xB1>(s);    // quad_perm [1,0,3,2]
+  s += dpp<0x4E>(s);    // quad_perm [2,3,0,1]
+  s += dpp<0x141>(s);   // row_half_mirror: the other quad
+  s += dpp<0x140>(s);   // row_mirror: the other eight lanes
+  return s;
+}
+
 // ---------------------------------------------------------------------------
 // Dense pairwise non-overlap tiles.  Tile (I, J) holds the pairs
 // (e_i, e_j) = (I*RB + li, J*64 + lj), li < RB, lj < 64, of which those with
@@ -287,7 +355,11 @@ __device__ __forceinline__ void pair_tile(const BucketDesc& b, const int32_t* ti
 // columns in registers and then across the four wavefronts.
 // Partials per tile: [row li][3] (RB rows) then [col lj][3] (64 columns).
 // ---------------------------------------------------------------------------
-constexpr int PAIR_UNROLL_F64 = 4;   // FP64 pair rows per unrolled step
+// What bounds it: for many tiles memory (96 B per FP64 pair), for few the
+// issue of a wavefront's 16 rows.  1000 disks in FP64 (136 tiles): 16.2 us per
+// x-pass, 20.0 while every pair took the root and every row its own three
+// wavefront sums; 2000 disks 36.8 (37.3).  All 16 rows' loads in flight: 14.9
+// and 40.0.
 template <typename T, bool A1, int MODE, int RB>
 __device__ __forceinline__ void xpass_pair(const XArgs<T>& a, const BucketDesc& b, int tile) {
   constexpr int CB = PB;              // columns per tile
@@ -325,72 +397,70 @@ __device__ __forceinline__ void xpass_pair(const XArgs<T>& a, const BucketDesc& 
   T* mt = a.pool + b.m_off + (int64_t)tile * TS;
   T* xt = a.pool + b.x_off + (int64_t)tile * TS;
   T ca0 = T(0), ca1 = T(0), ca2 = T(0);
-  T rv0 = T(0), rv1 = T(0), rv2 = T(0);
   T rmax = T(0);
+  const int32_t* dst = a.idx + b.dst_off + (int64_t)tile * (3 * (RB + CB));
   // FP64: rows four at a time, so that the loads in flight stay within the
   // registers of four wavefronts per SIMD
-  constexpr int UNR = sizeof(T) == 8 ? PAIR_UNROLL_F64 : PRR;
+  constexpr int UNR = sizeof(T) == 8 ? 1 : PRR / 4;
 #pragma unroll UNR
-  for (int k = 0; k < PRR; ++k) {
-    const int li = w * PRR + k;
-    const int ei = I * RB + li;
-    const bool valid = (ei < ej) && (ej < b.E);
-    const int p = li * CB + lj;
-    const T zz[6] = {zrow[li * 3 + 0], zrow[li * 3 + 1], zrow[li * 3 + 2], zj0, zj1, zj2};
-    T mv[6];
+  for (int k0 = 0; k0 < PRR; k0 += 4) {
+    T rs[3][4];   // the four rows' values to sum over the columns
+    T mv[4][6], xv[4][6];
 #pragma unroll
-    for (int s = 0; s < 6; ++s) mv[s] = mt[s * TSZ + p];
-    if constexpr (MODE == PM_RESID) {
+    for (int k = 0; k < 4; ++k)
 #pragma unroll
       for (int s = 0; s < 6; ++s) {
-        const T xv = xt[s * TSZ + p];
-        if (valid) rmax = tmax(rmax, tabs(xv - zz[s]));
+        const int p = (w * PRR + k0 + k) * CB + lj;
+        if constexpr (MODE != PM_RESID) mv[k][s] = mt[s * TSZ + p];
+        if constexpr (!A1 || MODE == PM_RESID) xv[k][s] = xt[s * TSZ + p];
       }
-    } else {
-      T u[6], v[6];
 #pragma unroll
-      for (int s = 0; s < 6; ++s) {
-        T xo = T(0);
-        if constexpr (!A1) xo = xt[s * TSZ + p];
-        state_un<T, A1>(mv[s], xo, zz[s], (T)b.alpha, u[s], v[s]);
-      }
-      prox_nonoverlap(v);
-      T mn[6];
+    for (int k = 0; k < 4; ++k) {
+      const int li = w * PRR + k0 + k;
+      const int ei = I * RB + li;
+      const bool valid = (ei < ej) && (ej < b.E);
+      const int p = li * CB + lj;
+      const T zz[6] = {zrow[li * 3 + 0], zrow[li * 3 + 1], zrow[li * 3 + 2], zj0, zj1, zj2};
+      if constexpr (MODE == PM_RESID) {
 #pragma unroll
-      for (int s = 0; s < 6; ++s) mn[s] = v[s] + u[s];
-      if (valid) {
+        for (int s = 0; s < 6; ++s)
+          if (valid) rmax = tmax(rmax, tabs(xv[k][s] - zz[s]));
+      } else {
+        T u[6], v[6];
 #pragma unroll
-        for (int s = 0; s < 6; ++s) {
-          mt[s * TSZ + p] = mn[s];
-          if constexpr (!A1 || MODE == PM_SAVE) xt[s * TSZ + p] = v[s];
+        for (int s = 0; s < 6; ++s)
+          state_un<T, A1>(mv[k][s], A1 ? T(0) : xv[k][s], zz[s], (T)b.alpha, u[s], v[s]);
+        if (!surely_apart(v)) prox_nonoverlap(v);
+        T mn[6];
+#pragma unroll
+        for (int s = 0; s < 6; ++s) mn[s] = v[s] + u[s];
+        if (valid) {
+#pragma unroll
+          for (int s = 0; s < 6; ++s) {
+            mt[s * TSZ + p] = mn[s];
+            if constexpr (!A1 || MODE == PM_SAVE) xt[s * TSZ + p] = v[s];
+          }
         }
+        ca0 += valid ? mn[3] : T(0);
+        ca1 += valid ? mn[4] : T(0);
+        ca2 += valid ? mn[5] : T(0);
+#pragma unroll
+        for (int s = 0; s < 3; ++s) rs[s][k] = valid ? mn[s] : T(0);
       }
-      ca0 += valid ? mn[3] : T(0);
-      ca1 += valid ? mn[4] : T(0);
-      ca2 += valid ? mn[5] : T(0);
-      const T r0 = admmi::wave_sum(valid ? mn[0] : T(0));
-      const T r1 = admmi::wave_sum(valid ? mn[1] : T(0));
-      const T r2 = admmi::wave_sum(valid ? mn[2] : T(0));
-      if (lane == k) {
-        rv0 = r0;
-        rv1 = r1;
-        rv2 = r2;
+    }
+    if constexpr (MODE != PM_RESID) {
+      // lane row l / 16 gets tile row k0 + l / 16; its lanes 0..2 store
+      const T r0 = four_row_sums(rs[0]), r1 = four_row_sums(rs[1]), r2 = four_row_sums(rs[2]);
+      const int q = lane & 15;
+      if (q < 3) {
+        const int d = dst[(w * PRR + k0 + (lane >> 4)) * 3 + q];
+        if (d >= 0) a.pool[d] = q == 0 ? r0 : (q == 1 ? r1 : r2);
       }
     }
   }
   if constexpr (MODE == PM_RESID) {
     block_max_store(rmax, a.blockmax);
   } else {
-    const int32_t* dst = a.idx + b.dst_off + (int64_t)tile * (3 * (RB + CB));
-    if (lane < PRR) {
-      const int li = w * PRR + lane;
-      const int d0 = dst[li * 3];
-      if (d0 >= 0) {
-        a.pool[d0] = rv0;
-        a.pool[dst[li * 3 + 1]] = rv1;
-        a.pool[dst[li * 3 + 2]] = rv2;
-      }
-    }
     cacc[w][lj * 3 + 0] = ca0;
     cacc[w][lj * 3 + 1] = ca1;
     cacc[w][lj * 3 + 2] = ca2;
@@ -1026,42 +1096,6 @@ __device__ __forceinline__ void xpass_hinge(const XArgs<T>& a, const BucketDesc&
   }
 }
 
-// Lane exchanges for sums over lane groups.  dpp: a DPP permutation within
-// 16-lane rows; pair16 / pair32: v plus the value 16 / 32 lanes away (the
-// same order of addends in both lanes).
-template <int CTRL>
-__device__ __forceinline__ float dpp(float v) { return ADMM_DPP(v, CTRL, 0xF); }
-template <int CTRL>
-__device__ __forceinline__ double dpp(double v) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, false);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-typedef unsigned int u2v __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ float pair16(float v) {
-  const u2v r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-__device__ __forceinline__ float pair32(float v) {
-  const u2v r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-__device__ __forceinline__ double pair16(double v) {
-  const long long b = __double_as_longlong(v);
-  const u2v l = __builtin_amdgcn_permlane16_swap((unsigned)b, (unsigned)b, false, false);
-  const u2v h = __builtin_amdgcn_permlane16_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
-  return __longlong_as_double(((long long)h[0] << 32) | l[0]) +
-         __longlong_as_double(((long long)h[1] << 32) | l[1]);
-}
-__device__ __forceinline__ double pair32(double v) {
-  const long long b = __double_as_longlong(v);
-  const u2v l = __builtin_amdgcn_permlane32_swap((unsigned)b, (unsigned)b, false, false);
-  const u2v h = __builtin_amdgcn_permlane32_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
-  return __longlong_as_double(((long long)h[0] << 32) | l[0]) +
-         __longlong_as_double(((long long)h[1] << 32) | l[1]);
-}
-
 // Hinge factors that all list the same variables (the SVM).  A workgroup
 // takes FB = FL V consecutive factors (V of them fill 16 bytes) and their
 // d + 1 edges, the b edge last (its parameter is y): lane (r, fl) = (t / FL,
@@ -1497,7 +1531,7 @@ __device__ __forceinline__ void xpass_geom(const XArgs<T>& a, const BucketDesc& 
       T u[6], v[6];
       gen_gather<T, A1, MODE, 6>(a, b, f, dims, 4, u, v, rmax);
       if constexpr (MODE != PM_RESID) {
-        prox_nonoverlap(v);
+        if (sizeof(T) == 4 || !surely_apart(v)) prox_nonoverlap(v);
         gen_store<T, A1, MODE, 6>(a, b, f, u, v);
       }
     } else {

@@ -478,7 +478,12 @@ mpc_solve_kernel(SolveArgs a) {
     __syncthreads();
     const int item = __builtin_amdgcn_readfirstlane(s_item);
     __syncthreads();
-    if (item >= a.n_items) break;
+    if (item >= a.n_items) {
+      // every workgroup passes here once: the last one leaves the queue as
+      // the next launch needs it
+      if (threadIdx.x == 0 && item == a.n_items + (int)gridDim.x - 1) atomicExch(a.counter, 0);
+      break;
+    }
     const int32_t* it = a.items + (int64_t)(MAXW + 1) * item;
     if (__builtin_amdgcn_readfirstlane(it[0]) == 0) {
       const int id = __builtin_amdgcn_readfirstlane(it[1 + w]);
@@ -491,10 +496,6 @@ mpc_solve_kernel(SolveArgs a) {
     }
     __syncthreads();
   }
-}
-
-__global__ void reset_counter_kernel(int32_t* c) {
-  if (threadIdx.x == 0) c[0] = 0;
 }
 
 // Dual completion from z: mu_{T-1} = Q x_T, mu_{t-1} = A^T mu_t + Q x_t, then
@@ -511,19 +512,36 @@ __global__ void reset_counter_kernel(int32_t* c) {
 //   qu = -R U[t], bx = B^T mu_t + R U[t], qx = -Q X[t], all divided by rho.
 // Lane i holds column i of A and of B; mu_t[j] reaches every lane of the
 // row by DPP row broadcast (row_newbcast:j), so a step is 2n FMAs.  The
-// instance's z is staged in LDS first.  Rows run max(T) steps; a row
-// whose instance is shorter or absent computes on zeros and stores
-// nothing.
+// instances' z is staged in LDS first (zrow floats each, the batch's longest)
+// by DUAL_T threads, enough that it takes one or two memory round trips; then
+// the first wavefront alone goes on.  Rows run max(T) steps; a row whose
+// instance is shorter or absent computes on zeros and stores nothing.
+// What bounds it: T dependent steps of n FMAs each.  2048 instances, T = 100,
+// n = 8: 36.1 us, 43.4 with one wavefront staging and twelve terms a step.
 template <int J>
 __device__ __forceinline__ float row_bcast(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + J, 0xF, 0xF, false));
 }
 
-__global__ __launch_bounds__(64) void mpc_dual_kernel(const MpcInst* inst, int32_t n_inst,
-                                                      const float* par, const float* z, float* u,
-                                                      float inv_rho) {
-  __shared__ float zs[4][TMAX * 16];
-  const int lane = threadIdx.x, row = lane >> 4, li = lane & 15;
+constexpr int DUAL_T = 256;
+__global__ __launch_bounds__(DUAL_T) void mpc_dual_kernel(const MpcInst* inst, int32_t n_inst,
+                                                          const float* par, const float* z,
+                                                          float* u, float inv_rho, int zrow) {
+  extern __shared__ float zs[];   // [4][zrow]
+  const int lane = threadIdx.x & 63, row = lane >> 4, li = lane & 15;
+  {
+    constexpr int PER = DUAL_T / 4;
+    const int r = threadIdx.x / PER, i = blockIdx.x * 4 + r;
+    if (i < n_inst) {
+      const MpcInst I = inst[i];
+      const float* zz = z + I.z_off;
+      const int count = I.T * (I.n + I.m);
+#pragma unroll 8
+      for (int e = threadIdx.x % PER; e < count; e += PER) zs[r * zrow + e] = zz[e];
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x >= 64) return;
   const int id = blockIdx.x * 4 + row;
   const bool have = id < n_inst;
   const MpcInst I = inst[have ? id : 0];
@@ -531,10 +549,6 @@ __global__ __launch_bounds__(64) void mpc_dual_kernel(const MpcInst* inst, int32
   const int N = pad_n(n);
   const ParOff o = par_offsets(N);
   const float* P = par + I.par_off;
-  const float* zz = z + I.z_off;
-  // eight loads in flight per lane before the first store waits
-#pragma unroll 8
-  for (int e = li; e < T * k; e += 16) zs[row][e] = zz[e];
   float acol[MN], bcol[MN];
 #pragma unroll
   for (int j = 0; j < MN; ++j) {
@@ -543,11 +557,13 @@ __global__ __launch_bounds__(64) void mpc_dual_kernel(const MpcInst* inst, int32
   }
   const float ql = li < n ? P[o.q + li] : 0.f;
   const float rl = li < m ? P[o.r + li] : 0.f;
-  __syncthreads();
-  int Tmax = T;
+  int Tmax = T, nmax = n;
   Tmax = max(Tmax, __shfl_xor(Tmax, 16, 64));
   Tmax = max(Tmax, __shfl_xor(Tmax, 32, 64));
-  const float* zr = zs[row];
+  nmax = max(nmax, __shfl_xor(nmax, 16, 64));
+  nmax = __builtin_amdgcn_readfirstlane(max(nmax, __shfl_xor(nmax, 32, 64)));
+  Tmax = __builtin_amdgcn_readfirstlane(Tmax);
+  const float* zr = zs + row * zrow;
   float mu = (T > 0 && li < n) ? ql * zr[(T - 1) * k + m + li] : 0.f;
   for (int s = 0; s < Tmax; ++s) {
     const int t = T - 1 - s;            // this row's step (< 0: nothing to do)
@@ -567,8 +583,12 @@ __global__ __launch_bounds__(64) void mpc_dual_kernel(const MpcInst* inst, int32
     b = fmaf(bcol[J], mj, b);               \
   }
     ADMM_DUAL_TERM(0) ADMM_DUAL_TERM(1) ADMM_DUAL_TERM(2) ADMM_DUAL_TERM(3)
-    ADMM_DUAL_TERM(4) ADMM_DUAL_TERM(5) ADMM_DUAL_TERM(6) ADMM_DUAL_TERM(7)
-    ADMM_DUAL_TERM(8) ADMM_DUAL_TERM(9) ADMM_DUAL_TERM(10) ADMM_DUAL_TERM(11)
+    if (nmax > 4) {   // uniform; terms past a row's n are zeros
+      ADMM_DUAL_TERM(4) ADMM_DUAL_TERM(5) ADMM_DUAL_TERM(6) ADMM_DUAL_TERM(7)
+    }
+    if (nmax > 8) {
+      ADMM_DUAL_TERM(8) ADMM_DUAL_TERM(9) ADMM_DUAL_TERM(10) ADMM_DUAL_TERM(11)
+    }
 #undef ADMM_DUAL_TERM
     if (t >= 0) {
       float* ut = u + I.u_off + (int64_t)t * 3 * k;
@@ -596,7 +616,11 @@ __global__ __launch_bounds__(64) void mpc_dual_kernel(const MpcInst* inst, int32
 // edge's dual moves with its step (the dynamics factor of step 0 has no x_t
 // edge, so that part of step 1 is dropped) and the new last step's duals are
 // zero; the duals around every variable keep their sum.
-// One workgroup per instance, one thread per step (T <= 256).
+// One workgroup per instance: the trajectory and the duals move as flat
+// arrays, coalesced; one lane per component of the two products, terms in
+// index order.  What bounds it: a memory round trip or two per instance.  64
+// instances of 20 to 200 steps: 5.9 us, 31.7 with a thread per step copying
+// its block and one thread on the products.
 __global__ __launch_bounds__(TMAX) void mpc_shift_kernel(
     const MpcInst* __restrict__ inst, const float* __restrict__ par, const float* __restrict__ x0,
     const float* __restrict__ z, const float* __restrict__ u, const float* __restrict__ w,
@@ -608,40 +632,38 @@ __global__ __launch_bounds__(TMAX) void mpc_shift_kernel(
   const ParOff o = par_offsets(Np);
   const float* P = par + I.par_off;
   const float* zi = z + I.z_off;
-  if (t == 0) {
+  if (t < n) {
     const float* xi = x0 + I.x0_off;
-    for (int r = 0; r < n; ++r) {
-      float s = 0.f;
-      for (int j = 0; j < n; ++j) s = fmaf(P[o.A + r * Np + j], xi[j], s);
-      for (int j = 0; j < m; ++j) s = fmaf(P[o.B + r * MM + j], zi[j], s);
-      if (w) s += w[I.x0_off + r];
-      x0n[I.x0_off + r] = s;
-    }
+    float s = 0.f;
+    for (int j = 0; j < n; ++j) s = fmaf(P[o.A + t * Np + j], xi[j], s);
+    for (int j = 0; j < m; ++j) s = fmaf(P[o.B + t * MM + j], zi[j], s);
+    if (w) s += w[I.x0_off + t];
+    x0n[I.x0_off + t] = s;
   }
-  if (t >= T) return;
   if (zn) {
-    float* zo = zn + I.z_off + (int64_t)t * k;
-    if (t + 1 < T) {
-      const float* src = zi + (int64_t)(t + 1) * k;
-      for (int q = 0; q < k; ++q) zo[q] = src[q];
-    } else {
-      const float* xT = zi + (int64_t)t * k + m;
-      for (int j = 0; j < m; ++j) zo[j] = 0.f;
-      for (int r = 0; r < n; ++r) {
-        float s = 0.f;
-        for (int j = 0; j < n; ++j) s = fmaf(P[o.A + r * Np + j], xT[j], s);
-        zo[m + r] = s;
-      }
+    float* zo = zn + I.z_off;
+    const int moved = (T - 1) * k;
+#pragma unroll 4
+    for (int e = t; e < moved; e += TMAX) zo[e] = zi[e + k];
+    if (t < m) zo[moved + t] = 0.f;
+    if (t >= 64 && t < 64 + n) {
+      const int r = t - 64;
+      const float* xT = zi + moved + m;
+      float s = 0.f;
+      for (int j = 0; j < n; ++j) s = fmaf(P[o.A + r * Np + j], xT[j], s);
+      zo[moved + m + r] = s;
     }
   }
   if (un) {
-    float* uo = un + I.u_off + (int64_t)t * 3 * k;
-    if (t + 1 < T) {
-      const float* src = u + I.u_off + (int64_t)(t + 1) * 3 * k;
-      for (int q = 0; q < 3 * k; ++q) uo[q] = (t == 0 && q < n) ? 0.f : src[q];
-    } else {
-      for (int q = 0; q < 3 * k; ++q) uo[q] = 0.f;
+    float* uo = un + I.u_off;
+    const float* ui = u + I.u_off;
+    const int k3 = 3 * k, moved = (T - 1) * k3;
+#pragma unroll 8
+    for (int e = t; e < moved; e += TMAX) {
+      const float v = ui[e + k3];
+      uo[e] = e < n ? 0.f : v;
     }
+    if (t < k3) uo[moved + t] = 0.f;
   }
 }
 
@@ -693,6 +715,7 @@ struct admm_mpc_batch {
   int resident = 0;          // workgroups resident per device at full occupancy
   bool short_h = false;      // every T <= TS
   int cus = 1;
+  int zrow = 0;              // most z entries of one instance
   std::vector<int32_t> measured;  // iterations per instance from the last tuning solve
   std::vector<void*> allocs;
   ~admm_mpc_batch() {
@@ -776,10 +799,14 @@ admm_status build_items(admm_mpc_batch* b, const Plan& pl) {
   return ADMM_OK;
 }
 
+void launch_dual(admm_mpc_batch* b, const float* z, float* u, hipStream_t st) {
+  mpc_dual_kernel<<<(b->n_inst + 3) / 4, DUAL_T, 4 * b->zrow * sizeof(float), st>>>(
+      b->d_inst, b->n_inst, b->d_par, z, u, (float)(1.0 / b->rho), b->zrow);
+}
+
 admm_status launch_solve(admm_mpc_batch* b, const float* x0, const float* zinit, const float* uinit,
                          float tol, int32_t max_iter, float* zout, float* uout, int32_t* iters,
                          hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
-  reset_counter_kernel<<<1, 64, 0, st>>>(b->d_counter);
   SolveArgs a;
   a.inst = b->d_inst;
   a.par = b->d_par;
@@ -840,6 +867,7 @@ admm_status admm_mpc_batch_create(int32_t n_inst, const int32_t* T, const int32_
     I.z_off = b->z_total;
     I.u_off = b->u_total;
     b->x0_total += ni;
+    b->zrow = std::max(b->zrow, T[i] * ki);
     b->z_total += (int64_t)T[i] * ki;
     b->u_total += (int64_t)T[i] * 3 * ki;
     const double* Ai = A + aoff;
@@ -908,6 +936,7 @@ admm_status admm_mpc_batch_create(int32_t n_inst, const int32_t* T, const int32_
   if ((s = mpc_alloc(b.get(), (void**)&b->d_u, sizeof(float) * b->u_total))) return s;
   if ((s = mpc_alloc(b.get(), (void**)&b->d_items, sizeof(int32_t) * (MAXW + 1) * (size_t)n_inst))) return s;
   if ((s = mpc_alloc(b.get(), (void**)&b->d_counter, sizeof(int32_t)))) return s;
+  ADMM_HIP(hipMemset(b->d_counter, 0, sizeof(int32_t)));
   ADMM_HIP(hipMemcpy(b->d_inst, b->h_inst.data(), sizeof(MpcInst) * n_inst, hipMemcpyHostToDevice));
   ADMM_HIP(hipMemcpy(b->d_par, par.data(), sizeof(float) * par.size(), hipMemcpyHostToDevice));
   int per_cu = 0;
@@ -939,8 +968,7 @@ admm_status admm_mpc_batch_dual_complete(admm_mpc_batch* b, const float* z, floa
   admmi::clear_err();
   if (!b || !z || !u) return admmi::set_err(ADMM_E_ARG, "NULL argument");
   ADMM_HIP(hipSetDevice(b->device));
-  mpc_dual_kernel<<<(b->n_inst + 3) / 4, 64, 0, (hipStream_t)stream>>>(b->d_inst, b->n_inst, b->d_par, z, u,
-                                                              (float)(1.0 / b->rho));
+  launch_dual(b, z, u, (hipStream_t)stream);
   ADMM_HIP(hipGetLastError());
   return ADMM_OK;
 }
@@ -957,8 +985,7 @@ admm_status admm_mpc_batch_solve(admm_mpc_batch* b, const float* x0, const float
   hipStream_t st = (hipStream_t)stream;
   const float* uinit = nullptr;
   if (dual_mode == 1) {
-    mpc_dual_kernel<<<(b->n_inst + 3) / 4, 64, 0, st>>>(b->d_inst, b->n_inst, b->d_par, z_init, b->d_u,
-                                                          (float)(1.0 / b->rho));
+    launch_dual(b, z_init, b->d_u, st);
     ADMM_HIP(hipGetLastError());
     uinit = b->d_u;
   }

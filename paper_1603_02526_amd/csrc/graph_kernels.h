@@ -28,6 +28,7 @@ constexpr int PR = PB * PB / NT;     // pair rows per thread
 constexpr int MAXN = 16;             // lindyn state dim limit (general path)
 constexpr int MAXM = 8;              // lindyn input dim limit (general path)
 constexpr int LANE_MAX = 4;          // z-lists up to this length: one lane
+constexpr int VEC_DMAX = 1 << 16;    // vector variables up to this length: one offset (vec_factor)
 constexpr int ZB_MIN = 128;          // z-lists longer than this: one workgroup
 
 enum BucketMode : int32_t {
@@ -56,15 +57,32 @@ struct BucketDesc {
   int32_t E, NB;        // pair layout: entities, column blocks
   int32_t rb;           // pair layout: entities per row block (16, 32 or 64)
   int32_t sparse;       // pair layout: state of unmoved pairs kept implicit (FP32, alpha = 1)
-  int64_t flag0;        // pair layout: first flag word of this bucket (per tile NT words)
-  int32_t ent_aff;      // pair layout: entity e's z offsets are ent_base + 3e (centre), + 2 (radius)
+  union {
+    int64_t flag0;      // pair layout: first flag word of this bucket (per tile NT words)
+    int64_t vec_off;    // vector variables (vd): index-buffer offset of the factors' offsets
+  };
+  union {
+    int32_t ent_aff;    // pair layout: entity e's z offsets are ent_base + 3e (centre), + 2 (radius)
+    int32_t pconst;     // separable: every slot has the first slot's parameters
+  };
   int32_t ent_base;
   int32_t ub;           // hinge/margin: the b edge is one variable for every factor
                         // of the bucket, which takes one partial sum per workgroup
   int32_t tri;          // pair layout: 64-row tiles in row-major order of the whole
                         // upper triangle (J >= I), so (I, J) follows from the tile index
-  int32_t fl;           // shared-variable hinge: lanes per row of factors (FL)
-  int32_t zaff;         // shared-variable hinge: z offset of edge k is zaff + k (-1: a list)
+  // Margin, equality and separable factors on whole vector variables of one
+  // dimension vd >= 2 (0: the tables): component c's z offset is that of
+  // component 0 plus c, its destination plus c vs, so that one z offset and
+  // one destination per factor edge (margin: its tables' first rows, else at
+  // vec_off: the edges' z offsets, then their destinations) stand for vd.
+  union {
+    int32_t fl;         // shared-variable hinge: lanes per row of factors (FL)
+    int32_t vd;
+  };
+  union {
+    int32_t zaff;       // shared-variable hinge: z offset of edge k is zaff + k (-1: a list)
+    int32_t vs;
+  };
   int64_t m_off, x_off;  // element offsets of the state regions in the pool
   int64_t twb_off;      // three-weight variant: first byte of this bucket's active flags
   int64_t dst_off;      // index-buffer offset of the contribution destinations
@@ -110,7 +128,8 @@ struct ZArgs {
   const T* deg_w;
   int64_t n_w;
   int32_t nb_w;
-  const int32_t* var_l;   // lists of at most LANE_MAX: one lane each, stride LANE_MAX
+  const int32_t* var_l;   // lists of at most LANE_MAX: one lane each, contribution j of list k at j n_l + k
+                          // (resident driver: LANE_MAX k + j, read together from LDS)
   const T* deg_l;         // 0: no edge, z keeps its value
   int64_t n_l;
   int64_t w_stride, w_base, l_base;  // padded list layout (pool positions)
@@ -995,9 +1014,18 @@ __device__ __forceinline__ void xpass_pair_sparse(const XArgs<float>& a, const B
 // onto y(w.x + b) + xi >= 1 with the slack xi as slot d+1, no upper bound
 // (C = +inf) and rho/(|x|^2+2) as the last parameter.
 // ---------------------------------------------------------------------------
-template <typename T, bool A1, int MODE, int DM>
+template <typename T>
+__device__ __forceinline__ T (&hinge_wsum())[NT / 64] {
+  __shared__ T sm[NT / 64];
+  return sm;
+}
+
+// VEC: margin on vector variables (b.vd), one z offset and one destination.
+// Of its own, as a test of b.vd at every offset kept the loads of the other
+// form from being issued together (2000 factors of 100: 68 us, 92 with it).
+template <typename T, bool A1, int MODE, int DM, bool VEC>
 __device__ __forceinline__ void xpass_hinge(const XArgs<T>& a, const BucketDesc& b, int blk) {
-  __shared__ T wsum[NT / 64];
+  T (&wsum)[NT / 64] = hinge_wsum<T>();
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int d = b.d;
   const int64_t f = (int64_t)blk * NT + t;
@@ -1008,13 +1036,14 @@ __device__ __forceinline__ void xpass_hinge(const XArgs<T>& a, const BucketDesc&
   const T* P = a.par + b.par_off;
   T* M = a.pool + b.m_off;
   T* X = a.pool + b.x_off;
+  const int z0 = VEC ? zo[ff] : 0, d0 = VEC ? a.idx[b.dst_off + ff] : 0;
   T nv[DM], uv[DM], ya[DM];
   T dot = T(0);
   T rmax = T(0);
 #pragma unroll
   for (int k = 0; k < DM; ++k) {
     if (k < d) {
-      const T zk = a.z[zo[k * nfp + ff]];
+      const T zk = a.z[VEC ? z0 + k : zo[k * nfp + ff]];
       const T mk = M[k * nfp + ff];
       T xo = T(0);
       if constexpr (!A1 || MODE == PM_RESID) xo = X[k * nfp + ff];
@@ -1031,7 +1060,7 @@ __device__ __forceinline__ void xpass_hinge(const XArgs<T>& a, const BucketDesc&
   const T mb = M[d * nfp + ff];
   T xob = T(0);
   if constexpr (!A1 || MODE == PM_RESID) xob = X[d * nfp + ff];
-  const bool margin = b.kind == KD_MARGIN;
+  const bool margin = VEC || b.kind == KD_MARGIN;
   T zs = T(0), ms = T(0), xos = T(0);
   if (margin) {
     zs = a.z[zo[(d + 1) * nfp + ff]];
@@ -1077,7 +1106,7 @@ __device__ __forceinline__ void xpass_hinge(const XArgs<T>& a, const BucketDesc&
         if (valid) {
           M[k * nfp + ff] = mk;
           if constexpr (!A1 || MODE == PM_SAVE) X[k * nfp + ff] = xk;
-          a.pool[a.idx[b.dst_off + k * nfp + ff]] = mk;
+          a.pool[VEC ? d0 + k * b.vs : a.idx[b.dst_off + k * nfp + ff]] = mk;
         }
       }
     }
@@ -1230,10 +1259,10 @@ __device__ __forceinline__ void xpass_hinge_tile(const XArgs<T>& a, const Bucket
 // over the components forms the dot product s = y(n_w.a + n_b) (+ n_xi);
 // once tau is known a second sweep reads each component's m, z and y a
 // again and writes its outputs, in the same order as xpass_hinge.
-template <typename T, bool A1, int MODE>
+template <typename T, bool A1, int MODE, bool VEC>
 __device__ __forceinline__ void xpass_hinge_wide(const XArgs<T>& a, const BucketDesc& b,
                                                  int blk) {
-  __shared__ T wsw[NT / 64];
+  T (&wsw)[NT / 64] = hinge_wsum<T>();
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int d = b.d;
   const int64_t f = (int64_t)blk * NT + t;
@@ -1245,9 +1274,10 @@ __device__ __forceinline__ void xpass_hinge_wide(const XArgs<T>& a, const Bucket
   T* M = a.pool + b.m_off;
   T* X = a.pool + b.x_off;
   const T alpha = (T)b.alpha;
+  const int z0 = VEC ? zo[ff] : 0, d0 = VEC ? a.idx[b.dst_off + ff] : 0;
   T dot = T(0), rmax = T(0);
   for (int k = 0; k < d; ++k) {
-    const T zk = a.z[zo[k * nfp + ff]];
+    const T zk = a.z[VEC ? z0 + k : zo[k * nfp + ff]];
     const T mk = M[k * nfp + ff];
     T xo = T(0);
     if constexpr (!A1 || MODE == PM_RESID) xo = X[k * nfp + ff];
@@ -1263,7 +1293,7 @@ __device__ __forceinline__ void xpass_hinge_wide(const XArgs<T>& a, const Bucket
   const T mb = M[d * nfp + ff];
   T xob = T(0);
   if constexpr (!A1 || MODE == PM_RESID) xob = X[d * nfp + ff];
-  const bool margin = b.kind == KD_MARGIN;
+  const bool margin = VEC || b.kind == KD_MARGIN;
   T zs = T(0), ms = T(0), xos = T(0);
   if (margin) {
     zs = a.z[zo[(d + 1) * nfp + ff]];
@@ -1302,7 +1332,7 @@ __device__ __forceinline__ void xpass_hinge_wide(const XArgs<T>& a, const Bucket
       }
     }
     for (int k = 0; k < d; ++k) {
-      const T zk = a.z[zo[k * nfp + ff]];
+      const T zk = a.z[VEC ? z0 + k : zo[k * nfp + ff]];
       const T mk = M[k * nfp + ff];
       T xo = T(0);
       if constexpr (!A1) xo = X[k * nfp + ff];
@@ -1313,7 +1343,7 @@ __device__ __forceinline__ void xpass_hinge_wide(const XArgs<T>& a, const Bucket
       if (valid) {
         M[k * nfp + ff] = mn;
         if constexpr (!A1 || MODE == PM_SAVE) X[k * nfp + ff] = xk;
-        a.pool[a.idx[b.dst_off + k * nfp + ff]] = mn;
+        a.pool[VEC ? d0 + k * b.vs : a.idx[b.dst_off + k * nfp + ff]] = mn;
       }
     }
     if (shared_b) {
@@ -1330,6 +1360,20 @@ __device__ __forceinline__ void xpass_hinge_wide(const XArgs<T>& a, const Bucket
   }
 }
 
+// Factor and component c of this thread's slot when every factor has vd of
+// them: the block's first slot is divided once for all threads; the thread's
+// distance from that factor, under vd + NT, is small enough (vd <= VEC_DMAX)
+// for a float quotient whose error, (vd + NT) / vd 2^-22, stays below the
+// half slot, 1 / (2 vd), that it is moved off the integers by.
+__device__ __forceinline__ int64_t vec_factor(int blk, int vd, int& c) {
+  const unsigned first = (unsigned)blk * NT;
+  const unsigned f0 = first / (unsigned)vd;
+  const int r = (int)(first - f0 * (unsigned)vd) + (int)threadIdx.x;
+  const int q = (int)(((float)r + 0.5f) * (1.f / (float)vd));
+  c = r - q * vd;
+  return (int64_t)f0 + q;
+}
+
 // ---------------------------------------------------------------------------
 // Separable operators, one thread per scalar slot.  Params [2][nfp]:
 //   RADIUS  x = max(0, p0 n), p0 = rho/(rho - gamma)
@@ -1337,17 +1381,28 @@ __device__ __forceinline__ void xpass_hinge_wide(const XArgs<T>& a, const Bucket
 //   L2      x = p0 n,         p0 = rho/(rho + lambda)
 //   BOX     x = min(p1, max(p0, n)), (p0, p1) = (lo, hi)
 //   MINERR  x = max(0, n - p0),  p0 = lambda/rho  (App. C, minimal error)
+// VL: buckets may have the vector layout and constant parameters (pconst).
 // ---------------------------------------------------------------------------
-template <typename T, bool A1, int MODE>
+template <typename T, bool A1, int MODE, bool VL>
 __device__ __forceinline__ void xpass_slot(const XArgs<T>& a, const BucketDesc& b, int blk) {
   const int64_t s = (int64_t)blk * NT + threadIdx.x;
   T rmax = T(0);
   if (s < b.n) {
-    const int32_t* zi = a.idx + b.idx_off;
     const T* P = a.par + b.par_off;
     T* M = a.pool + b.m_off;
     T* X = a.pool + b.x_off;
-    const T zv = a.z[zi[s]];
+    int zi, ds = 0;
+    if (VL && b.vd) {
+      int c;
+      const int64_t f = vec_factor(blk, b.vd, c);
+      const int2 e = ((const int2*)(a.idx + b.vec_off))[f];
+      zi = e.x + c;
+      ds = e.y + c * b.vs;
+    } else {
+      zi = a.idx[b.idx_off + s];
+      if constexpr (MODE != PM_RESID) ds = a.idx[b.dst_off + s];
+    }
+    const T zv = a.z[zi];
     if constexpr (MODE == PM_RESID) {
       rmax = tabs(X[s] - zv);
     } else {
@@ -1355,10 +1410,11 @@ __device__ __forceinline__ void xpass_slot(const XArgs<T>& a, const BucketDesc& 
       if constexpr (!A1) xo = X[s];
       T u, n;
       state_un<T, A1>(M[s], xo, zv, (T)b.alpha, u, n);
-      const T p0 = P[s];
+      const int64_t sp = VL && b.pconst ? 0 : s;
+      const T p0 = P[sp];
       T x;
       if (b.kind == KD_BOX) {
-        x = tmin(P[b.nfp + s], tmax(p0, n));
+        x = tmin(P[b.nfp + sp], tmax(p0, n));
       } else if (b.kind == KD_RADIUS) {
         x = tmax(T(0), p0 * n);
       } else if (b.kind == KD_MINERR) {
@@ -1368,7 +1424,7 @@ __device__ __forceinline__ void xpass_slot(const XArgs<T>& a, const BucketDesc& 
       }
       M[s] = x + u;
       if constexpr (!A1 || MODE == PM_SAVE) X[s] = x;
-      a.pool[a.idx[b.dst_off + s]] = x + u;
+      a.pool[ds] = x + u;
     }
   }
   if constexpr (MODE == PM_RESID) block_max_store(rmax, a.blockmax);
@@ -1503,7 +1559,7 @@ __device__ __forceinline__ void geom_tw(const XArgs<T>& a, const BucketDesc& b, 
 // Non-overlap and wall factors on arbitrary variables, and equality
 // factors split into scalar component pairs (App. C: with equal weights
 // both copies take the mean of the pair).
-template <typename T, bool A1, int MODE, bool TW = false>
+template <typename T, bool A1, int MODE, bool TW, bool VL>
 __device__ __forceinline__ void xpass_geom(const XArgs<T>& a, const BucketDesc& b, int blk) {
   const int64_t f = (int64_t)blk * NT + threadIdx.x;
   T rmax = T(0);
@@ -1516,7 +1572,31 @@ __device__ __forceinline__ void xpass_geom(const XArgs<T>& a, const BucketDesc& 
       geom_tw<T, MODE, 3>(a, b, f, dims, 2, rmax);
     }
   } else if (f < b.n) {
-    if (b.kind == KD_EQUAL) {
+    if (VL && b.kind == KD_EQUAL && b.vd) {
+      int c;
+      const int4 e = ((const int4*)(a.idx + b.vec_off))[vec_factor(blk, b.vd, c)];
+      const int64_t nfp = b.nfp;
+      T* M = a.pool + b.m_off;
+      T* X = a.pool + b.x_off;
+      const T z0 = a.z[e.x + c], z1 = a.z[e.y + c];
+      if constexpr (MODE == PM_RESID) {
+        rmax = tmax(tabs(X[f] - z0), tabs(X[nfp + f] - z1));
+      } else {
+        T u0, u1, v0, v1;
+        state_un<T, A1>(M[f], A1 ? T(0) : X[f], z0, (T)b.alpha, u0, v0);
+        state_un<T, A1>(M[nfp + f], A1 ? T(0) : X[nfp + f], z1, (T)b.alpha, u1, v1);
+        const T mean = (v0 + v1) * T(0.5);
+        const T m0 = mean + u0, m1 = mean + u1;
+        M[f] = m0;
+        M[nfp + f] = m1;
+        if constexpr (!A1 || MODE == PM_SAVE) {
+          X[f] = mean;
+          X[nfp + f] = mean;
+        }
+        a.pool[e.z + c * b.vs] = m0;
+        a.pool[e.w + c * b.vs] = m1;
+      }
+    } else if (b.kind == KD_EQUAL) {
       const int dims[4] = {1, 1, 0, 0};
       T u[2], v[2];
       gen_gather<T, A1, MODE, 2>(a, b, f, dims, 2, u, v, rmax);
@@ -1667,6 +1747,7 @@ enum Features : int {
   FT_TWA = 64,     // three-weight variant (packing graphs: pair tiles, constraints, slots)
   FT_W64 = 128,    // general hinge and margin with 32 < d <= 64
   FT_LINDYN = 256, // linear-dynamics projections
+  FT_LDS = 512,    // resident driver: tables in LDS, no vector layout
 };
 constexpr int FS_PAIR = FT_PAIR | FT_GEN;
 constexpr int FS_PAIRSP = FT_PAIRSP | FT_GEN;
@@ -1700,7 +1781,7 @@ struct BTab {
 // buckets, b is the bucket that holds it.
 template <typename T, bool A1, int MODE, int FS>
 __device__ __forceinline__ void xpass_block(XArgs<T> a, int blk, const BucketDesc& b) {
-  constexpr bool TW = (FS & FT_TWA) != 0;
+  constexpr bool TW = (FS & FT_TWA) != 0, VL = !(FS & FT_LDS);
   a.blockmax += blk;
   const int local = blk - b.blk0;
   if ((FS & (FT_PAIR | FT_PAIRSP)) && b.mode == BM_PAIR) {
@@ -1738,15 +1819,18 @@ __device__ __forceinline__ void xpass_block(XArgs<T> a, int blk, const BucketDes
     else if (b.fl == 32) xpass_hinge_tile<T, A1, MODE, 32>(a, b, local);
     else xpass_hinge_tile<T, A1, MODE, 64>(a, b, local);
   } else if ((FS & FT_GEN) && b.mode == BM_GEN_SLOT) {
-    xpass_slot<T, A1, MODE>(a, b, local);
+    xpass_slot<T, A1, MODE, VL>(a, b, local);
   } else if ((FS & FT_GEN) && (b.kind == KD_NONOVERLAP || b.kind == KD_WALL || b.kind == KD_EQUAL)) {
-    xpass_geom<T, A1, MODE, TW>(a, b, local);
+    xpass_geom<T, A1, MODE, TW, VL>(a, b, local);
   } else if ((FS & FT_XWIDE) && (b.kind == KD_HINGE || b.kind == KD_MARGIN) && b.dmax == 0) {
-    xpass_hinge_wide<T, A1, MODE>(a, b, local);
+    if (VL && b.vd) xpass_hinge_wide<T, A1, MODE, true>(a, b, local);
+    else xpass_hinge_wide<T, A1, MODE, false>(a, b, local);
   } else if ((FS & FT_W64) && (b.kind == KD_HINGE || b.kind == KD_MARGIN) && b.dmax == 64) {
-    xpass_hinge<T, A1, MODE, 64>(a, b, local);
+    if (VL && b.vd) xpass_hinge<T, A1, MODE, 64, true>(a, b, local);
+    else xpass_hinge<T, A1, MODE, 64, false>(a, b, local);
   } else if ((FS & FT_WIDE) && (b.kind == KD_HINGE || b.kind == KD_MARGIN)) {
-    xpass_hinge<T, A1, MODE, 32>(a, b, local);
+    if (VL && b.vd) xpass_hinge<T, A1, MODE, 32, true>(a, b, local);
+    else xpass_hinge<T, A1, MODE, 32, false>(a, b, local);
   } else if (FS & FT_LINDYN) {
     xpass_lindyn<T, A1, MODE>(a, b, local);
   }
@@ -1922,12 +2006,12 @@ __device__ __forceinline__ void zpass_block_tw(ZArgs<T> a, int blk) {
   } else {
     const int64_t k = (int64_t)(blk - a.n_b - a.nb_w) * NT + threadIdx.x;
     if (k < a.n_l) {
-      const int64_t o = a.l_base + k * LANE_MAX;
+      const int64_t o = a.l_base + k;
       T num = a.pool[o], den = a.wc[o];
 #pragma unroll
       for (int j = 1; j < LANE_MAX; ++j) {
-        num += a.pool[o + j];
-        den += a.wc[o + j];
+        num += a.pool[o + j * a.n_l];
+        den += a.wc[o + j * a.n_l];
       }
       finish(a.var_l[k], num, den);
     }
@@ -1935,7 +2019,7 @@ __device__ __forceinline__ void zpass_block_tw(ZArgs<T> a, int blk) {
   if (a.check) block_max_store(dmax, a.blockmax + blk);
 }
 
-template <typename T>
+template <typename T, bool LDS>
 __device__ __forceinline__ void zpass_block(ZArgs<T> a, int blk) {
   if (a.wc) {
     zpass_block_tw(a, blk);
@@ -2018,17 +2102,17 @@ __device__ __forceinline__ void zpass_block(ZArgs<T> a, int blk) {
     if (k < a.n_l) {
       const int zi = a.var_l[k];
       const T d = a.deg_l[k];
-      const int64_t o = a.l_base + k * LANE_MAX;
+      const int64_t o = a.l_base + (LDS ? k * LANE_MAX : k), step = LDS ? 1 : a.n_l;
       const T* p = a.pool + o;
       T s;
       if (a.wz) {
         s = a.wz[o] * p[0];
 #pragma unroll
-        for (int j = 1; j < LANE_MAX; ++j) s += a.wz[o + j] * p[j];
+        for (int j = 1; j < LANE_MAX; ++j) s += a.wz[o + j * step] * p[j * step];
       } else {
         s = p[0];
 #pragma unroll
-        for (int j = 1; j < LANE_MAX; ++j) s += p[j];
+        for (int j = 1; j < LANE_MAX; ++j) s += p[j * step];
       }
       T zn;
       if (d > T(0))
@@ -2044,7 +2128,7 @@ __device__ __forceinline__ void zpass_block(ZArgs<T> a, int blk) {
 
 template <typename T>
 __global__ __launch_bounds__(NT) void zpass_kernel(ZArgs<T> a) {
-  zpass_block<T>(a, blockIdx.x);
+  zpass_block<T, false>(a, blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -2057,7 +2141,7 @@ __global__ __launch_bounds__(NT) void zpass_kernel(ZArgs<T> a) {
 // The bucket table is staged in LDS too.  Pair tiles are not used here.
 // ---------------------------------------------------------------------------
 constexpr int RES_MAX_REG = 16;
-constexpr int FS_RES = FT_UHINGE | FT_GEN | FT_WIDE | FT_XWIDE | FT_W64 | FT_LINDYN;
+constexpr int FS_RES = FT_UHINGE | FT_GEN | FT_WIDE | FT_XWIDE | FT_W64 | FT_LINDYN | FT_LDS;
 
 struct ResRegion {
   const void* src;  // global source
@@ -2140,7 +2224,7 @@ __global__ __launch_bounds__(NT) void resident_kernel(XArgs<T> xa, ZArgs<T> za, 
     za.zout = (T*)(lds_img + zoff[zc ^ 1]);
     za.check = last ? 1 : 0;
     for (int b = 0; b < r.zblocks; ++b) {
-      zpass_block<T>(za, b);
+      zpass_block<T, true>(za, b);
       __syncthreads();
     }
     zc ^= 1;
@@ -2160,7 +2244,7 @@ __global__ __launch_bounds__(NT) void resident_kernel(XArgs<T> xa, ZArgs<T> za, 
 // blocks and the same arithmetic as resident_kernel.  What bounds it: the
 // dependent LDS reads of a pass (index, z, m) and its barrier.  10 disks (3
 // and 2 blocks): a solve of 100 iterations with its transfers 216 us against 534.
-constexpr int FS_TEAM = FT_GEN;
+constexpr int FS_TEAM = FT_GEN | FT_LDS;
 
 template <typename T, bool A1>
 __global__ __launch_bounds__(NT * TEAMS) void resident_team_kernel(XArgs<T> xa, ZArgs<T> za,
@@ -2190,7 +2274,7 @@ __global__ __launch_bounds__(NT * TEAMS) void resident_team_kernel(XArgs<T> xa, 
     // the residual maximum of a checked block holds one barrier: every team
     // meets it as often
     for (int b = 0; b < r.zblocks; b += TEAMS) {
-      if (b + team < r.zblocks) zpass_block<T>(za, b + team);
+      if (b + team < r.zblocks) zpass_block<T, true>(za, b + team);
       else if (last) __syncthreads();
       if (last) __syncthreads();
     }

@@ -42,7 +42,7 @@ struct Plan {
   int64_t algo_elems = 0, layout_idx_bytes = 0, layout_elems = 0;
   int64_t n_pair_tiles = 0;
   int64_t n_flags = 0;          // sparse pair-state flag words (NT per tile)
-  bool no_tiles = false;        // input: build no dense pair tiles
+  bool no_tiles = false;        // input: for the resident driver (no dense pair tiles, no vector layout)
   bool resident = false;        // output of finalize: resident driver chosen
 };
 

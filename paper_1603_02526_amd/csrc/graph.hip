@@ -245,9 +245,10 @@ bool detect_complete_pairs(const admm_graph& g, const Group& gr, std::vector<int
   return true;
 }
 
-// Hinge and margin factors take up to NT - 1 weight components; factors
-// without a shared variable list keep one register per component up to 64
-// (dmax 32 or 64) and make two sweeps over memory above that (dmax 0).
+// Hinge and margin factors take up to NT - 1 weight components; in the
+// resident driver, factors without a shared variable list keep one register
+// per component up to 64 (dmax 32 or 64) and make two sweeps over LDS above
+// that (dmax 0).
 constexpr int HINGE_DMAX = NT - 1;
 int hinge_dmax(int d) { return d <= 32 ? 32 : d <= 64 ? 64 : 0; }
 
@@ -271,6 +272,16 @@ int hinge_lanes(int64_t n, int d, int v, bool resident) {
   } else if (n * (d + 1) >= MIN_SLOTS) {
     while (fl > 8 && (n + fl * v - 1) / (fl * v) < MIN_BLOCKS) fl /= 2;
   }
+  return fl;
+}
+
+// Factors per workgroup of the general hinge and margin (xpass_hinge_split):
+// the most that keep a thread to eight components and give every CU a
+// workgroup.
+int split_lanes(int64_t n, int d) {
+  constexpr int64_t MIN_BLOCKS = 256;
+  int fl = 64;
+  while (fl > 8 && ((d + NT / fl - 1) / (NT / fl) > 8 || (n + fl - 1) / fl < MIN_BLOCKS)) fl /= 2;
   return fl;
 }
 
@@ -592,10 +603,11 @@ admm_status build_plan(admm_graph& g, Plan& P, bool no_tiles) {
       P.layout_idx_bytes += 2 * np * 4;
     } else if (gr.kind == KD_MARGIN) {
       // ---------------- margin: the general hinge path with a slack slot ----------------
-      b.mode = BM_GEN_FACTOR;
+      const int d = g.dim[gr.vids[0]];
+      b.mode = P.no_tiles ? BM_GEN_FACTOR : BM_HINGE_SPLIT;
+      if (!P.no_tiles) b.hl = split_lanes(gr.n, d);
       b.n = gr.n;
       b.nfp = round_up(gr.n, 64);
-      const int d = g.dim[gr.vids[0]];
       b.d = d;
       if (d > HINGE_DMAX)
         return admmi::set_err(ADMM_E_UNSUPPORTED, "MARGIN with d > %d is not supported", HINGE_DMAX);
@@ -623,7 +635,8 @@ admm_status build_plan(admm_graph& g, Plan& P, bool no_tiles) {
       // one bias for every factor (the usual graph): one partial per workgroup
       b.ub = 1;
       for (int64_t f = 1; f < gr.n && b.ub; ++f) b.ub = zof(f, 1) == zof(0, 1);
-      const int64_t tiles = (gr.n + NT - 1) / NT;
+      const int64_t fb = P.no_tiles ? NT : b.hl;   // factors per workgroup
+      const int64_t tiles = (gr.n + fb - 1) / fb;
       for (int64_t f = 0; f < gr.n; ++f)
         for (int s = 0; s < d + 2; ++s) {
           const int64_t zi = P.idx[i0 + s * b.nfp + f];
@@ -703,6 +716,10 @@ admm_status build_plan(admm_graph& g, Plan& P, bool no_tiles) {
         if (b.d > HINGE_DMAX)
           return admmi::set_err(ADMM_E_UNSUPPORTED, "HINGE with d > %d is not supported", HINGE_DMAX);
         b.dmax = hinge_dmax(b.d);
+        if (!P.no_tiles) {
+          b.mode = BM_HINGE_SPLIT;
+          b.hl = split_lanes(gr.n, b.d);
+        }
       }
       if (gr.kind == KD_LINDYN || gr.kind == KD_LINDYN0) {
         b.nn = nn;
@@ -805,7 +822,8 @@ admm_status build_plan(admm_graph& g, Plan& P, bool no_tiles) {
         }
       }
       b.blk0 = (int32_t)blocks;
-      blocks += (gr.n + NT - 1) / NT;
+      const int64_t fb = b.mode == BM_HINGE_SPLIT ? b.hl : NT;   // factors per workgroup
+      blocks += (gr.n + fb - 1) / fb;
       b.blk1 = (int32_t)blocks;
       P.algo_elems += 2 * (int64_t)gr.n * b.nslot;
       P.layout_idx_bytes += (int64_t)gr.n * gr.arity * 4;

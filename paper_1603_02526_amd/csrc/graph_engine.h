@@ -187,12 +187,10 @@ struct Engine : EngineBase {
       for (const BucketDesc& b : P.bt) {
         if (b.mode == BM_PAIR) need |= b.sparse ? FT_PAIRSP : FT_PAIR;
         else if (b.mode == BM_UNIF_HINGE) need |= FT_UHINGE;
-        else if ((b.kind == KD_HINGE || b.kind == KD_MARGIN) && b.dmax == 0) need |= FT_XWIDE;
-        else if ((b.kind == KD_HINGE || b.kind == KD_MARGIN) && b.dmax == 64) need |= FT_W64;
+        else if (b.mode == BM_HINGE_SPLIT) need |= FT_WIDE;
         else if (b.mode == BM_GEN_SLOT || b.kind == KD_NONOVERLAP || b.kind == KD_WALL ||
                  b.kind == KD_EQUAL)
           need |= FT_GEN;
-        else if (b.kind == KD_HINGE || b.kind == KD_MARGIN) need |= FT_WIDE;
         else need |= FT_LINDYN;
       }
       if (twa) need |= FT_TWA;
@@ -202,9 +200,7 @@ struct Engine : EngineBase {
            : ((need & ~FS_HINGE) == 0)  ? FS_HINGE
            : ((need & ~FS_WIDE) == 0)   ? FS_WIDE
            : ((need & ~FS_DYN) == 0)    ? FS_DYN
-           : ((need & ~FS_XW) == 0)     ? FS_XW
-           : ((need & ~FS_ALL) == 0)    ? FS_ALL
-                                        : FS_ALLX;
+                                        : FS_ALL;
     }
     n_b = (int64_t)P.var_b.size();
     w_stride = P.w_stride;
@@ -364,9 +360,7 @@ struct Engine : EngineBase {
     else if (fs == FS_HINGE) launch_x_fs<A1, FS_HINGE>(mode, st, e0, e1);
     else if (fs == FS_WIDE) launch_x_fs<A1, FS_WIDE>(mode, st, e0, e1);
     else if (fs == FS_DYN) launch_x_fs<A1, FS_DYN>(mode, st, e0, e1);
-    else if (fs == FS_XW) launch_x_fs<A1, FS_XW>(mode, st, e0, e1);
     else if (fs == FS_ALL) launch_x_fs<A1, FS_ALL>(mode, st, e0, e1);
-    else if (fs == FS_ALLX) launch_x_fs<A1, FS_ALLX>(mode, st, e0, e1);
     else if constexpr (A1) {
       // the three-weight variant runs with alpha = 1 only
       if (fs == FS_PAIRSP_TW) launch_x_fs<A1, FS_PAIRSP_TW>(mode, st, e0, e1);

@@ -36,6 +36,7 @@ enum BucketMode : int32_t {
   BM_UNIF_HINGE = 2,  // hinge factors that all share one variable list
   BM_GEN_FACTOR = 3,  // one thread per factor, per-edge z offsets
   BM_GEN_SLOT = 4,    // separable prox: one thread per scalar slot
+  BM_HINGE_SPLIT = 5, // general hinge and margin: lanes split a factor's components
 };
 
 enum PassMode : int { PM_NORMAL = 0, PM_SAVE = 1, PM_RESID = 2 };
@@ -53,7 +54,12 @@ struct BucketDesc {
   int64_t n;            // factors (factor modes), slots (GEN_SLOT), tiles (PAIR)
   int64_t nfp;          // SoA row stride
   int32_t arity, nslot; // edges / scalar slots per factor
-  int32_t d, nn, mm, dmax;  // hinge d (and its register bound); lindyn n, m
+  int32_t d;            // hinge and margin: components
+  union {
+    int32_t nn;         // lindyn n
+    int32_t hl;         // split hinge and margin: factors per row of lanes
+  };
+  int32_t mm, dmax;     // lindyn m; hinge, one thread per factor: register bound on d
   int32_t E, NB;        // pair layout: entities, column blocks
   int32_t rb;           // pair layout: entities per row block (16, 32 or 64)
   int32_t sparse;       // pair layout: state of unmoved pairs kept implicit (FP32, alpha = 1)
@@ -1020,10 +1026,7 @@ __device__ __forceinline__ T (&hinge_wsum())[NT / 64] {
   return sm;
 }
 
-// VEC: margin on vector variables (b.vd), one z offset and one destination.
-// Of its own, as a test of b.vd at every offset kept the loads of the other
-// form from being issued together (2000 factors of 100: 68 us, 92 with it).
-template <typename T, bool A1, int MODE, int DM, bool VEC>
+template <typename T, bool A1, int MODE, int DM>
 __device__ __forceinline__ void xpass_hinge(const XArgs<T>& a, const BucketDesc& b, int blk) {
   T (&wsum)[NT / 64] = hinge_wsum<T>();
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
@@ -1036,14 +1039,13 @@ __device__ __forceinline__ void xpass_hinge(const XArgs<T>& a, const BucketDesc&
   const T* P = a.par + b.par_off;
   T* M = a.pool + b.m_off;
   T* X = a.pool + b.x_off;
-  const int z0 = VEC ? zo[ff] : 0, d0 = VEC ? a.idx[b.dst_off + ff] : 0;
   T nv[DM], uv[DM], ya[DM];
   T dot = T(0);
   T rmax = T(0);
 #pragma unroll
   for (int k = 0; k < DM; ++k) {
     if (k < d) {
-      const T zk = a.z[VEC ? z0 + k : zo[k * nfp + ff]];
+      const T zk = a.z[zo[k * nfp + ff]];
       const T mk = M[k * nfp + ff];
       T xo = T(0);
       if constexpr (!A1 || MODE == PM_RESID) xo = X[k * nfp + ff];
@@ -1060,7 +1062,7 @@ __device__ __forceinline__ void xpass_hinge(const XArgs<T>& a, const BucketDesc&
   const T mb = M[d * nfp + ff];
   T xob = T(0);
   if constexpr (!A1 || MODE == PM_RESID) xob = X[d * nfp + ff];
-  const bool margin = VEC || b.kind == KD_MARGIN;
+  const bool margin = b.kind == KD_MARGIN;
   T zs = T(0), ms = T(0), xos = T(0);
   if (margin) {
     zs = a.z[zo[(d + 1) * nfp + ff]];
@@ -1106,7 +1108,7 @@ __device__ __forceinline__ void xpass_hinge(const XArgs<T>& a, const BucketDesc&
         if (valid) {
           M[k * nfp + ff] = mk;
           if constexpr (!A1 || MODE == PM_SAVE) X[k * nfp + ff] = xk;
-          a.pool[VEC ? d0 + k * b.vs : a.idx[b.dst_off + k * nfp + ff]] = mk;
+          a.pool[a.idx[b.dst_off + k * nfp + ff]] = mk;
         }
       }
     }
@@ -1259,7 +1261,7 @@ __device__ __forceinline__ void xpass_hinge_tile(const XArgs<T>& a, const Bucket
 // over the components forms the dot product s = y(n_w.a + n_b) (+ n_xi);
 // once tau is known a second sweep reads each component's m, z and y a
 // again and writes its outputs, in the same order as xpass_hinge.
-template <typename T, bool A1, int MODE, bool VEC>
+template <typename T, bool A1, int MODE>
 __device__ __forceinline__ void xpass_hinge_wide(const XArgs<T>& a, const BucketDesc& b,
                                                  int blk) {
   T (&wsw)[NT / 64] = hinge_wsum<T>();
@@ -1274,10 +1276,9 @@ __device__ __forceinline__ void xpass_hinge_wide(const XArgs<T>& a, const Bucket
   T* M = a.pool + b.m_off;
   T* X = a.pool + b.x_off;
   const T alpha = (T)b.alpha;
-  const int z0 = VEC ? zo[ff] : 0, d0 = VEC ? a.idx[b.dst_off + ff] : 0;
   T dot = T(0), rmax = T(0);
   for (int k = 0; k < d; ++k) {
-    const T zk = a.z[VEC ? z0 + k : zo[k * nfp + ff]];
+    const T zk = a.z[zo[k * nfp + ff]];
     const T mk = M[k * nfp + ff];
     T xo = T(0);
     if constexpr (!A1 || MODE == PM_RESID) xo = X[k * nfp + ff];
@@ -1293,7 +1294,7 @@ __device__ __forceinline__ void xpass_hinge_wide(const XArgs<T>& a, const Bucket
   const T mb = M[d * nfp + ff];
   T xob = T(0);
   if constexpr (!A1 || MODE == PM_RESID) xob = X[d * nfp + ff];
-  const bool margin = VEC || b.kind == KD_MARGIN;
+  const bool margin = b.kind == KD_MARGIN;
   T zs = T(0), ms = T(0), xos = T(0);
   if (margin) {
     zs = a.z[zo[(d + 1) * nfp + ff]];
@@ -1332,7 +1333,7 @@ __device__ __forceinline__ void xpass_hinge_wide(const XArgs<T>& a, const Bucket
       }
     }
     for (int k = 0; k < d; ++k) {
-      const T zk = a.z[VEC ? z0 + k : zo[k * nfp + ff]];
+      const T zk = a.z[zo[k * nfp + ff]];
       const T mk = M[k * nfp + ff];
       T xo = T(0);
       if constexpr (!A1) xo = X[k * nfp + ff];
@@ -1343,7 +1344,7 @@ __device__ __forceinline__ void xpass_hinge_wide(const XArgs<T>& a, const Bucket
       if (valid) {
         M[k * nfp + ff] = mn;
         if constexpr (!A1 || MODE == PM_SAVE) X[k * nfp + ff] = xk;
-        a.pool[VEC ? d0 + k * b.vs : a.idx[b.dst_off + k * nfp + ff]] = mn;
+        a.pool[a.idx[b.dst_off + k * nfp + ff]] = mn;
       }
     }
     if (shared_b) {
@@ -1356,6 +1357,142 @@ __device__ __forceinline__ void xpass_hinge_wide(const XArgs<T>& a, const Bucket
         for (int q = 1; q < NT / 64; ++q) acc += wsw[q];
         a.pool[a.idx[b.dst_off + d * nfp + blk]] = acc;
       }
+    }
+  }
+}
+
+// The same operators outside the resident driver: a workgroup takes FL = b.hl
+// consecutive factors, thread (r, fl) = (t / FL, t % FL) the components r, r +
+// RL, ... (RL = NT / FL) of factor fl, at most EM = 8 of them in registers,
+// and row RL - 1 the edges after them (b, and margin's slack).  The dot
+// products are added over a thread's components, then over the rows in order;
+// the shared b edge over the factors of the workgroup.  VEC: margin on vector
+// variables (b.vd), one z offset and one destination per factor.
+// What bounds it: memory, 2 (d + 2) + d + 3 numbers and the offsets per
+// factor; a thread per factor held 3 d numbers in registers (121 of them at d
+// <= 32, which also set how many wavefronts of the launch's other buckets fit),
+// went twice over memory above d = 64, and left most CUs without a workgroup
+// (2000 factors: eight).  So FL keeps to EM, and is no larger than gives every
+// CU a workgroup (split_lanes in graph.hip).  Per iteration before and after:
+// FP32 margin on copies 100,000 x 20 54 -> 45 us, 10,000 x 50 32 -> 14, 10,000 x
+// 100 82 -> 23, 500 x 10 8.6 -> 6.3; FP64 100,000 x 20 91 -> 71; hinge on 2000 x
+// 100 variables 68 -> 10.
+template <typename T, bool A1, int MODE, bool VEC>
+__device__ __forceinline__ void xpass_hinge_split(const XArgs<T>& a, const BucketDesc& b, int blk) {
+  constexpr int EM = 8;
+  __shared__ T red[NT];
+  const int t = threadIdx.x, d = b.d, FL = b.hl, sh = __builtin_ctz(FL), RL = NT >> sh;
+  const int fl = t & (FL - 1), r = t >> sh;
+  const int64_t f = (int64_t)blk * FL + fl;
+  const bool valid = f < b.n;
+  const int64_t ff = valid ? f : 0;
+  const int64_t nfp = b.nfp;
+  const int32_t* zo = a.idx + b.idx_off;
+  const int32_t* ds = a.idx + b.dst_off;
+  const T* P = a.par + b.par_off;
+  T* M = a.pool + b.m_off;
+  T* X = a.pool + b.x_off;
+  const bool margin = VEC || b.kind == KD_MARGIN, last = r == RL - 1;
+  constexpr bool READX = !A1 || MODE == PM_RESID, WRITEX = !A1 || MODE == PM_SAVE;
+  // all loads first; components past the last are its copies, left out below
+  int zi[EM], di[EM];
+  T zv[EM], nv[EM], uv[EM], ya[EM], xo[EM];
+  if constexpr (VEC) {
+    zi[0] = zo[ff];
+    if constexpr (MODE != PM_RESID) di[0] = ds[ff];
+  }
+#pragma unroll
+  for (int i = 0; i < EM; ++i) {
+    const int k = r + i * RL;
+    if (i * RL < d) {
+      const int64_t row = (k < d ? k : d - 1) * nfp + ff;
+      if constexpr (!VEC) {
+        zi[i] = zo[row];
+        if constexpr (MODE != PM_RESID) di[i] = ds[row];
+      }
+      uv[i] = M[row];
+      if constexpr (MODE != PM_RESID) ya[i] = P[row];
+      if constexpr (READX) xo[i] = X[row];
+    }
+  }
+  const int64_t rb = d * nfp + ff, rs = rb + nfp;
+  const int zib = zo[rb], zis = margin ? zo[rs] : 0;
+  const T mb = M[rb], ms = margin ? M[rs] : T(0);
+  T xob = T(0), xos = T(0);
+  if constexpr (READX) {
+    xob = X[rb];
+    if (margin) xos = X[rs];
+  }
+#pragma unroll
+  for (int i = 0; i < EM; ++i) {
+    const int k = r + i * RL;
+    if (i * RL < d) zv[i] = a.z[VEC ? zi[0] + (k < d ? k : d - 1) : zi[i]];
+  }
+  const T zb = a.z[zib], zs = margin ? a.z[zis] : T(0);
+  if constexpr (MODE == PM_RESID) {
+    T rmax = T(0);
+    if (valid) {
+#pragma unroll
+      for (int i = 0; i < EM; ++i)
+        if (i * RL < d) rmax = tmax(rmax, tabs(xo[i] - zv[i]));
+      rmax = tmax(rmax, tabs(xob - zb));
+      if (margin) rmax = tmax(rmax, tabs(xos - zs));
+    }
+    block_max_store(rmax, a.blockmax);
+  } else {
+    const T y = P[rb], C = P[rb + nfp], iD = P[rb + 2 * nfp];
+    const T alpha = (T)b.alpha;
+    T dot = T(0);
+#pragma unroll
+    for (int i = 0; i < EM; ++i) {
+      if (i * RL < d) {
+        T u, n;
+        state_un<T, A1>(uv[i], READX ? xo[i] : T(0), zv[i], alpha, u, n);
+        uv[i] = u;
+        nv[i] = n;
+        if (r + i * RL < d) dot += n * ya[i];
+      }
+    }
+    T ub, nb, us = T(0), ns = T(0);
+    state_un<T, A1>(mb, xob, zb, alpha, ub, nb);
+    if (margin) state_un<T, A1>(ms, xos, zs, alpha, us, ns);
+    if (last) dot += y * nb + ns;
+    red[t] = dot;
+    __syncthreads();
+    dot = red[fl];
+    for (int q = 1; q < RL; ++q) dot += red[q * FL + fl];
+    const T tau = tmin(C, tmax(T(0), (T(1) - dot) * iD));
+    const T st = tau * (T)b.irho;
+    const T xb = nb + st * y;
+    const T mnb = xb + ub;
+    if (valid) {
+#pragma unroll
+      for (int i = 0; i < EM; ++i) {
+        const int k = r + i * RL;
+        if (k < d) {
+          const T xk = nv[i] + st * ya[i];
+          const T mk = xk + uv[i];
+          M[k * nfp + ff] = mk;
+          if constexpr (WRITEX) X[k * nfp + ff] = xk;
+          a.pool[VEC ? di[0] + k * b.vs : di[i]] = mk;
+        }
+      }
+      if (last) {
+        M[rb] = mnb;
+        if constexpr (WRITEX) X[rb] = xb;
+        if (!b.ub) a.pool[ds[rb]] = mnb;
+        if (margin) {
+          const T xs = ns + st;
+          M[rs] = xs + us;
+          if constexpr (WRITEX) X[rs] = xs;
+          a.pool[ds[rs]] = xs + us;
+        }
+      }
+    }
+    // the shared b edge: the last row, inside the last wavefront (FL <= 64)
+    if (b.ub && t >= NT - 64) {
+      const T sb = admmi::wave_sum(last && valid ? mnb : T(0));
+      if (t == NT - 64) a.pool[ds[d * nfp + blk]] = sb;
     }
   }
 }
@@ -1741,11 +1878,10 @@ enum Features : int {
   FT_PAIR = 1,     // dense pair tiles
   FT_UHINGE = 2,   // shared-variable hinge
   FT_GEN = 4,      // non-overlap/wall on arbitrary variables, separable slots
-  FT_WIDE = 8,     // general hinge and margin with d <= 32
+  FT_WIDE = 8,     // general hinge and margin, lanes split the components
   FT_PAIRSP = 16,  // dense pair tiles with sparse pair state
-  FT_XWIDE = 32,   // general hinge and margin with 64 < d < NT (two sweeps, no register arrays)
+  FT_THREAD = 32,  // general hinge and margin, one thread per factor (resident driver)
   FT_TWA = 64,     // three-weight variant (packing graphs: pair tiles, constraints, slots)
-  FT_W64 = 128,    // general hinge and margin with 32 < d <= 64
   FT_LINDYN = 256, // linear-dynamics projections
   FT_LDS = 512,    // resident driver: tables in LDS, no vector layout
 };
@@ -1754,11 +1890,9 @@ constexpr int FS_PAIRSP = FT_PAIRSP | FT_GEN;
 constexpr int FS_HINGE = FT_UHINGE | FT_GEN;
 constexpr int FS_WIDE = FT_GEN | FT_WIDE;
 constexpr int FS_DYN = FT_GEN | FT_LINDYN;
-constexpr int FS_ALL = FT_PAIR | FT_UHINGE | FT_GEN | FT_WIDE | FT_PAIRSP | FT_W64 | FT_LINDYN;
-constexpr int FS_XW = FT_XWIDE | FT_GEN;
+constexpr int FS_ALL = FT_PAIR | FT_UHINGE | FT_GEN | FT_WIDE | FT_PAIRSP | FT_LINDYN;
 constexpr int FS_PAIRSP_TW = FT_PAIRSP | FT_GEN | FT_TWA;
 constexpr int FS_GEN_TW = FT_GEN | FT_TWA;
-constexpr int FS_ALLX = FS_ALL | FT_XWIDE;
 
 // The bucket of x-pass block blk, from the table in memory.
 template <typename T>
@@ -1822,15 +1956,15 @@ __device__ __forceinline__ void xpass_block(XArgs<T> a, int blk, const BucketDes
     xpass_slot<T, A1, MODE, VL>(a, b, local);
   } else if ((FS & FT_GEN) && (b.kind == KD_NONOVERLAP || b.kind == KD_WALL || b.kind == KD_EQUAL)) {
     xpass_geom<T, A1, MODE, TW, VL>(a, b, local);
-  } else if ((FS & FT_XWIDE) && (b.kind == KD_HINGE || b.kind == KD_MARGIN) && b.dmax == 0) {
-    if (VL && b.vd) xpass_hinge_wide<T, A1, MODE, true>(a, b, local);
-    else xpass_hinge_wide<T, A1, MODE, false>(a, b, local);
-  } else if ((FS & FT_W64) && (b.kind == KD_HINGE || b.kind == KD_MARGIN) && b.dmax == 64) {
-    if (VL && b.vd) xpass_hinge<T, A1, MODE, 64, true>(a, b, local);
-    else xpass_hinge<T, A1, MODE, 64, false>(a, b, local);
-  } else if ((FS & FT_WIDE) && (b.kind == KD_HINGE || b.kind == KD_MARGIN)) {
-    if (VL && b.vd) xpass_hinge<T, A1, MODE, 32, true>(a, b, local);
-    else xpass_hinge<T, A1, MODE, 32, false>(a, b, local);
+  } else if ((FS & FT_WIDE) && b.mode == BM_HINGE_SPLIT) {
+    if (b.vd) xpass_hinge_split<T, A1, MODE, true>(a, b, local);
+    else xpass_hinge_split<T, A1, MODE, false>(a, b, local);
+  } else if ((FS & FT_THREAD) && (b.kind == KD_HINGE || b.kind == KD_MARGIN) && b.dmax == 0) {
+    xpass_hinge_wide<T, A1, MODE>(a, b, local);
+  } else if ((FS & FT_THREAD) && (b.kind == KD_HINGE || b.kind == KD_MARGIN) && b.dmax == 64) {
+    xpass_hinge<T, A1, MODE, 64>(a, b, local);
+  } else if ((FS & FT_THREAD) && (b.kind == KD_HINGE || b.kind == KD_MARGIN)) {
+    xpass_hinge<T, A1, MODE, 32>(a, b, local);
   } else if (FS & FT_LINDYN) {
     xpass_lindyn<T, A1, MODE>(a, b, local);
   }
@@ -2141,7 +2275,7 @@ __global__ __launch_bounds__(NT) void zpass_kernel(ZArgs<T> a) {
 // The bucket table is staged in LDS too.  Pair tiles are not used here.
 // ---------------------------------------------------------------------------
 constexpr int RES_MAX_REG = 16;
-constexpr int FS_RES = FT_UHINGE | FT_GEN | FT_WIDE | FT_XWIDE | FT_W64 | FT_LINDYN | FT_LDS;
+constexpr int FS_RES = FT_UHINGE | FT_GEN | FT_THREAD | FT_LINDYN | FT_LDS;
 
 struct ResRegion {
   const void* src;  // global source

@@ -79,3 +79,30 @@ def test_vector_offsets_long(n, d):
     g.run(8)
     o.run(8)
     P.check(P.errors(g.z(), g.u(), g.x(), o.z, o.u, o.x, o.slot_z), 1e-9)
+
+
+@pytest.mark.parametrize("prec", [A.FP32, A.FP64])
+@pytest.mark.parametrize("n,d,alpha", [(1, 1, 1.0), (7, 8, 1.3), (16_400, 32, 1.0), (16_300, 9, 1.3), (300, 33, 1.0),
+                                       (65, 64, 1.3), (2_050, 65, 1.0), (130, 128, 1.0), (33, 129, 1.3), (17, 255, 1.0)])
+def test_hinge_on_own_variables(prec, n, d, alpha):
+    """Hinge factors on differing variables, at every split of a workgroup
+    between factors (8 to 64) and their components."""
+    p = W.svm(n, d, seed=d)
+    rng = np.random.default_rng(9)
+    g = next(g for g in p.groups if g.kind == "hinge")
+    nv = d + 1 + min(n, 200)
+    p.var_dims, p.z0 = np.ones(nv, np.int32), np.zeros(nv)
+    g.var_ids = ((np.arange(d + 1)[None, :] * 3 + rng.integers(0, nv, n)[:, None]) % nv).astype(np.int32)
+    if nv % 3 == 0:
+        g.var_ids = ((np.arange(d + 1)[None, :] + rng.integers(0, nv, n)[:, None]) % nv).astype(np.int32)
+    z0, u0 = 0.3 * rng.standard_normal(nv), 0.1 * rng.standard_normal(p.n_slots)
+    gr = A.Graph.from_problem(p, precision=prec, alpha=alpha, driver=A.DRIVER_LAUNCHES)
+    o = O.OracleGraph(p, alpha=alpha)
+    gr.set_state(z0, u0)
+    o.set_state(z0, u0)
+    gr.run(8)
+    o.run(8)
+    tol = 1e-9 if prec == A.FP64 else 1e-4
+    P.check(P.errors(gr.z(), gr.u(), gr.x(), o.z, o.u, o.x, o.slot_z), tol)
+    r, ro = gr.residuals()[0], o.residuals()[0]
+    assert abs(r - ro) <= tol * (ro + float(np.max(np.abs(o.z))))

@@ -52,3 +52,15 @@ def test_shared_workgroups_change_nothing(t_range):
     _, z, u, it = _solve(insts, 1e-4, 400, pack=4)
     _, z1, u1, it1 = _solve(insts, 1e-4, 400, pack=1)
     assert np.array_equal(it, it1) and np.array_equal(z, z1) and np.array_equal(u, u1)
+
+
+def test_workgroup_size_changes_nothing():
+    """Horizons up to 64 run on four wavefronts, up to 128 on eight, else on
+    sixteen: the same instances beside a longer one keep their bits."""
+    insts = W.mpc_batch(300, seed=72, T_range=(1, 64))
+    runs = [_solve(insts + extra, 1e-4, 400) for extra in
+            ([], W.mpc_batch(1, seed=73, T_range=(128, 128)), W.mpc_batch(1, seed=74, T_range=(129, 129)))]
+    for _, z, u, it in runs[1:]:
+        assert np.array_equal(it[:300], runs[0][3])
+        assert np.array_equal(z[:len(runs[0][1])], runs[0][1])
+        assert np.array_equal(u[:len(runs[0][2])], runs[0][2])

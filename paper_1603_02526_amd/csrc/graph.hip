@@ -245,31 +245,38 @@ bool detect_complete_pairs(const admm_graph& g, const Group& gr, std::vector<int
   return true;
 }
 
-// Hinge and margin factors take up to NT - 1 weight components; in the
-// resident driver, factors without a shared variable list keep one register
-// per component up to 64 (dmax 32 or 64) and make two sweeps over LDS above
-// that (dmax 0).
+// Hinge and margin factors take up to NT - 1 weight components.  Where one
+// thread takes a factor (the resident driver, and margin with one bias under
+// MIN_SPLIT_SLOTS) it keeps one register per component up to 64 (dmax 32 or
+// 64) and makes two sweeps above that (dmax 0).
 constexpr int HINGE_DMAX = NT - 1;
 int hinge_dmax(int d) { return d <= 32 ? 32 : d <= 64 ? 64 : 0; }
+
+// Buckets whose factors share variables have at least this many edge slots
+// before their factors go to more workgroups of fewer factors each, every one
+// with a partial sum per shared variable.  Splitting is the faster from some
+// 40,000 on, by up to a microsecond per iteration; smaller buckets keep one
+// partial sum per 256 factors, the count that n_contributions has had for them.
+constexpr int64_t MIN_SPLIT_SLOTS = 131072;
 
 // Lanes per row of factors of the shared-variable hinge (xpass_hinge_tile;
 // v factors per 16 bytes).  NT / fl lanes share a factor's d + 1 edges, at
 // most eight each; of the shapes that allow that, the one with the most
 // factors per workgroup (fewest partial sums) that still gives every CU a
-// workgroup; buckets under MIN_SLOTS edge slots keep the fewest workgroups
-// (1500 x 3: 4.6 us per iteration, split 4.9; at 4000 x 15 the split gives
-// 5.4 against 5.6).  Iterations with at least 256 / 512 / 1024 workgroups where
+// workgroup; buckets under MIN_SPLIT_SLOTS keep the fewest workgroups and
+// partial sums (1500 x 3: 4.6 us per iteration, split 4.9; 4000 x 15 5.6, split
+// 5.4; 2000 x 20 6.4, split 5.3).  Iterations with at least 256 / 512 / 1024 workgroups where
 // there are that many, FP32: 30,000 x 50 7.1 / 7.9 / 8.0 us, 100,000 x 8
 // 6.0 / 6.6 / 8.3, 100,000 x 20 8.2 / 7.9 / 10.0, 10,000 x 200 9.2 / 9.5 /
 // 9.3.  In a plan for the resident driver (one workgroup, its LDS image) the
 // rows must not need more padding than to 64 factors.
 int hinge_lanes(int64_t n, int d, int v, bool resident) {
-  constexpr int64_t MIN_BLOCKS = 256, MIN_SLOTS = 40000;
+  constexpr int64_t MIN_BLOCKS = 256;
   int fl = 64;
   while (fl > 8 && (d + NT / fl) / (NT / fl) > 8) fl /= 2;
   if (resident) {
     while (fl > 8 && round_up(n, fl * v) > round_up(n, 64)) fl /= 2;
-  } else if (n * (d + 1) >= MIN_SLOTS) {
+  } else if (n * (d + 1) >= MIN_SPLIT_SLOTS) {
     while (fl > 8 && (n + fl * v - 1) / (fl * v) < MIN_BLOCKS) fl /= 2;
   }
   return fl;
@@ -604,8 +611,12 @@ admm_status build_plan(admm_graph& g, Plan& P, bool no_tiles) {
     } else if (gr.kind == KD_MARGIN) {
       // ---------------- margin: the general hinge path with a slack slot ----------------
       const int d = g.dim[gr.vids[0]];
-      b.mode = P.no_tiles ? BM_GEN_FACTOR : BM_HINGE_SPLIT;
-      if (!P.no_tiles) b.hl = split_lanes(gr.n, d);
+      // one bias for every factor (the usual graph): one partial per workgroup
+      b.ub = 1;
+      for (int64_t f = 1; f < gr.n && b.ub; ++f) b.ub = zof(f, 1) == zof(0, 1);
+      const bool split = !P.no_tiles && !(b.ub && gr.n * (d + 2) < MIN_SPLIT_SLOTS);
+      b.mode = split ? BM_HINGE_SPLIT : BM_GEN_FACTOR;
+      if (split) b.hl = split_lanes(gr.n, d);
       b.n = gr.n;
       b.nfp = round_up(gr.n, 64);
       b.d = d;
@@ -632,10 +643,7 @@ admm_status build_plan(admm_graph& g, Plan& P, bool no_tiles) {
       P.n_m += (int64_t)b.nslot * b.nfp;
       b.dst_off = (int64_t)P.idx.size();
       P.idx.resize(P.idx.size() + (int64_t)b.nslot * b.nfp, -1);
-      // one bias for every factor (the usual graph): one partial per workgroup
-      b.ub = 1;
-      for (int64_t f = 1; f < gr.n && b.ub; ++f) b.ub = zof(f, 1) == zof(0, 1);
-      const int64_t fb = P.no_tiles ? NT : b.hl;   // factors per workgroup
+      const int64_t fb = split ? b.hl : NT;   // factors per workgroup
       const int64_t tiles = (gr.n + fb - 1) / fb;
       for (int64_t f = 0; f < gr.n; ++f)
         for (int s = 0; s < d + 2; ++s) {
@@ -833,7 +841,9 @@ admm_status build_plan(admm_graph& g, Plan& P, bool no_tiles) {
     if (!P.ualpha.empty())
       for (int64_t q = us0; q < us; ++q) P.ualpha[q] = ag;
     // components per edge, if one number for every factor of vector_layout's kinds
-    int vd = gr.kind == KD_MARGIN || gr.kind == KD_EQUAL || (separable && gr.arity == 1) ? g.dim[gr.vids[0]] : 0;
+    const bool vec = b.mode == BM_HINGE_SPLIT ? gr.kind == KD_MARGIN
+                                              : gr.kind == KD_EQUAL || (separable && gr.arity == 1);
+    int vd = vec ? g.dim[gr.vids[0]] : 0;
     for (int64_t f = 1; f < gr.n && vd; ++f)
       if (g.dim[gr.vids[f * gr.arity]] != vd) vd = 0;
     vec_dim.push_back(vd);

@@ -191,6 +191,7 @@ struct Engine : EngineBase {
         else if (b.mode == BM_GEN_SLOT || b.kind == KD_NONOVERLAP || b.kind == KD_WALL ||
                  b.kind == KD_EQUAL)
           need |= FT_GEN;
+        else if (b.kind == KD_HINGE || b.kind == KD_MARGIN) need |= FT_THREAD;
         else need |= FT_LINDYN;
       }
       if (twa) need |= FT_TWA;
@@ -200,7 +201,9 @@ struct Engine : EngineBase {
            : ((need & ~FS_HINGE) == 0)  ? FS_HINGE
            : ((need & ~FS_WIDE) == 0)   ? FS_WIDE
            : ((need & ~FS_DYN) == 0)    ? FS_DYN
-                                        : FS_ALL;
+           : ((need & ~FS_THREAD) == 0) ? FS_THREAD
+           : ((need & ~FS_ALL) == 0)    ? FS_ALL
+                                        : FS_ALLX;
     }
     n_b = (int64_t)P.var_b.size();
     w_stride = P.w_stride;
@@ -360,7 +363,9 @@ struct Engine : EngineBase {
     else if (fs == FS_HINGE) launch_x_fs<A1, FS_HINGE>(mode, st, e0, e1);
     else if (fs == FS_WIDE) launch_x_fs<A1, FS_WIDE>(mode, st, e0, e1);
     else if (fs == FS_DYN) launch_x_fs<A1, FS_DYN>(mode, st, e0, e1);
+    else if (fs == FS_THREAD) launch_x_fs<A1, FS_THREAD>(mode, st, e0, e1);
     else if (fs == FS_ALL) launch_x_fs<A1, FS_ALL>(mode, st, e0, e1);
+    else if (fs == FS_ALLX) launch_x_fs<A1, FS_ALLX>(mode, st, e0, e1);
     else if constexpr (A1) {
       // the three-weight variant runs with alpha = 1 only
       if (fs == FS_PAIRSP_TW) launch_x_fs<A1, FS_PAIRSP_TW>(mode, st, e0, e1);

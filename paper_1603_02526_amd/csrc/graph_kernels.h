@@ -1361,8 +1361,9 @@ __device__ __forceinline__ void xpass_hinge_wide(const XArgs<T>& a, const Bucket
   }
 }
 
-// The same operators outside the resident driver: a workgroup takes FL = b.hl
-// consecutive factors, thread (r, fl) = (t / FL, t % FL) the components r, r +
+// The same operators with a factor's components split over lanes (outside the
+// resident driver; not where few factors share a bias, whose partial sums are
+// one per NT factors): a workgroup takes FL = b.hl consecutive factors, thread (r, fl) = (t / FL, t % FL) the components r, r +
 // RL, ... (RL = NT / FL) of factor fl, at most EM = 8 of them in registers,
 // and row RL - 1 the edges after them (b, and margin's slack).  The dot
 // products are added over a thread's components, then over the rows in order;
@@ -1880,7 +1881,7 @@ enum Features : int {
   FT_GEN = 4,      // non-overlap/wall on arbitrary variables, separable slots
   FT_WIDE = 8,     // general hinge and margin, lanes split the components
   FT_PAIRSP = 16,  // dense pair tiles with sparse pair state
-  FT_THREAD = 32,  // general hinge and margin, one thread per factor (resident driver)
+  FT_THREAD = 32,  // general hinge and margin, one thread per factor
   FT_TWA = 64,     // three-weight variant (packing graphs: pair tiles, constraints, slots)
   FT_LINDYN = 256, // linear-dynamics projections
   FT_LDS = 512,    // resident driver: tables in LDS, no vector layout
@@ -1893,6 +1894,8 @@ constexpr int FS_DYN = FT_GEN | FT_LINDYN;
 constexpr int FS_ALL = FT_PAIR | FT_UHINGE | FT_GEN | FT_WIDE | FT_PAIRSP | FT_LINDYN;
 constexpr int FS_PAIRSP_TW = FT_PAIRSP | FT_GEN | FT_TWA;
 constexpr int FS_GEN_TW = FT_GEN | FT_TWA;
+constexpr int FS_THREAD = FT_GEN | FT_THREAD;
+constexpr int FS_ALLX = FS_ALL | FT_THREAD;
 
 // The bucket of x-pass block blk, from the table in memory.
 template <typename T>

@@ -44,7 +44,10 @@ def _copies(n, d, form):
 @pytest.mark.parametrize("prec", [A.FP32, A.FP64])
 @pytest.mark.parametrize("form", ["vector", "lists", "dims"])
 @pytest.mark.parametrize("n,d,alpha", [(1, 2, 1.0), (300, 1, 1.0), (129, 2, 1.3), (700, 31, 1.0), (64, 32, 1.3),
-                                       (515, 33, 1.0), (90, 65, 1.0), (70, 200, 1.3)])
+                                       (515, 33, 1.0), (90, 65, 1.0), (70, 200, 1.3),
+                                       # margins large enough to be split over lanes
+                                       (33_000, 2, 1.3), (16_400, 7, 1.0), (4_001, 31, 1.0), (3_900, 32, 1.3),
+                                       (3_745, 33, 1.0), (2_000, 65, 1.3), (1_000, 129, 1.0), (511, 255, 1.0)])
 def test_vector_offsets(prec, form, n, d, alpha):
     p = _copies(n, d, form)
     rng = np.random.default_rng(9)

@@ -64,3 +64,29 @@ def test_workgroup_size_changes_nothing():
         assert np.array_equal(it[:300], runs[0][3])
         assert np.array_equal(z[:len(runs[0][1])], runs[0][1])
         assert np.array_equal(u[:len(runs[0][2])], runs[0][2])
+
+
+@pytest.mark.parametrize("sizes", [[(256, 12, 4), (1, 12, 4), (256, 4, 1), (100, 8, 3), (17, 5, 2)], [(1, 1, 1)],
+                                   [(40, 12, 4)] * 5])
+def test_dual_completion_sizes(sizes):
+    """Dual completion with the longest z of its range (64 KB staged per
+    workgroup) beside the shortest, and ragged groups of four instances.
+    A stable A (spectral radius 0.95) keeps mu within its terms' sum: FP32
+    rounding of a backward recursion, 1e-5 in norm."""
+    from oracle import warmstart as WS
+    from paper_1603_02526_amd import mpc as M
+    from tests.test_gpu_mpc import _gpu_u_to_oracle
+    rng = np.random.default_rng(5)
+    insts = []
+    for T, n, m in sizes:
+        A, B = W.mpc_system(rng, n, m)
+        insts.append(W.MPCInstance(T, n, m, A, B, rng.standard_normal(n), np.ones(n), np.full(m, 0.1), 1.0))
+    b = M.MPCBatch(insts)
+    z = rng.standard_normal(b.z_total).astype(np.float32)
+    u = torch.full((b.u_total,), 7.0, dtype=torch.float32, device="cuda")
+    b.dual_complete(torch.tensor(z, device="cuda"), u)
+    got = u.cpu().numpy().astype(np.float64)
+    for i, (inst, zi) in enumerate(zip(insts, b.split_z(z))):
+        ug = got[b.u_off[i]:b.u_off[i] + 3 * inst.T * (inst.n + inst.m)]
+        want = WS.dual_completion(inst, zi.astype(np.float64))
+        assert rel(_gpu_u_to_oracle(inst, ug), want) < 1e-5, (inst.T, inst.n)

@@ -246,8 +246,8 @@ bool detect_complete_pairs(const admm_graph& g, const Group& gr, std::vector<int
 }
 
 // Hinge and margin factors take up to NT - 1 weight components.  Where one
-// thread takes a factor (the resident driver, and margin with one bias under
-// MIN_SPLIT_SLOTS) it keeps one register per component up to 64 (dmax 32 or
+// thread takes a factor (the resident driver, and margin with one bias and d <=
+// 32 under MIN_SPLIT_SLOTS) it keeps one register per component up to 64 (dmax 32 or
 // 64) and makes two sweeps above that (dmax 0).
 constexpr int HINGE_DMAX = NT - 1;
 int hinge_dmax(int d) { return d <= 32 ? 32 : d <= 64 ? 64 : 0; }
@@ -614,7 +614,10 @@ admm_status build_plan(admm_graph& g, Plan& P, bool no_tiles) {
       // one bias for every factor (the usual graph): one partial per workgroup
       b.ub = 1;
       for (int64_t f = 1; f < gr.n && b.ub; ++f) b.ub = zof(f, 1) == zof(0, 1);
-      const bool split = !P.no_tiles && !(b.ub && gr.n * (d + 2) < MIN_SPLIT_SLOTS);
+      // a small bucket keeps one partial sum per 256 factors where a thread can
+      // hold a factor in registers; above, its chain of d dependent loads and two
+      // sweeps would be the iteration (700 x 180: 145 us, split 9)
+      const bool split = !P.no_tiles && !(b.ub && d <= 32 && gr.n * (d + 2) < MIN_SPLIT_SLOTS);
       b.mode = split ? BM_HINGE_SPLIT : BM_GEN_FACTOR;
       if (split) b.hl = split_lanes(gr.n, d);
       b.n = gr.n;

@@ -1185,28 +1185,32 @@ admm_status admm_graph_finalize(admm_graph* g, int32_t device) {
     }
   }
   admm_graph_info& I = g->info;
-  I.n_vars = (int64_t)g->dim.size();
-  I.n_scalars = g->nz;
-  I.n_factors = g->n_factors;
-  I.n_edges = g->n_edges;
-  I.n_slots = g->n_slots;
-  I.n_buckets = (int64_t)P.bt.size();
-  I.n_pair_tiles = P.n_pair_tiles;
-  I.n_contributions = P.n_zc;
-  I.precision = g->precision;
-  I.alpha_is_one = P.alpha_one;
-  I.state_bytes = (P.zc_span + 2 * P.n_m) * es;
-  // algorithmic: state read + write per slot (m; plus x when alpha != 1) and
-  // per-factor prox data; layout: indices, partial sums and their reads.
-  I.algo_bytes_per_iter = P.algo_elems * es * (P.alpha_one ? 1 : 2);
-  I.layout_bytes_per_iter = P.layout_elems * es + P.layout_idx_bytes;
-  // without the resident driver: launches when asked for, else recorded
-  // iteration blocks (the same kernels in the same order)
-  const int32_t eager = g->driver == ADMM_DRIVER_LAUNCHES ? ADMM_DRIVER_LAUNCHES : ADMM_DRIVER_GRAPH;
-  I.driver = P.resident ? ADMM_DRIVER_RESIDENT : eager;
-  I.sparse_pair_state = P.n_flags > 0 ? 1 : 0;
-  I.three_weight = g->twa;
-  I.resident_lds_bytes = P.resident ? (int32_t)resident_image_bytes(P, g->nz, es) : 0;
+  // (of the plan that runs: again after a change of driver)
+  auto fill_info = [&]() {
+    I.n_vars = (int64_t)g->dim.size();
+    I.n_scalars = g->nz;
+    I.n_factors = g->n_factors;
+    I.n_edges = g->n_edges;
+    I.n_slots = g->n_slots;
+    I.n_buckets = (int64_t)P.bt.size();
+    I.n_pair_tiles = P.n_pair_tiles;
+    I.n_contributions = P.n_zc;
+    I.precision = g->precision;
+    I.alpha_is_one = P.alpha_one;
+    I.state_bytes = (P.zc_span + 2 * P.n_m) * es;
+    // algorithmic: state read + write per slot (m; plus x when alpha != 1) and
+    // per-factor prox data; layout: indices, partial sums and their reads.
+    I.algo_bytes_per_iter = P.algo_elems * es * (P.alpha_one ? 1 : 2);
+    I.layout_bytes_per_iter = P.layout_elems * es + P.layout_idx_bytes;
+    // without the resident driver: launches when asked for, else recorded
+    // iteration blocks (the same kernels in the same order)
+    const int32_t eager = g->driver == ADMM_DRIVER_LAUNCHES ? ADMM_DRIVER_LAUNCHES : ADMM_DRIVER_GRAPH;
+    I.driver = P.resident ? ADMM_DRIVER_RESIDENT : eager;
+    I.sparse_pair_state = P.n_flags > 0 ? 1 : 0;
+    I.three_weight = g->twa;
+    I.resident_lds_bytes = P.resident ? (int32_t)resident_image_bytes(P, g->nz, es) : 0;
+  };
+  fill_info();
   if (admm_status s = admmi::probe_device(device)) {
     g->state = 1;
     return s;
@@ -1218,9 +1222,10 @@ admm_status admm_graph_finalize(admm_graph* g, int32_t device) {
     if (admm_status s = eng->resident_check(P, g->nz, P.alpha_one)) {
       if (g->driver == ADMM_DRIVER_RESIDENT) return s;
       admmi::clear_err();
-      g->plan.resident = false;  // auto: the same plan runs with launches
-      I.driver = eager;
-      I.resident_lds_bytes = 0;
+      // auto: launches, on a plan laid out for them (the short z-lists and
+      // the shared hinge of a resident plan are laid out for LDS)
+      if (admm_status e = build_plan(*g, g->plan, false)) return e;
+      fill_info();
     }
   }
   eng->graph_block = I.driver == ADMM_DRIVER_GRAPH ? g->graph_block : 0;

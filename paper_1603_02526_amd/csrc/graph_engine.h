@@ -176,6 +176,8 @@ struct Engine : EngineBase {
 
   admm_status upload(const Plan& P, const std::vector<double>& z0, double rho,
                      double alpha_) override {
+    if (P.no_tiles != P.resident)
+      return admmi::set_err(ADMM_E_ARG, "internal: the plan is laid out for another driver");
     alpha1 = P.alpha_one;
     (void)alpha_;
     alpha = (T)alpha_;

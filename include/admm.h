@@ -322,7 +322,10 @@ admm_status admm_mpc_batch_sizes(const admm_mpc_batch* b, int64_t* z_total,
  * u^0 = 0; 1: u^0 from dual completion of z_init (requires z_init).  Each
  * instance stops at the first iteration with r = max_e |x_e - z_b| <= tol and
  * s = rho max_b |z_b - z_b(previous)| <= tol; iters_out holds that iteration,
- * or -max_iter when it did not converge. */
+ * or -max_iter when it did not converge.  The solves of one batch share its
+ * work queue and its dual buffer: on different streams they have to be ordered
+ * (solves that overlap may leave each other's instances out; the next one
+ * handles every instance again). */
 admm_status admm_mpc_batch_solve(admm_mpc_batch* b, const float* x0, const float* z_init,
                                  int32_t dual_mode, float tol, int32_t max_iter,
                                  float* z_out, int32_t* iters_out, void* stream);

@@ -196,7 +196,9 @@ __device__ __forceinline__ int solve_tiles(const SolveArgs& a, const MpcInst& I,
       At[c] = r < K4 ? P[o.MT + r * N4 + 4 * c + g] : 0.f;
     }
   }
-  // per component: cost factor, box bounds (none for states)
+  // per component: cost factor, box bounds.  Without bounds: two NaN, of which
+  // v_med3_f32 (the least of the operands that are numbers) keeps its input,
+  // a NaN too, which infinite bounds would make an infinity.
   f4v cq = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
@@ -204,8 +206,9 @@ __device__ __forceinline__ int solve_tiles(const SolveArgs& a, const MpcInst& I,
     if (isx && i < N) cq[q] = P[o.cq + i];
     if (isu) cq[q] = P[o.cr + q];
   }
-  const float lo = isu ? P[o.lo] : -__builtin_inff(), hi = isu ? P[o.lo + 1] : __builtin_inff();
   const bool nobox = isu && !box;
+  const float lo = isu && box ? P[o.lo] : __builtin_nanf("");
+  const float hi = isu && box ? P[o.lo + 1] : __builtin_nanf("");
   constexpr float THIRD = 1.f / 3.f;
   TileState<TPW> s, d;   // before and after an iteration
   float cz[TPW], cA[TPW];   // z-averages of the own variable and of x_t

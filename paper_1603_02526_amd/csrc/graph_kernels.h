@@ -1207,8 +1207,7 @@ __device__ __forceinline__ void xpass_hinge_tile(const XArgs<T>& a, const Bucket
         T u, n;
         state_un<T, A1>(mv[i][v], A1 ? T(0) : xv[i][v], zv[i], alpha, u, n);
         mv[i][v] = u;          // mv holds u from here on
-        pv[i][v] = on ? pv[i][v] : T(0);
-        dot[v] += n * pv[i][v];
+        dot[v] += on ? n * pv[i][v] : T(0);
       }
     }
 #pragma unroll

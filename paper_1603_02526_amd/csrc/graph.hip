@@ -31,22 +31,42 @@ using namespace admmg;
 
 namespace admmg {
 
-int64_t zpass_blocks(const Plan& P) {
-  return ((int64_t)P.var_t.size() + P.t_lpb - 1) / P.t_lpb + (int64_t)P.var_b.size() +
-         ((int64_t)P.var_w.size() + ZPB - 1) / ZPB + ((int64_t)P.var_l.size() + NT - 1) / NT;
+int64_t ImageSizes::zblocks() const {
+  return n_b + (n_w + ZPB - 1) / ZPB + (n_l + NT - 1) / NT;
 }
 
-// Bytes of the resident driver's LDS image: every region rounded up to 16 B,
-// in the order resident_layout assigns them.
-int64_t resident_image_bytes(const Plan& P, int64_t nz, int64_t es) {
+int64_t ImageSizes::bytes(int64_t nz, int64_t es) const {
   auto r16 = [](int64_t b) { return (b + 15) / 16 * 16; };
-  int64_t b = r16((P.zc_span + 2 * P.n_m) * es) + 2 * r16(nz * es) + r16((int64_t)P.par.size() * es) +
-              r16((int64_t)P.idx.size() * 4);
-  b += r16((int64_t)P.var_b.size() * 4) + r16((int64_t)P.rng_b.size() * 8) + r16((int64_t)P.deg_b.size() * es);
-  b += r16((int64_t)P.var_w.size() * 4) + r16((int64_t)P.rng_w.size() * 8) + r16((int64_t)P.deg_w.size() * es);
-  b += r16((int64_t)P.var_l.size() * 4) + r16((int64_t)P.deg_l.size() * es);
-  b += r16((int64_t)P.bt.size() * (int64_t)sizeof(BucketDesc));
+  int64_t b = r16((zc + 2 * m) * es) + 2 * r16(nz * es) + r16(par * es) + r16(idx * 4);
+  b += r16(n_b * 4) + r16(n_b * 16) + r16(n_b * es);
+  b += r16(n_w * 4) + r16(rng_w * 16) + r16(n_w * es);
+  b += r16(n_l * 4) + r16(n_l * es);
+  b += r16(buckets * (int64_t)sizeof(BucketDesc));
   return b;
+}
+
+// Those of a plan as it is laid out.
+ImageSizes image_sizes(const Plan& P) {
+  ImageSizes s;
+  s.zc = P.zc_span;
+  s.m = P.n_m;
+  s.par = (int64_t)P.par.size();
+  s.idx = (int64_t)P.idx.size();
+  s.n_b = (int64_t)P.var_b.size();
+  s.n_w = (int64_t)P.var_w.size();
+  s.rng_w = (int64_t)P.rng_w.size() / 2;
+  s.n_l = (int64_t)P.var_l.size();
+  s.buckets = (int64_t)P.bt.size();
+  s.xblocks = P.xblocks;
+  return s;
+}
+
+int64_t zpass_blocks(const Plan& P) {
+  return ((int64_t)P.var_t.size() + P.t_lpb - 1) / P.t_lpb + image_sizes(P).zblocks();
+}
+
+int64_t resident_image_bytes(const Plan& P, int64_t nz, int64_t es) {
+  return image_sizes(P).bytes(nz, es);
 }
 
 }  // namespace admmg
@@ -352,6 +372,8 @@ admm_status build_plan(admm_graph& g, Plan& P, bool no_tiles) {
   if (alpha_mixed) P.ualpha.assign(g.n_slots, g.alpha);
   P.no_tiles = no_tiles;
   std::vector<int> vec_dim;   // per bucket, for vector_layout
+  ImageSizes adm;                          // Plan::admit, here as the difference from the layout
+  std::vector<int64_t> adm_len(g.nz, 0);   // (z-list lengths too)
   // Every contribution to a z scalar, in emission order: z index and the
   // index-buffer slot that will receive its position in the z-major buffer.
   struct Emit { int64_t z; int64_t key; };
@@ -545,6 +567,7 @@ admm_status build_plan(admm_graph& g, Plan& P, bool no_tiles) {
         if (zof(0, e) != zof(0, 0) + e) b.zaff = -1;
       }
       // state and parameters per workgroup: [edge][FB], 16-byte aligned
+      const int64_t par0 = (int64_t)P.par.size();
       P.par.resize((size_t)round_up((int64_t)P.par.size(), 4), 0.0);
       b.par_off = (int64_t)P.par.size();
       P.par.resize(P.par.size() + (size_t)(d + 3) * b.nfp, 0.0);
@@ -574,6 +597,15 @@ admm_status build_plan(admm_graph& g, Plan& P, bool no_tiles) {
           ++us;
         }
       P.algo_elems += (int64_t)gr.n * (2 * gr.arity + d + 3);
+      // Admission to the resident driver (Plan::admit) counts a bucket as rows
+      // of all factors, padded to 64, and a partial sum per 128 factors up
+      // to d = 32 and per 256 above.
+      const int64_t an = round_up(gr.n, 64), af = d <= 32 ? NT / 2 : NT, at = (gr.n + af - 1) / af;
+      adm.par -= (d + 3) * (b.nfp - an) + (b.par_off - par0);
+      adm.m -= gr.arity * (b.nfp - an);
+      adm.idx -= gr.arity * (tiles - at);
+      adm.xblocks -= tiles - at;
+      for (int e = 0; e < gr.arity; ++e) adm_len[zof(0, e)] -= tiles - at;
     } else if (gr.kind == KD_EQUAL) {
       // ---------------- equality: one thread per component pair ----------------
       b.mode = BM_GEN_FACTOR;
@@ -883,19 +915,30 @@ admm_status build_plan(admm_graph& g, Plan& P, bool no_tiles) {
     P.var_t.push_back((int32_t)tz[k]);
     P.deg_t.push_back(deg[tz[k]]);
   }
-  int64_t sum_w = 0, max_w = 0, n_wl = 0, n_ll = 0, sum_b = 0;
-  for (int64_t zi = 0; zi < g.nz; ++zi) {
-    if (tk[zi] >= 0) continue;
-    if (len[zi] > ZB_MIN) sum_b += len[zi];
-    else if (len[zi] > LANE_MAX) { sum_w += len[zi]; max_w = std::max(max_w, len[zi]); ++n_wl; }
-    else ++n_ll;
-  }
-  const int64_t S_w = round_up(std::max<int64_t>(max_w, 1), ZSEG);
-  const bool pad_w = n_wl > 0 && S_w * n_wl <= 2 * sum_w + 4096;
+  struct Lists { int64_t n_b, n_w, n_l, S_w, w_base, l_base, total; bool pad_w; };
+  auto size_lists = [&](auto length) {
+    Lists s{};
+    int64_t sum_w = 0, max_w = 0, sum_b = 0;
+    for (int64_t zi = 0; zi < g.nz; ++zi) {
+      if (tk[zi] >= 0) continue;
+      const int64_t L = length(zi);
+      if (L > ZB_MIN) { sum_b += L; ++s.n_b; }
+      else if (L > LANE_MAX) { sum_w += L; max_w = std::max(max_w, L); ++s.n_w; }
+      else ++s.n_l;
+    }
+    s.S_w = round_up(std::max<int64_t>(max_w, 1), ZSEG);
+    s.pad_w = s.n_w > 0 && s.S_w * s.n_w <= 2 * sum_w + 4096;
+    s.w_base = round_up(t_span + sum_b, 16);
+    s.l_base = round_up(s.w_base + (s.pad_w ? s.S_w * s.n_w : sum_w), 16);
+    s.total = s.l_base + LANE_MAX * s.n_l;
+    return s;
+  };
+  const Lists ls = size_lists([&](int64_t zi) { return len[zi]; });
+  const int64_t S_w = ls.S_w, n_ll = ls.n_l, zc_total = ls.total;
+  const bool pad_w = ls.pad_w;
   P.w_stride = pad_w ? S_w : 0;
-  P.w_base = round_up(t_span + sum_b, 16);
-  P.l_base = round_up(P.w_base + (pad_w ? S_w * n_wl : sum_w), 16);
-  const int64_t zc_total = P.l_base + LANE_MAX * n_ll;
+  P.w_base = ls.w_base;
+  P.l_base = ls.l_base;
   std::vector<int64_t> base(g.nz, 0);
   {
     int64_t pb = t_span, pw = P.w_base, kw = 0, kl = 0;
@@ -957,6 +1000,7 @@ admm_status build_plan(admm_graph& g, Plan& P, bool no_tiles) {
   if (!P.no_tiles)
     for (size_t i = 0; i < P.bt.size(); ++i) vector_layout(P, P.bt[i], vec_dim[i]);
   // pool = [contributions | m regions | x regions], each region aligned
+  const int64_t n_m0 = P.n_m;
   P.n_m = round_up(P.n_m, 64);
   P.zc_span = round_up(zc_total, 64);
   for (BucketDesc& b : P.bt) {
@@ -964,6 +1008,20 @@ admm_status build_plan(admm_graph& g, Plan& P, bool no_tiles) {
     b.x_off = b.m_off + P.n_m;
   }
   for (auto& v : P.upos) v += P.zc_span;
+  if (P.no_tiles) {
+    const Lists al = size_lists([&](int64_t zi) { return len[zi] + adm_len[zi]; });
+    const ImageSizes is = image_sizes(P);
+    P.admit = is;
+    P.admit.zc = round_up(al.total, 64);
+    P.admit.m = round_up(n_m0 + adm.m, 64);
+    P.admit.par += adm.par;
+    P.admit.idx += adm.idx;
+    P.admit.n_b = al.n_b;
+    P.admit.n_w = al.n_w;
+    P.admit.rng_w = al.pad_w ? 0 : al.n_w;
+    P.admit.n_l = al.n_l;
+    P.admit.xblocks += adm.xblocks;
+  }
   if (P.zc_span + 2 * P.n_m > 0x7fffffffLL)
     return admmi::set_err(ADMM_E_UNSUPPORTED, "more than 2^31 pool elements");
   // each contribution is written once and read once; its destination index read once
@@ -972,7 +1030,7 @@ admm_status build_plan(admm_graph& g, Plan& P, bool no_tiles) {
   return ADMM_OK;
 }
 
-constexpr int64_t RES_LDS_BYTES = 96 * 1024;   // image limit of the resident driver
+constexpr int64_t RES_LDS_BYTES = 96 * 1024;   // admission limit of the resident driver (Plan::admit)
 constexpr int32_t DEFAULT_GRAPH_BLOCK = 32;     // iterations per block of the graph driver
 constexpr int64_t RES_AUTO_MAX_BLOCKS = 64;    // auto: resident up to this many pass blocks
 
@@ -1155,8 +1213,9 @@ admm_status admm_graph_finalize(admm_graph* g, int32_t device) {
                           (long long)g->n_slots);
   if (admm_status s = build_plan(*g, g->plan, want_res)) return s;
   if (want_res) {
-    const int64_t bytes = resident_image_bytes(g->plan, g->nz, es_);
-    const int64_t blocks = g->plan.xblocks + zpass_blocks(g->plan);
+    const ImageSizes& a = g->plan.admit;
+    const int64_t bytes = a.bytes(g->nz, es_);
+    const int64_t blocks = a.xblocks + a.zblocks();
     bool ok = bytes <= RES_LDS_BYTES;
     if (g->driver == ADMM_DRIVER_RESIDENT && !ok)
       return admmi::set_err(ADMM_E_UNSUPPORTED, "resident driver: LDS image of %lld B exceeds %lld B",

@@ -10,6 +10,16 @@
 
 namespace admmg {
 
+// Element counts of the resident driver's LDS image, and its pass blocks.
+struct ImageSizes {
+  int64_t zc = 0, m = 0, par = 0, idx = 0;           // contributions, state, parameters, tables
+  int64_t n_b = 0, n_w = 0, rng_w = 0, n_l = 0;      // z lists: long, medium (with ranges), short
+  int64_t buckets = 0, xblocks = 0;
+  int64_t zblocks() const;
+  // every region rounded up to 16 B, in the order resident_layout assigns them
+  int64_t bytes(int64_t nz, int64_t es) const;
+};
+
 // Host layout of a finalized graph (precision independent).
 struct Plan {
   std::vector<BucketDesc> bt;
@@ -42,6 +52,10 @@ struct Plan {
   int64_t algo_elems = 0, layout_idx_bytes = 0, layout_elems = 0;
   int64_t n_pair_tiles = 0;
   int64_t n_flags = 0;          // sparse pair-state flag words (NT per tile)
+  // Resident plans: the sizes by which the driver admits a graph.  They are
+  // the image's own but for the shared hinge, whose split into workgroups
+  // (padding, partial sums: at most 1.2 KB more) does not decide what fits.
+  ImageSizes admit;
   bool no_tiles = false;        // input: for the resident driver (no dense pair tiles, no vector layout)
   bool resident = false;        // output of finalize: resident driver chosen
 };

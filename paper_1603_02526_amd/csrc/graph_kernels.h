@@ -1880,7 +1880,7 @@ enum Features : int {
   FT_GEN = 4,      // non-overlap/wall on arbitrary variables, separable slots
   FT_WIDE = 8,     // general hinge and margin, lanes split the components
   FT_PAIRSP = 16,  // dense pair tiles with sparse pair state
-  FT_THREAD = 32,  // general hinge and margin, one thread per factor
+  FT_THREAD = 32,  // general hinge and margin, one thread per factor (launches: margin, d <= 32)
   FT_TWA = 64,     // three-weight variant (packing graphs: pair tiles, constraints, slots)
   FT_LINDYN = 256, // linear-dynamics projections
   FT_LDS = 512,    // resident driver: tables in LDS, no vector layout
@@ -1961,9 +1961,12 @@ __device__ __forceinline__ void xpass_block(XArgs<T> a, int blk, const BucketDes
   } else if ((FS & FT_WIDE) && b.mode == BM_HINGE_SPLIT) {
     if (b.vd) xpass_hinge_split<T, A1, MODE, true>(a, b, local);
     else xpass_hinge_split<T, A1, MODE, false>(a, b, local);
-  } else if ((FS & FT_THREAD) && (b.kind == KD_HINGE || b.kind == KD_MARGIN) && b.dmax == 0) {
+  } else if ((FS & FT_THREAD) && (FS & FT_LDS) && (b.kind == KD_HINGE || b.kind == KD_MARGIN) &&
+             b.dmax == 0) {
+    // (above 32 components, a thread per factor in the resident driver only)
     xpass_hinge_wide<T, A1, MODE>(a, b, local);
-  } else if ((FS & FT_THREAD) && (b.kind == KD_HINGE || b.kind == KD_MARGIN) && b.dmax == 64) {
+  } else if ((FS & FT_THREAD) && (FS & FT_LDS) && (b.kind == KD_HINGE || b.kind == KD_MARGIN) &&
+             b.dmax == 64) {
     xpass_hinge<T, A1, MODE, 64>(a, b, local);
   } else if ((FS & FT_THREAD) && (b.kind == KD_HINGE || b.kind == KD_MARGIN)) {
     xpass_hinge<T, A1, MODE, 32>(a, b, local);

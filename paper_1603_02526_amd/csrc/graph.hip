@@ -1030,7 +1030,7 @@ admm_status build_plan(admm_graph& g, Plan& P, bool no_tiles) {
   return ADMM_OK;
 }
 
-constexpr int64_t RES_LDS_BYTES = 96 * 1024;   // admission limit of the resident driver (Plan::admit)
+constexpr int64_t RES_LDS_BYTES = 96 * 1024;   // image limit of the resident driver
 constexpr int32_t DEFAULT_GRAPH_BLOCK = 32;     // iterations per block of the graph driver
 constexpr int64_t RES_AUTO_MAX_BLOCKS = 64;    // auto: resident up to this many pass blocks
 
@@ -1213,7 +1213,11 @@ admm_status admm_graph_finalize(admm_graph* g, int32_t device) {
                           (long long)g->n_slots);
   if (admm_status s = build_plan(*g, g->plan, want_res)) return s;
   if (want_res) {
-    const ImageSizes& a = g->plan.admit;
+    // Asked for, the driver is given by Plan::admit; chosen by itself, by the
+    // image as it is (FP32, 300 factors of d = 23, admitted but 1 KB over the
+    // limit: launches 5.7 us per iteration, resident 10.1; 20 of d = 150, the
+    // other way round: 5.2 and 3.7).
+    const ImageSizes a = g->driver == ADMM_DRIVER_RESIDENT ? g->plan.admit : image_sizes(g->plan);
     const int64_t bytes = a.bytes(g->nz, es_);
     const int64_t blocks = a.xblocks + a.zblocks();
     bool ok = bytes <= RES_LDS_BYTES;

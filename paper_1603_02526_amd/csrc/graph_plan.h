@@ -52,9 +52,10 @@ struct Plan {
   int64_t algo_elems = 0, layout_idx_bytes = 0, layout_elems = 0;
   int64_t n_pair_tiles = 0;
   int64_t n_flags = 0;          // sparse pair-state flag words (NT per tile)
-  // Resident plans: the sizes by which the driver admits a graph.  They are
-  // the image's own but for the shared hinge, whose split into workgroups
-  // (padding, partial sums: at most 1.2 KB more) does not decide what fits.
+  // Resident plans: the sizes by which the driver admits a graph that asks
+  // for it.  They are the image's own but for the shared hinge, whose split
+  // into workgroups (padding, partial sums: at most 1.2 KB more) does not
+  // decide what fits.
   ImageSizes admit;
   bool no_tiles = false;        // input: for the resident driver (no dense pair tiles, no vector layout)
   bool resident = false;        // output of finalize: resident driver chosen

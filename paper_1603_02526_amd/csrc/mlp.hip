@@ -572,8 +572,20 @@ void forward(admm_mlp* n, const float* x, int batch, float* y, hipStream_t st) {
 // each.  Consecutive workgroups go to different XCDs, so with eight each XCD
 // reads its own eighth of the activations and gradients (19.0 us against 23.4 with
 // five and the splits in order, measured with two groups per workgroup).
-constexpr int MAX_SPLITS = 8;
-int grad_splits(int batch) { return std::max(1, std::min(MAX_SPLITS, batch / 32)); }
+// Networks whose tiles fill the chip by themselves take fewer, nine workgroups
+// per CU at most: every split writes all gradients once and the step reads
+// them (2048-4096-2048, 512 rows: 0.69 ms, 1.32 with eight; 8-1024-1100, 256
+// rows, 560 tiles: 91 us with four, 113 with eight, 78 with one, but 2048 rows
+// 219 with four, 229 with one).
+constexpr int MAX_SPLITS = 8, MAX_GRAD_BLOCKS = 9 * 256;
+int grad_splits(const admm_mlp* n, int batch) {
+  const int64_t h = tiles(n->hid, BM);
+  const int64_t blocks = h * (tiles(n->n_out, BM) + h + tiles(n->n_in, 64));
+  int most = MAX_SPLITS;
+  while (most > 1 && most * blocks > MAX_GRAD_BLOCKS) most /= 2;
+  // (not decreasing with the batch: the workspace is that of max_batch)
+  return std::max(1, std::min(most, batch / 32));
+}
 
 // gradients of mean((y - t)^2) into g, or, with lr > 0, the Adam step they
 // give; loss (device scalar) when non-null
@@ -599,7 +611,7 @@ void backward(admm_mlp* n, const float* x, const float* tg, int batch, float* lo
     a.blocks += tiles(M[l], BM) * tiles(N[l], 64);
   }
   a.batch = batch;
-  a.splits = grad_splits(batch);
+  a.splits = grad_splits(n, batch);
   a.ws = n->ws;
   a.n_params = n->n_params;
   a.part = n->part;
@@ -660,7 +672,7 @@ admm_status admm_mlp_create(int32_t n_in, int32_t hidden, int32_t n_out, int32_t
   if ((s = mlp_alloc(n.get(), &n->dh2, B * hidden))) return s;
   if ((s = mlp_alloc(n.get(), &n->part, (int64_t)tiles(max_batch, BM) * tiles(n_out, LN)))) return s;
   if ((s = mlp_alloc(n.get(), &n->mu, n_out))) return s;
-  if ((s = mlp_alloc(n.get(), &n->ws, n->n_params * grad_splits(max_batch)))) return s;
+  if ((s = mlp_alloc(n.get(), &n->ws, n->n_params * grad_splits(n.get(), max_batch)))) return s;
   if ((s = mlp_alloc(n.get(), &n->sd, n_out))) return s;
   fill_kernel<<<(n_out + 255) / 256, 256>>>(n_out, 0.f, n->mu);
   fill_kernel<<<(n_out + 255) / 256, 256>>>(n_out, 1.f, n->sd);

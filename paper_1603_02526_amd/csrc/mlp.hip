@@ -206,7 +206,7 @@ __device__ __forceinline__ void group_product(const Operand& A, int M, const Ope
 //   AFFINE  C = mu + sd C
 //   LOSS    on normalised outputs: with th = (target - mu) / sd per column,
 //           C = 2 (yh - th) scale, and per workgroup the sum of (yh - th)^2
-// One group per tile with all of K (the order of its sums decides how the
+// One group per tile (LN columns: layer_tile, loss_tile) with all of K (the order of its sums decides how the
 // next layer's operands round).  What bounds it: a chunk's memory round trip
 // (the operands are what other XCDs have just written) and the launch; a
 // 64-wide tile, with half as many wavefronts, took 16.2 us for the loss
@@ -215,8 +215,7 @@ __device__ __forceinline__ void group_product(const Operand& A, int M, const Ope
 // (31.9 in three launches).
 enum Epi : int { EPI_RELU = 0, EPI_AFFINE = 1, EPI_LOSS = 2 };
 
-constexpr int LN = 32;
-template <int EPI>
+template <int EPI, int LN>
 __global__ __launch_bounds__(GT) void layer_kernel(int M, int N, int K, Operand A, Operand B,
                                                    const float* __restrict__ bias,
                                                    float* __restrict__ C,
@@ -322,27 +321,42 @@ __device__ __forceinline__ float split_sum(const SplitSmem<BN, KW>& sm, int e) {
 // bounds it: as above.  Batch 2048: K = 1100 and 256 10.9 us on average (17.9
 // with split products in memory and their sum in a second launch; 15.5 with
 // a 64-wide tile, 12.3 with one group).
-constexpr int BW = 32;
-__global__ __launch_bounds__(BSPLIT * GT) void back_kernel(int M, int N, int K, Operand G,
-                                                          Operand W, const float* __restrict__ h,
-                                                          float* __restrict__ D) {
-  __shared__ SplitSmem<BW, BSPLIT> sm;
+template <int BW, int KW>
+__global__ __launch_bounds__(KW * GT) void back_kernel(int M, int N, int K, Operand G,
+                                                       Operand W, const float* __restrict__ h,
+                                                       float* __restrict__ D) {
+  __shared__ SplitSmem<BW, KW> sm;
   const int gm = tiles(M, BM), g = threadIdx.x / GT;
   const int m0 = (int)blockIdx.x % gm * BM, n0 = (int)blockIdx.x / gm * BW;
-  const int ks = k_share(K, BSPLIT), k0 = min(K, g * ks);
+  const int ks = k_share(K, KW), k0 = min(K, g * ks);
   Tile<BW> tile;
   float asum;
   group_product<false, true, false>(G, M, W, N, m0, n0, k0, min(K, k0 + ks), tiles(ks, KC),
                                     sm.g[g], tile, asum);
-  __syncthreads();
-  split_store(sm, tile);
-  __syncthreads();
+  if constexpr (KW == 1) {
 #pragma unroll
-  for (int x = 0; x < BM * BW / (BSPLIT * GT); ++x) {
-    const int e = threadIdx.x + x * BSPLIT * GT, row = m0 + e / BW, col = n0 + e % BW;
-    if (row < M && col < N) {
-      const int64_t at = (int64_t)row * N + col;
-      D[at] = h[at] > 0.f ? split_sum(sm, e) : 0.f;
+    for (int i = 0; i < Tile<BW>::MI; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int row = m0 + Tile<BW>::row(i, q), col = n0 + Tile<BW>::col(j);
+          if (row < M && col < N) {
+            const int64_t at = (int64_t)row * N + col;
+            D[at] = h[at] > 0.f ? tile.acc[i][j][q] : 0.f;
+          }
+        }
+  } else {
+    __syncthreads();
+    split_store(sm, tile);
+    __syncthreads();
+#pragma unroll
+    for (int x = 0; x < BM * BW / (KW * GT); ++x) {
+      const int e = threadIdx.x + x * KW * GT, row = m0 + e / BW, col = n0 + e % BW;
+      if (row < M && col < N) {
+        const int64_t at = (int64_t)row * N + col;
+        D[at] = h[at] > 0.f ? split_sum(sm, e) : 0.f;
+      }
     }
   }
 }
@@ -547,12 +561,38 @@ admm_status mlp_alloc(admm_mlp* n, float** q, int64_t count) {
   return ADMM_OK;
 }
 
+// Columns of a product's tile.  A tile twice as wide reads half as much, a
+// narrow one has twice the workgroups and wavefronts: 64 from four workgroups
+// per CU on (hidden 256, 8192 rows: forward 41.5 us, 44.2 with 32; 1024 hidden,
+// 2048 rows and 512 or 576 tiles: 58.5, 51.9 with 64, but 256 -> 1100 outputs at
+// as many 68.6, with 32 66.2 per step).
+int layer_tile(int M, int N) { return (int64_t)tiles(M, BM) * tiles(N, 64) >= 1024 ? 64 : 32; }
+
+// The loss epilogue holds the targets as well, so that its wider tile pays by
+// the product's size (a step at 1024 -> 1100 with 16,384 rows 1.22 ms, 1.35 with
+// 32; at 256 -> 1100 0.271 and 0.264).
+int loss_tile(int M, int N, int K) {
+  return (int64_t)tiles(M, BM) * tiles(N, 64) * K >= 1 << 21 ? layer_tile(M, N) : 32;
+}
+
 template <int EPI>
 void layer(int M, int N, int K, const float* A, const float* B, const float* bias, float* C,
            hipStream_t st, const float* mu = nullptr, const float* sd = nullptr,
            const float* target = nullptr, float scale = 0.f, float* part = nullptr) {
-  layer_kernel<EPI><<<tiles(M, BM) * tiles(N, LN), GT, 0, st>>>(
+  const int ln = EPI == EPI_LOSS ? loss_tile(M, N, K) : layer_tile(M, N);
+  (ln == 64 ? layer_kernel<EPI, 64> : layer_kernel<EPI, 32>)<<<tiles(M, BM) * tiles(N, ln), GT, 0, st>>>(
       M, N, K, operand(A, K), operand(B, K), bias, C, mu, sd, target, scale, part);
+}
+
+// Gradients through a layer, as wide a tile as its forward pass.
+void back(int M, int N, int K, const float* G, const float* W, const float* h, float* D,
+          hipStream_t st) {
+  const Operand g = operand(G, K), w = operand(W, N);
+  const int gm = tiles(M, BM);
+  if (layer_tile(M, N) == 64)
+    back_kernel<64, 1><<<gm * tiles(N, 64), GT, 0, st>>>(M, N, K, g, w, h, D);
+  else
+    back_kernel<32, BSPLIT><<<gm * tiles(N, 32), BSPLIT * GT, 0, st>>>(M, N, K, g, w, h, D);
 }
 
 // h1 = relu(x W1^T + b1), h2 = relu(h1 W2^T + b2)
@@ -595,11 +635,8 @@ void backward(admm_mlp* n, const float* x, const float* tg, int batch, float* lo
   const float scale = 1.f / (float)((int64_t)batch * n->n_out);
   layer<EPI_LOSS>(batch, n->n_out, n->hid, n->h2, n->p + n->oW3, n->p + n->ob3, n->dy, st, n->mu,
                   n->sd, tg, scale, n->part);
-  const int gh = tiles(batch, BM) * tiles(n->hid, BW);
-  back_kernel<<<gh, BSPLIT * GT, 0, st>>>(batch, n->hid, n->n_out, operand(n->dy, n->n_out),
-                                          operand(n->p + n->oW3, n->hid), n->h2, n->dh2);
-  back_kernel<<<gh, BSPLIT * GT, 0, st>>>(batch, n->hid, n->hid, operand(n->dh2, n->hid),
-                                          operand(n->p + n->oW2, n->hid), n->h1, n->dh1);
+  back(batch, n->hid, n->n_out, n->dy, n->p + n->oW3, n->h2, n->dh2, st);
+  back(batch, n->hid, n->hid, n->dh2, n->p + n->oW2, n->h1, n->dh1, st);
   GradArgs a{};
   const float* G[3] = {n->dy, n->dh2, n->dh1};
   const float* H[3] = {n->h2, n->h1, x};
@@ -615,7 +652,7 @@ void backward(admm_mlp* n, const float* x, const float* tg, int batch, float* lo
   a.ws = n->ws;
   a.n_params = n->n_params;
   a.part = n->part;
-  a.n_part = (int64_t)tiles(batch, BM) * tiles(n->n_out, LN);
+  a.n_part = (int64_t)tiles(batch, BM) * tiles(n->n_out, loss_tile(batch, n->n_out, n->hid));
   a.scale = scale;
   a.loss = loss;
   grad_kernel<<<a.blocks * a.splits + (loss ? 1 : 0), GT, 0, st>>>(a);
@@ -670,7 +707,7 @@ admm_status admm_mlp_create(int32_t n_in, int32_t hidden, int32_t n_out, int32_t
   if ((s = mlp_alloc(n.get(), &n->dy, B * n_out))) return s;
   if ((s = mlp_alloc(n.get(), &n->dh1, B * hidden))) return s;
   if ((s = mlp_alloc(n.get(), &n->dh2, B * hidden))) return s;
-  if ((s = mlp_alloc(n.get(), &n->part, (int64_t)tiles(max_batch, BM) * tiles(n_out, LN)))) return s;
+  if ((s = mlp_alloc(n.get(), &n->part, (int64_t)tiles(max_batch, BM) * tiles(n_out, 32)))) return s;
   if ((s = mlp_alloc(n.get(), &n->mu, n_out))) return s;
   if ((s = mlp_alloc(n.get(), &n->ws, n->n_params * grad_splits(n.get(), max_batch)))) return s;
   if ((s = mlp_alloc(n.get(), &n->sd, n_out))) return s;

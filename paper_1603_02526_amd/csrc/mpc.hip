@@ -145,9 +145,9 @@ __device__ __forceinline__ f4v row_transpose(f4v v) {
 // SIMD), and with one wavefront per SIMD the chain of one iteration (three
 // products, 48 cycles to a result, a transpose each, and the barrier).
 // Latency of one iteration, one instance alone, against one lane per time
-// step with the matrices read from LDS: T = 64, n = 8: 0.74 us (1.73);
-// T = 100, n = 8: 0.95 (2.15); T = 200, n = 12: 1.93 (3.33).  The uneven
-// batch of 4096: 6.9 ms (12.4).
+// step with the matrices read from LDS: T = 64, n = 8: 0.66 us (1.71);
+// T = 100, n = 8: 0.89 (2.04); T = 200, n = 12: 1.85 (3.29).  The uneven
+// batch of 4096: 6.9 ms (12.2).
 template <int WV>
 struct LockBuf {
   f4v first[2][WV + 1][4];   // mA of each wavefront's first step (last entry: zeros)
@@ -264,7 +264,10 @@ __device__ __forceinline__ int solve_tiles(const SolveArgs& a, const MpcInst& I,
   for (int j = 0; j < TPW; ++j) xa[j] = xb[j] = xq[j] = sB[j] = sA[j] = zo[j] = zero4;
   // |x - z| and |z - z(prev)|, the averages' products rounded with the
   // differences.  Maxima drop a NaN operand: a NaN in a new z makes chk
-  // NaN, and the rule is then not met.
+  // NaN, and the rule is then not met.  The primal residual only where z has
+  // settled (uniform): until shortly before the end some 24 instructions fewer
+  // per tile (16,384 instances of T = 64, n = 8 from predictions: 1.76 ms, 1.89
+  // with both).
   auto met = [&]() {
     float rmax = 0.f, rbmax = 0.f, smax = 0.f, chk = 0.f;
 #pragma unroll
@@ -272,14 +275,19 @@ __device__ __forceinline__ int solve_tiles(const SolveArgs& a, const MpcInst& I,
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         smax = fmaxf(smax, fabsf(fmaf(cz[j], sB[j][q], -zo[j][q])));
+        chk += s.zB[j][q];
+      }
+    if (__builtin_amdgcn_ballot_w64(!((smax * a.rho <= a.tol) & (chk == chk))) != 0) return false;
+#pragma unroll
+    for (int j = 0; j < TPW; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
         rmax = fmaxf(rmax, fmaxf(fabsf(fmaf(-cA[j], sA[j][q], xa[j][q])),
                                  fabsf(fmaf(-cz[j], sB[j][q], xq[j][q]))));
         rbmax = fmaxf(rbmax, fabsf(fmaf(-cz[j], sB[j][q], xb[j][q])));
-        chk += s.zB[j][q];
       }
     rmax = fmaxf(rmax, nobox ? 0.f : rbmax);
-    return __builtin_amdgcn_ballot_w64(!((rmax <= a.tol) & (smax * a.rho <= a.tol) &
-                                         (chk == chk))) == 0;
+    return __builtin_amdgcn_ballot_w64(!(rmax <= a.tol)) == 0;
   };
   int it = 1;
   bool stop;
@@ -740,7 +748,7 @@ admm_status mpc_alloc(admm_mpc_batch* b, void** p, size_t bytes) {
 // their own; shorter ones take one wavefront each, pack1 to every four
 // wavefronts of a workgroup, but no more than it takes to give every CU a
 // workgroup (a lone wavefront has a SIMD to itself).  One instance per
-// workgroup and more than one tile: in lockstep (0.75 against 1.0 us per
+// workgroup and more than one tile: in lockstep (a quarter less time per
 // iteration at T = 20).  Items are ordered by the plan's order key.
 admm_status build_items(admm_mpc_batch* b, const Plan& pl) {
   std::vector<int32_t> ids(b->n_inst);
@@ -751,8 +759,8 @@ admm_status build_items(admm_mpc_batch* b, const Plan& pl) {
   };
   // expected duration of a solve: measured iterations x the latency of one
   // iteration, which grows with the products' size and with the wavefronts
-  // per SIMD (fitted to single-instance timings: 0.74 us at T = 64, n = 8,
-  // 1.24 at T = 114, n = 9, 1.93 at T = 200, n = 12)
+  // per SIMD (fitted to single-instance timings: 0.66 us at T = 64, n = 8,
+  // 1.02 at T = 100, n = 12, 1.85 at T = 200, n = 12)
   auto duration = [&](int i) {
     const MpcInst& I = b->h_inst[i];
     const double gx = (I.n + 3) / 4, wps = (I.T + 63) / 64;

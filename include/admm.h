@@ -369,14 +369,16 @@ admm_status admm_mpc_batch_shift(admm_mpc_batch* b, const float* x0, const float
  * T <= 32 share workgroups, one wavefront each (1: one per workgroup, 2 or
  * 4: up to that many per four wavefronts, as far as there are more of them
  * than compute units); longer instances take a workgroup each, one
- * wavefront per sixteen steps;
+ * wavefront per sixteen steps.  Batches that fill the device with equal work
+ * run with one lane per time step, where pack1 = instances of T <= 64 per
+ * workgroup (at most 2 where all have T <= 128);
  * order (0 as given, 1 most work per iteration first,
  * 2 grouped by (n, m), 3 longest expected solve first: the iteration counts
  * of the autotuner's cold solve times the latency of one iteration; as 1
  * before a tuning run), grid = workgroups (0: as many as fit on the device
  * at once).  A batch finishes with its slowest instance, so starting the
  * longest solves first shortens it.  Results do not depend on the plan
- * (bitwise). */
+ * (bitwise).  resident: how many workgroups of a cold solve fit at once. */
 admm_status admm_mpc_batch_set_plan(admm_mpc_batch* b, int32_t pack1, int32_t order,
                                     int32_t grid);
 admm_status admm_mpc_batch_get_plan(const admm_mpc_batch* b, int32_t* pack1,

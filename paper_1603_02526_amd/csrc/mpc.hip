@@ -9,12 +9,15 @@
 // average.  alpha = 1, so the per-edge state is m alone (u = m - z).
 //
 // Mapping to gfx950: sixteen time steps are the columns of an f32 MFMA tile
-// and the projection's products run on the matrix cores (solve_one).
+// and the projection's products run on the matrix cores (solve_tiles).
 // Instances with T <= 32 run one per wavefront and share workgroups;
 // longer ones on the wavefronts of a workgroup in lockstep, one tile each.
-// All of an instance's per-edge state, its z and the
-// matrices stay in registers for the whole solve; neighbouring time steps
-// exchange z and m by lane shifts, and through LDS between wavefronts.
+// An instance's per-edge state, its z and the matrices stay in registers for
+// the whole solve, but for what four wavefronts per SIMD leave no room for: up
+// to 30 registers per lane are spilled to scratch, most of them outside the
+// iteration.  Neighbouring time steps exchange z and m by lane shifts, and
+// through LDS between wavefronts.  Batches that keep the chip busy with equal
+// instances run with one lane per time step instead (lane_solve).
 // Workgroups take work items from a queue until it is empty.  Each instance
 // stops at the first iteration with
 //   r = max_e |x_e - z_b| <= tol  and  s = rho max_b |z_b - z_b(prev)| <= tol.
@@ -83,7 +86,7 @@ struct SolveArgs {
   float* zout;
   float* uout;          // nullable: final per-edge duals
   int32_t* iters;
-  const int32_t* items; // [n_items][MAXW + 1]: mode, instances (-1 = none)
+  const int32_t* items; // [n_items][MAXW + 1] or [n_items][LANE_ITEM]
   int32_t n_items;
   int32_t* counter;     // work queue, zero at the launch; null: one workgroup per item
   float tol;
@@ -506,6 +509,429 @@ mpc_solve_kernel(SolveArgs a) {
   }
 }
 
+// The same solve with one lane per time step: a wavefront holds 64 steps, and
+// the products' matrices are read from an LDS copy of the parameter block
+// with uniform addresses.  Every product is the same chain of fmaf in k order
+// as the tiles', so the results have the same bits.  What bounds it: the
+// issue of some 700 vector instructions (n = 8) per 64 steps, where four tiles
+// take as many again for their idle lane rows and transposes, and one
+// iteration's latency, a chain of them all: 1.71 us at T = 64, n = 8 against
+// 0.66.  So it is the form of batches that keep every SIMD busy with equal
+// work (use_lanes).  Per iteration and 1024 instances, lanes against tiles:
+// T = 64, n = 4 0.67 us, 1.16; n = 8 1.17, 1.41; n = 12 1.78, 1.59; T = 100, n = 8
+// 2.49, 2.92; T = 256, n = 8 5.52, 6.74; T = 32, n = 8 1.06, 0.74.
+//
+template <bool LOCK>
+__device__ __forceinline__ void isync() {
+  if constexpr (LOCK) {
+    __syncthreads();
+  } else {
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+  }
+}
+
+
+// Whole-wavefront shifts by one lane (DPP wave_shr:1 / wave_shl:1): lane t
+// receives lane t-1's (resp. t+1's) value; lane 0 (resp. 63) receives 0.
+// Every lane of the wavefront must be active.
+__device__ __forceinline__ float lane_prev(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float lane_next(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xF, 0xF, false));
+}
+
+// out[i] += sum_c P[i*C + c] x[c] for i < R, P in LDS with 16-byte aligned
+// rows of C floats (C % 4 == 0), terms added in c order.  Row i+1 is read
+// while row i is summed; the scheduling barrier per row keeps the compiler
+// from reading every row ahead (the whole block would not fit in registers).
+template <int R, int C>
+__device__ __forceinline__ void mv_rows(const float* P, const float (&x)[C], float (&out)[R]) {
+  f4v cur[C / 4], nxt[C / 4];
+#pragma unroll
+  for (int q = 0; q < C / 4; ++q) cur[q] = ((const f4v*)P)[q];
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+    if (i + 1 < R) {
+#pragma unroll
+      for (int q = 0; q < C / 4; ++q) nxt[q] = ((const f4v*)(P + (i + 1) * C))[q];
+    }
+    float s = out[i];
+#pragma unroll
+    for (int q = 0; q < C / 4; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s = fmaf(cur[q][e], x[4 * q + e], s);
+    out[i] = s;
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int q = 0; q < C / 4; ++q) cur[q] = nxt[q];
+  }
+}
+
+// One instance.  LOCK: all wavefronts of the workgroup work on it in
+// lockstep (t = threadIdx.x); otherwise this wavefront alone (t = lane).
+// xb: first exchange slot of this instance.  red: per-wavefront residuals.
+// ps: its parameter slot.  N: padded state dimension; inputs are padded to MM.
+template <bool LOCK, int N>
+__device__ __forceinline__ void lane_solve(const SolveArgs& a, int id, int t, int xb, float* xz,
+                                          float* xm, float* red, float* ps) {
+  constexpr ParOff o = par_offsets(N);
+  const MpcInst I = a.inst[id];
+  const int T = __builtin_amdgcn_readfirstlane(I.T);
+  const int n = __builtin_amdgcn_readfirstlane(I.n);
+  const int m = __builtin_amdgcn_readfirstlane(I.m);
+  const int k = n + m;  // unpadded step width of z and of the u layout / 3
+  const bool box = __builtin_amdgcn_readfirstlane(I.box) != 0;
+  const bool act = t < T;
+  // Stage the parameter block in this instance's LDS slot.
+  {
+    const float* __restrict__ Pg = a.par + __builtin_amdgcn_readfirstlane(I.par_off);
+    const int nthr = LOCK ? (int)blockDim.x : 64;
+    const int tid = LOCK ? (int)threadIdx.x : (int)(threadIdx.x & 63);
+    for (int q = tid; q < o.size; q += nthr) ps[q] = Pg[q];
+  }
+  isync<LOCK>();
+  const float* Pb = ps;
+  const float lo = Pb[o.lo], hi = Pb[o.lo + 1];
+
+  float zu[MM], zx1[N];
+  float mdx[N], mdu[MM], mdx1[N], mqu[MM], mbx[MM], mqx[N];
+  float cvec[N];  // c = A x0, used by time step 0 only
+#pragma unroll
+  for (int i = 0; i < N; ++i) cvec[i] = 0.f;
+#pragma unroll
+  for (int i = 0; i < N; ++i) { zx1[i] = 0.f; mdx[i] = 0.f; mdx1[i] = 0.f; mqx[i] = 0.f; }
+#pragma unroll
+  for (int j = 0; j < MM; ++j) { zu[j] = 0.f; mdu[j] = 0.f; mqu[j] = 0.f; mbx[j] = 0.f; }
+
+  if (act && a.zinit) {
+    const float* zi = a.zinit + I.z_off + (int64_t)t * k;
+#pragma unroll
+    for (int j = 0; j < MM; ++j) if (j < m) zu[j] = zi[j];
+#pragma unroll
+    for (int i = 0; i < N; ++i) if (i < n) zx1[i] = zi[m + i];
+  }
+  // z of x_t, the previous step's x_{t+1} (0 at t = 0).  One wavefront per
+  // instance exchanges neighbours by lane shifts; lockstep wavefronts
+  // through LDS.  The same value is carried across iterations in zxpc.
+  float zxpc[N];
+  if constexpr (LOCK) {
+    if (act) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) xz[(xb + t) * MN + i] = zx1[i];
+    }
+    isync<LOCK>();
+#pragma unroll
+    for (int i = 0; i < N; ++i) zxpc[i] = (act && t >= 1) ? xz[(xb + t - 1) * MN + i] : 0.f;
+  } else {
+#pragma unroll
+    for (int i = 0; i < N; ++i) zxpc[i] = lane_prev(zx1[i]);
+  }
+  if (act) {
+    float zxp[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) zxp[i] = zxpc[i];
+    // m = u + z per edge; u per step laid out [dx n | du m | dx1 n | qu m | bx m | qx n]
+    if (a.uinit) {
+      const float* ui = a.uinit + I.u_off + (int64_t)t * 3 * k;
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        if (i < n) {
+          mdx[i] = ui[i];
+          mdx1[i] = ui[n + m + i];
+          mqx[i] = ui[2 * n + 3 * m + i];
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < MM; ++j) {
+        if (j < m) {
+          mdu[j] = ui[n + j];
+          mqu[j] = ui[2 * n + m + j];
+          mbx[j] = ui[2 * n + 2 * m + j];
+        }
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      mdx[i] += zxp[i];
+      mdx1[i] += zx1[i];
+      mqx[i] += zx1[i];
+    }
+  }
+  if (act) {
+#pragma unroll
+    for (int j = 0; j < MM; ++j) {
+      mdu[j] += zu[j];
+      mqu[j] += zu[j];
+      mbx[j] += zu[j];
+    }
+    if (t == 0) {
+      const float* x0 = a.x0 + I.x0_off;
+      float xv[N];
+#pragma unroll
+      for (int j = 0; j < N; ++j) xv[j] = (j < n) ? x0[j] : 0.f;
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        float s = 0.f;
+#pragma unroll
+        for (int j = 0; j < N; ++j) s += Pb[o.A + i * N + j] * xv[j];
+        cvec[i] = s;
+      }
+    }
+  }
+
+  int done_it = -1;
+  const int nw = LOCK ? (T + 63) / 64 : 1;
+  const int w = threadIdx.x >> 6;
+  for (int it = 1; it <= a.max_iter; ++it) {
+    float ax[N], au[MM], bv[N], xqu[MM], xbx[MM], xqx[N];
+    float rloc = 0.f, sloc = 0.f;
+    // The parameter block is re-read from LDS every iteration: an opaque
+    // zero offset keeps the compiler from hoisting several hundred
+    // loop-invariant matrix entries into registers.
+    int zoff;
+    asm volatile("s_mov_b32 %0, 0" : "=s"(zoff));
+    const float* P = Pb + zoff;
+    float zxp[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) zxp[i] = zxpc[i];
+    if (act) {
+      // ---- x-update.  n = z - u = 2z - m on every edge.
+#pragma unroll
+      for (int i = 0; i < N; ++i) ax[i] = (t >= 1) ? (2.f * zxp[i] - mdx[i]) : 0.f;
+#pragma unroll
+      for (int j = 0; j < MM; ++j) au[j] = 2.f * zu[j] - mdu[j];
+#pragma unroll
+      for (int i = 0; i < N; ++i) bv[i] = 2.f * zx1[i] - mdx1[i];
+      // dynamics: w = M a + c - b; v = S w (S0 at t = 0); a -= M^T v; b += v
+      constexpr int N4 = o.N4, K4 = o.K4;
+      float xa[K4], wv[N], wp[N4], vv[N], vp[N4], sx[N], su[MM];
+#pragma unroll
+      for (int c = 0; c < K4; ++c) xa[c] = c < N ? ax[c < N ? c : 0] : (c >= N4 ? au[c >= N4 ? c - N4 : 0] : 0.f);
+#pragma unroll
+      for (int i = 0; i < N; ++i) wv[i] = cvec[i] - bv[i];
+      mv_rows<N, K4>(P + o.M, xa, wv);
+#pragma unroll
+      for (int c = 0; c < N4; ++c) wp[c] = c < N ? wv[c < N ? c : 0] : 0.f;
+#pragma unroll
+      for (int i = 0; i < N; ++i) vv[i] = 0.f;
+      mv_rows<N, N4>(P + ((t >= 1) ? o.S : o.S0), wp, vv);
+#pragma unroll
+      for (int c = 0; c < N4; ++c) vp[c] = c < N ? vv[c < N ? c : 0] : 0.f;
+#pragma unroll
+      for (int i = 0; i < N; ++i) sx[i] = 0.f;
+#pragma unroll
+      for (int j = 0; j < MM; ++j) su[j] = 0.f;
+      mv_rows<N, N4>(P + o.MT, vp, sx);
+      mv_rows<MM, N4>(P + o.MT + N4 * N4, vp, su);
+#pragma unroll
+      for (int j = 0; j < N; ++j) ax[j] -= sx[j];
+#pragma unroll
+      for (int j = 0; j < MM; ++j) au[j] -= su[j];
+#pragma unroll
+      for (int i = 0; i < N; ++i) bv[i] += vv[i];
+      // separable costs and the box
+#pragma unroll
+      for (int j = 0; j < MM; ++j) {
+        xqu[j] = P[o.cr + j] * (2.f * zu[j] - mqu[j]);
+        const float nb = 2.f * zu[j] - mbx[j];
+        xbx[j] = nb < lo ? lo : (nb > hi ? hi : nb);
+      }
+#pragma unroll
+      for (int i = 0; i < N; ++i) xqx[i] = P[o.cq + i] * (2.f * zx1[i] - mqx[i]);
+      // ---- m-update: m = x + u, u = m_old - z_old
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        mdx[i] = ax[i] + (mdx[i] - zxp[i]);
+        mdx1[i] = bv[i] + (mdx1[i] - zx1[i]);
+        mqx[i] = xqx[i] + (mqx[i] - zx1[i]);
+      }
+#pragma unroll
+      for (int j = 0; j < MM; ++j) {
+        mdu[j] = au[j] + (mdu[j] - zu[j]);
+        mqu[j] = xqu[j] + (mqu[j] - zu[j]);
+        mbx[j] = xbx[j] + (mbx[j] - zu[j]);
+      }
+    }
+    // From step t+1 (lane t+1): the m and the x of its dynamics edge on
+    // x_{t+1}.  Lane shifts inside a wavefront; in lockstep mode lane 63
+    // takes them from the next wavefront's lane 0 through LDS.
+    float xmn[N], axn[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      xmn[i] = lane_next(mdx[i]);
+      axn[i] = lane_next(ax[i]);
+    }
+    if constexpr (LOCK) {
+      if ((t & 63) == 0) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+          xm[w * 2 * MN + i] = mdx[i];
+          xm[w * 2 * MN + MN + i] = ax[i];
+        }
+      }
+      __syncthreads();
+      if ((t & 63) == 63 && w + 1 < nw) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+          xmn[i] = xm[(w + 1) * 2 * MN + i];
+          axn[i] = xm[(w + 1) * 2 * MN + MN + i];
+        }
+      }
+    }
+    float zx1n[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) zx1n[i] = 0.f;
+    // residual maxima use v_max (which drops NaN): a NaN in this step's new
+    // z makes chk NaN, and the step then reports an infinite residual
+    float chk = 0.f;
+    if (act) {
+      // ---- z-update: 3-term averages (x_T and box-free inputs: 2 terms).
+      // The residual of step t+1's dynamics edge on x_{t+1} is taken here,
+      // where the new z of x_{t+1} is.
+      const bool nxt = (t + 1 < T);
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        float s = mdx1[i] + mqx[i];
+        if (nxt) s += xmn[i];
+        const float zn = s * (nxt ? (1.f / 3.f) : 0.5f);
+        sloc = fmaxf(sloc, fabsf(zn - zx1[i]));
+        rloc = fmaxf(rloc, fmaxf(fabsf(bv[i] - zn), fabsf(xqx[i] - zn)));
+        if (nxt) rloc = fmaxf(rloc, fabsf(axn[i] - zn));
+        zx1n[i] = zn;
+        chk += zn;
+      }
+#pragma unroll
+      for (int j = 0; j < MM; ++j) {
+        const float s = box ? (mdu[j] + mqu[j] + mbx[j]) : (mdu[j] + mqu[j]);
+        const float zn = s * (box ? (1.f / 3.f) : 0.5f);
+        sloc = fmaxf(sloc, fabsf(zn - zu[j]));
+        float r = fmaxf(fabsf(au[j] - zn), fabsf(xqu[j] - zn));
+        if (box) r = fmaxf(r, fabsf(xbx[j] - zn));
+        rloc = fmaxf(rloc, r);
+        chk += zn;
+        zu[j] = zn;
+      }
+#pragma unroll
+      for (int i = 0; i < N; ++i) zx1[i] = zx1n[i];
+    }
+    // next iteration's z of x_t: the new z of step t-1 (lane t-1); in
+    // lockstep mode lane 0 takes it from the previous wavefront's lane 63
+    // through LDS, across the barrier of the stopping-rule reduction
+#pragma unroll
+    for (int i = 0; i < N; ++i) zxpc[i] = lane_prev(zx1n[i]);
+    if constexpr (LOCK) {
+      if ((t & 63) == 63) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) xz[w * MN + i] = zx1n[i];
+      }
+    }
+    if (!(chk == chk)) rloc = __builtin_inff();
+    // ---- stopping rule, reduced over the instance
+    float r = admmi::wave_max_nonneg(rloc), s = admmi::wave_max_nonneg(sloc);
+    if constexpr (LOCK) {
+      if ((threadIdx.x & 63) == 0) { red[2 * w] = r; red[2 * w + 1] = s; }
+      __syncthreads();
+      r = red[0];
+      s = red[1];
+      for (int q = 1; q < nw; ++q) { r = fmaxf(r, red[2 * q]); s = fmaxf(s, red[2 * q + 1]); }
+      if ((t & 63) == 0 && w >= 1) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) zxpc[i] = xz[(w - 1) * MN + i];
+      }
+    }
+    s *= a.rho;
+    if (r <= a.tol && s <= a.tol) {
+      done_it = it;
+      break;
+    }
+  }
+  if (act) {
+    float* zo = a.zout + I.z_off + (int64_t)t * k;
+#pragma unroll
+    for (int j = 0; j < MM; ++j) if (j < m) zo[j] = zu[j];
+#pragma unroll
+    for (int i = 0; i < N; ++i) if (i < n) zo[m + i] = zx1[i];
+    if (a.uout) {
+      // u = m - z with the final z (the state the next solve continues from);
+      // zxpc already holds the final z of x_t
+      float* uo = a.uout + I.u_off + (int64_t)t * 3 * k;
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        if (i < n) {
+          uo[i] = t >= 1 ? mdx[i] - zxpc[i] : 0.f;
+          uo[n + m + i] = mdx1[i] - zx1[i];
+          uo[2 * n + 3 * m + i] = mqx[i] - zx1[i];
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < MM; ++j) {
+        if (j < m) {
+          uo[n + j] = mdu[j] - zu[j];
+          uo[2 * n + m + j] = mqu[j] - zu[j];
+          uo[2 * n + 2 * m + j] = mbx[j] - zu[j];
+        }
+      }
+    }
+  }
+  if (t == 0) a.iters[id] = done_it > 0 ? done_it : -a.max_iter;
+}
+
+template <bool LOCK>
+__device__ __forceinline__ void lane_dispatch(const SolveArgs& a, int id, int t, int xb, float* xz,
+                                               float* xm, float* red, float* ps) {
+  const int N = pad_n(__builtin_amdgcn_readfirstlane(a.inst[id].n));
+  switch (N) {
+    case 4: lane_solve<LOCK, 4>(a, id, t, xb, xz, xm, red, ps); break;
+    case 5: lane_solve<LOCK, 5>(a, id, t, xb, xz, xm, red, ps); break;
+    case 6: lane_solve<LOCK, 6>(a, id, t, xb, xz, xm, red, ps); break;
+    case 7: lane_solve<LOCK, 7>(a, id, t, xb, xz, xm, red, ps); break;
+    case 8: lane_solve<LOCK, 8>(a, id, t, xb, xz, xm, red, ps); break;
+    case 9: lane_solve<LOCK, 9>(a, id, t, xb, xz, xm, red, ps); break;
+    case 10: lane_solve<LOCK, 10>(a, id, t, xb, xz, xm, red, ps); break;
+    case 11: lane_solve<LOCK, 11>(a, id, t, xb, xz, xm, red, ps); break;
+    default: lane_solve<LOCK, 12>(a, id, t, xb, xz, xm, red, ps); break;
+  }
+}
+
+// WG threads per workgroup: WG / 64 one-wavefront instances, or one instance
+// of up to WG / 64 lockstep wavefronts, per work item (LANE_ITEM numbers: the
+// wavefronts per instance, 1 or more, and the instances, -1 = none).  128
+// threads where no horizon passes 128.  The register budget is held at two
+// waves per SIMD for both sizes.
+constexpr int LANE_WG = 256, LANE_WGS = 128, LANE_ITEM = 5;
+constexpr int PBLK = par_offsets(MN).size + MN;   // parameter slot (floats)
+static_assert(PBLK % 4 == 0, "parameter slots must stay 16-byte aligned");
+
+template <int WG>
+__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2, 2))) void
+mpc_lane_kernel(SolveArgs a) {
+  __shared__ float xz[WG * MN];
+  __shared__ float xm[WG * MN];
+  __shared__ float red[8];
+  __shared__ __align__(16) float ps[(WG / 64) * PBLK];   // rows read as 16-byte vectors
+  __shared__ int s_item;
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  for (;;) {
+    if (threadIdx.x == 0) s_item = a.counter ? atomicAdd(a.counter, 1) : (int)blockIdx.x;
+    __syncthreads();
+    const int item = __builtin_amdgcn_readfirstlane(s_item);
+    __syncthreads();
+    if (item >= a.n_items) break;
+    const int32_t* it = a.items + (int64_t)LANE_ITEM * item;
+    if (__builtin_amdgcn_readfirstlane(it[0]) == 1) {
+      const int id = __builtin_amdgcn_readfirstlane(it[1 + w]);
+      if (id >= 0) lane_dispatch<false>(a, id, lane, w * 64, xz, xm, red, ps + w * PBLK);
+    } else {
+      lane_dispatch<true>(a, __builtin_amdgcn_readfirstlane(it[1]), threadIdx.x, 0, xz, xm, red, ps);
+    }
+    if (!a.counter) break;
+    __syncthreads();
+  }
+}
+
 __global__ void reset_queue_kernel(int32_t* counter) {
   if (threadIdx.x == 0) *counter = 0;
 }
@@ -701,10 +1127,20 @@ std::vector<double> inv_spd(std::vector<double> a, int n) {
 }
 
 struct Plan {
-  int pack1 = 4;  // instances of T <= T1 per four wavefronts (1: per workgroup)
+  int pack1 = 4;  // tiles: instances of T <= T1 per four wavefronts (1: per workgroup);
+                  // lanes: instances of T <= 64 per workgroup
   int order = 1;  // 0 as given, 1 longest first, 2 by (n, m) then longest first,
                   // 3 longest measured solve first (iterations of the last tuning solve)
   int grid = 0;   // persistent workgroups; 0: resident capacity
+};
+
+// One form of the solver for a batch: its launch and its work items.
+struct Form {
+  int threads = 0;           // per workgroup
+  int resident = 0;          // workgroups resident per device at full occupancy
+  int32_t* d_items = nullptr;
+  int32_t n_items = 0;
+  double work = 0, latency = 0;   // per iteration, us: SIMD time of all instances, longest instance alone
 };
 
 }  // namespace
@@ -718,12 +1154,10 @@ struct admm_mpc_batch {
   MpcInst* d_inst = nullptr;
   float* d_par = nullptr;
   float* d_u = nullptr;       // dual-completion output
-  int32_t* d_items = nullptr;
-  int32_t n_items = 0;
+  Form tiles, lanes;
   int32_t* d_counter = nullptr;
   Plan plan;
-  int resident = 0;          // workgroups resident per device at full occupancy
-  int wv = MAXW;             // wavefronts per workgroup: the longest horizon's tiles, at least 4
+  int wv = MAXW;             // wavefronts per workgroup of tiles: the longest horizon's, at least 4
   int cus = 1;
   int zrow = 0;              // most z entries of one instance
   std::vector<int32_t> measured;  // iterations per instance from the last tuning solve
@@ -780,37 +1214,85 @@ admm_status build_items(admm_mpc_batch* b, const Plan& pl) {
       return X.T > Y.T;
     });
   }
+  // Items of `width` numbers: up to `pack` instances of at most short_t steps
+  // (first number `mode`), or one longer instance (first number mode + 1).
   std::vector<int32_t> items;
-  std::vector<int32_t> pend;
-  auto flush = [&]() {
-    if (pend.empty()) return;
-    items.push_back(0);
-    for (int q = 0; q < MAXW; ++q) items.push_back(q < (int)pend.size() ? pend[q] : -1);
-    pend.clear();
+  auto fill = [&](Form& f, int width, int mode, int pack, int short_t) -> admm_status {
+    items.clear();
+    std::vector<int32_t> pend;
+    auto flush = [&]() {
+      if (pend.empty()) return;
+      items.push_back(mode);
+      for (int q = 0; q < width - 1; ++q) items.push_back(q < (int)pend.size() ? pend[q] : -1);
+      pend.clear();
+    };
+    for (int32_t i : ids) {
+      if (b->h_inst[i].T <= short_t) {
+        pend.push_back(i);
+        if ((int)pend.size() == pack) flush();
+      } else {
+        items.push_back(mode + 1);
+        items.push_back(i);
+        for (int q = 2; q < width; ++q) items.push_back(-1);
+      }
+    }
+    flush();
+    f.n_items = (int32_t)(items.size() / width);
+    ADMM_HIP(hipMemcpy(f.d_items, items.data(), items.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+    return ADMM_OK;
   };
   int n_short = 0;
   for (const MpcInst& I : b->h_inst) n_short += I.T <= T1;
   const int share = pl.pack1 == 1 ? 1 : pl.pack1 * b->wv / 4;
   const int pack = std::max(1, std::min(share, (n_short + b->cus - 1) / b->cus));
-  for (int32_t i : ids) {
-    if (b->h_inst[i].T <= (pack > 1 ? T1 : 16)) {
-      pend.push_back(i);
-      if ((int)pend.size() == pack) flush();
-    } else {
-      items.push_back(1);
-      items.push_back(i);
-      for (int q = 1; q < MAXW; ++q) items.push_back(-1);
-    }
-  }
-  flush();
-  b->n_items = (int32_t)(items.size() / (MAXW + 1));
-  ADMM_HIP(hipMemcpy(b->d_items, items.data(), items.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+  if (admm_status s = fill(b->tiles, MAXW + 1, 0, pack, pack > 1 ? T1 : 16)) return s;
+  if (admm_status s = fill(b->lanes, LANE_ITEM, 1, std::min(pl.pack1, b->lanes.threads / 64), 64)) return s;
   b->plan = pl;
   return ADMM_OK;
 }
 
-auto solve_kernel(int wv) {
-  return wv == 4 ? mpc_solve_kernel<4> : wv == 8 ? mpc_solve_kernel<8> : mpc_solve_kernel<MAXW>;
+// What an iteration takes in either form, fitted to even batches of T = 10 to
+// 256 and n = 2 to 12 that run a given number of iterations (within some 15%):
+// the SIMD time of all instances, and the longest instance alone.  Tiles: the
+// issue of an instance's tiles on the four SIMDs, but no less than its latency
+// for the wavefronts that its workgroup (the batch's longest horizon) takes.
+void estimate(admm_mpc_batch* b) {
+  for (const MpcInst& I : b->h_inst) {
+    const int t = (I.T + 15) / 16, t4 = (t + 3) / 4 * 4, g = (I.T + 63) / 64, gx = (I.n + 3) / 4;
+    const double N = pad_n(I.n), wide = I.n > 8 ? 1.0 : 0.0;
+    const double tile = 0.235 + 0.055 * gx;
+    const double tl = ((t == 1 ? 0.40 : 0.54) + 0.065 * gx) * (g == 1 ? 1.0 : 0.4 + 0.5 * g);
+    b->tiles.latency = std::max(b->tiles.latency, tl);
+    b->tiles.work += I.T <= T1 ? 1.15 * tile * t
+                               : std::max(tile * (b->wv == 4 ? 1.0 : 1.1) * 0.5 * (t + t4), tl * b->wv / 4);
+    const double lat[4] = {1.0, 1.21, 1.31, 1.35}, thr[4] = {1.0, 2.25, 4.2, 4.75};
+    b->lanes.latency = std::max(b->lanes.latency, (0.35 + 0.17 * N + 0.25 * wide) * lat[g - 1]);
+    b->lanes.work += (0.17 + 0.125 * N + 0.15 * wide) * thr[g - 1];
+  }
+}
+
+// Lanes where the SIMD time that they save outweighs their longer chain.  A
+// solve lasts about (mean iterations) x work / SIMDs and some share of (most
+// iterations) x latency; how many times the mean the slowest instance takes is
+// not known before, so lanes have to save `most` latencies per mean iteration.
+// Measured, lanes against tiles are even where that ratio is a third of (most
+// / mean): cold batches had 8 to 58 there, those from predictions 2 to 12 but
+// for families with a system that converges slowly (80 to 180).  Lanes / tiles
+// (ratio; cold, from predictions): 16,384 of T = 64, n = 4 (18) 0.86, 1.19; of T =
+// 60, n = 6 (11) 0.98, 0.75; 4096 of T = 200, n = 4 (no longer chain) 0.87, 0.94; 16,384
+// of T = 50, n = 8 and one of T = 200 (51) 0.78, 0.47; but 16,384 of T = 64, n = 8 (3)
+// 1.23, 0.91; 4096 of T = 20 to 200, n = 4 to 12 (1.5) 1.76, 1.07.  And only
+// batches that keep the lanes' wavefronts on every SIMD for their latency.
+bool use_lanes(const admm_mpc_batch* b, bool warm) {
+  const double most = warm ? 9.0 : 16.0;
+  const double simds = 4.0 * b->cus, saved = (b->tiles.work - b->lanes.work) / simds;
+  return b->lanes.work > simds * b->lanes.latency &&
+         saved > most * std::max(b->lanes.latency - b->tiles.latency, 0.0);
+}
+
+auto solve_kernel(const admm_mpc_batch* b, const Form& f) {
+  if (&f == &b->lanes) return f.threads == LANE_WGS ? mpc_lane_kernel<LANE_WGS> : mpc_lane_kernel<LANE_WG>;
+  return b->wv == 4 ? mpc_solve_kernel<4> : b->wv == 8 ? mpc_solve_kernel<8> : mpc_solve_kernel<MAXW>;
 }
 
 void launch_dual(admm_mpc_batch* b, const float* z, float* u, int32_t* counter, hipStream_t st) {
@@ -828,6 +1310,7 @@ void launch_dual(admm_mpc_batch* b, const float* z, float* u, int32_t* counter, 
 admm_status launch_solve(admm_mpc_batch* b, const float* x0, const float* zinit, const float* uinit,
                          float tol, int32_t max_iter, float* zout, float* uout, int32_t* iters,
                          bool emptied, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
+  const Form& f = use_lanes(b, zinit != nullptr) ? b->lanes : b->tiles;
   SolveArgs a;
   a.inst = b->d_inst;
   a.par = b->d_par;
@@ -837,16 +1320,16 @@ admm_status launch_solve(admm_mpc_batch* b, const float* x0, const float* zinit,
   a.zout = zout;
   a.uout = uout;
   a.iters = iters;
-  a.items = b->d_items;
-  a.n_items = b->n_items;
+  a.items = f.d_items;
+  a.n_items = f.n_items;
   a.tol = tol;
   a.max_iter = max_iter;
   a.rho = (float)b->rho;
-  int grid = b->plan.grid > 0 ? b->plan.grid : b->resident;
-  grid = std::max(1, std::min(grid, b->n_items));
-  a.counter = grid < b->n_items || grid > b->cus ? b->d_counter : nullptr;
+  int grid = b->plan.grid > 0 ? b->plan.grid : f.resident;
+  grid = std::max(1, std::min(grid, f.n_items));
+  a.counter = grid < f.n_items || grid > b->cus ? b->d_counter : nullptr;
   if (a.counter && !emptied) reset_queue_kernel<<<1, 64, 0, st>>>(b->d_counter);
-  hipExtLaunchKernelGGL(solve_kernel(b->wv), dim3(grid), dim3(b->wv * 64), 0, st, e0, e1, 0, a);
+  hipExtLaunchKernelGGL(solve_kernel(b, f), dim3(grid), dim3(f.threads), 0, st, e0, e1, 0, a);
   ADMM_HIP(hipGetLastError());
   return ADMM_OK;
 }
@@ -955,17 +1438,23 @@ admm_status admm_mpc_batch_create(int32_t n_inst, const int32_t* T, const int32_
   if ((s = mpc_alloc(b.get(), (void**)&b->d_inst, sizeof(MpcInst) * n_inst))) return s;
   if ((s = mpc_alloc(b.get(), (void**)&b->d_par, sizeof(float) * par.size()))) return s;
   if ((s = mpc_alloc(b.get(), (void**)&b->d_u, sizeof(float) * b->u_total))) return s;
-  if ((s = mpc_alloc(b.get(), (void**)&b->d_items, sizeof(int32_t) * (MAXW + 1) * (size_t)n_inst))) return s;
+  if ((s = mpc_alloc(b.get(), (void**)&b->tiles.d_items, sizeof(int32_t) * (MAXW + 1) * (size_t)n_inst))) return s;
+  if ((s = mpc_alloc(b.get(), (void**)&b->lanes.d_items, sizeof(int32_t) * LANE_ITEM * (size_t)n_inst))) return s;
   if ((s = mpc_alloc(b.get(), (void**)&b->d_counter, sizeof(int32_t)))) return s;
   ADMM_HIP(hipMemcpy(b->d_inst, b->h_inst.data(), sizeof(MpcInst) * n_inst, hipMemcpyHostToDevice));
   ADMM_HIP(hipMemcpy(b->d_par, par.data(), sizeof(float) * par.size(), hipMemcpyHostToDevice));
-  int per_cu = 0;
   int maxT = 0;
   for (int32_t i = 0; i < n_inst; ++i) maxT = std::max(maxT, (int)T[i]);
   b->wv = maxT <= 64 ? 4 : maxT <= 128 ? 8 : MAXW;
-  ADMM_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, solve_kernel(b->wv), b->wv * 64, 0));
+  b->tiles.threads = b->wv * 64;
+  b->lanes.threads = maxT <= 128 ? LANE_WGS : LANE_WG;
   ADMM_HIP(hipDeviceGetAttribute(&b->cus, hipDeviceAttributeMultiprocessorCount, device));
-  b->resident = std::max(1, per_cu) * std::max(1, b->cus);
+  for (Form* f : {&b->tiles, &b->lanes}) {
+    int per_cu = 0;
+    ADMM_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, solve_kernel(b.get(), *f), f->threads, 0));
+    f->resident = std::max(1, per_cu) * std::max(1, b->cus);
+  }
+  estimate(b.get());
   if ((s = build_items(b.get(), Plan()))) return s;
   *out = b.release();
   return ADMM_OK;
@@ -1060,7 +1549,7 @@ admm_status admm_mpc_batch_get_plan(const admm_mpc_batch* b, int32_t* pack1, int
   if (pack1) *pack1 = b->plan.pack1;
   if (order) *order = b->plan.order;
   if (grid) *grid = b->plan.grid;
-  if (resident) *resident = b->resident;
+  if (resident) *resident = (use_lanes(b, false) ? b->lanes : b->tiles).resident;
   return ADMM_OK;
 }
 

@@ -1207,7 +1207,8 @@ __device__ __forceinline__ void xpass_hinge_tile(const XArgs<T>& a, const Bucket
         T u, n;
         state_un<T, A1>(mv[i][v], A1 ? T(0) : xv[i][v], zv[i], alpha, u, n);
         mv[i][v] = u;          // mv holds u from here on
-        dot[v] += on ? n * pv[i][v] : T(0);
+        const T sum = dot[v] + n * pv[i][v];
+        dot[v] = on ? sum : dot[v];
       }
     }
 #pragma unroll

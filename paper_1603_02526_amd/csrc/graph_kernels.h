@@ -1146,7 +1146,7 @@ __device__ __forceinline__ void xpass_hinge(const XArgs<T>& a, const BucketDesc&
 // dsh: one allocation per precision whatever the shape.
 template <typename T>
 __device__ __forceinline__ T (&hinge_smem())[NT / 64][64 * (16 / sizeof(T))] {
-  __shared__ T sm[NT / 64][64 * (16 / sizeof(T))];
+  __shared__ __align__(16) T sm[NT / 64][64 * (16 / sizeof(T))];
   return sm;
 }
 

@@ -122,11 +122,14 @@ __device__ __forceinline__ void store_chunk(const Chunk<R>& c, __bf16 (*s)[LROW]
   }
 }
 
+// (rows are written and read as vectors of 8 and 16 bytes)
 template <int BN>
 struct GroupSmem {
-  __bf16 a[BM][LROW];
-  __bf16 b[BN][LROW];
+  alignas(16) __bf16 a[BM][LROW];
+  alignas(16) __bf16 b[BN][LROW];
 };
+static_assert(LROW * sizeof(__bf16) % 16 == 0 && alignof(GroupSmem<32>) % 16 == 0,
+              "rows of operands are 16-byte aligned");
 
 template <int BN>
 struct Tile {

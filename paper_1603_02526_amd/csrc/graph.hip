@@ -345,12 +345,24 @@ void vector_layout(Plan& P, BucketDesc& b, int d) {
     return P.idx[off + (margin ? c * b.nfp + f : e * b.nfp + f * d + c)];
   };
   const int64_t vs = at(b.dst_off, 0, 0, 1) - at(b.dst_off, 0, 0, 0);
-  for (int64_t f = 0; f < nf; ++f)
-    for (int e = 0; e < edges; ++e)
-      for (int64_t c = 1; c < d; ++c)
-        if (at(b.idx_off, f, e, c) != at(b.idx_off, f, e, 0) + c ||
-            at(b.dst_off, f, e, c) != at(b.dst_off, f, e, 0) + c * vs)
-          return;
+  // the tables in memory order: margin's rows are components
+  const int64_t outer = margin ? d : nf, inner = margin ? nf : d;
+  for (int64_t e = 0; e < edges; ++e) {
+    const int32_t* z = P.idx.data() + b.idx_off + e * b.nfp;
+    const int32_t* q = P.idx.data() + b.dst_off + e * b.nfp;
+    const int64_t step = margin ? b.nfp : d;
+    for (int64_t i = 0; i < outer; ++i) {
+      int64_t off = 0;
+      if (margin) {
+        for (int64_t f = 0; f < inner; ++f)
+          off |= (z[i * step + f] - z[f] - i) | (q[i * step + f] - q[f] - i * vs);
+      } else {
+        for (int64_t c = 1; c < inner; ++c)
+          off |= (z[i * step + c] - z[i * step] - c) | (q[i * step + c] - q[i * step] - c * vs);
+      }
+      if (off) return;
+    }
+  }
   b.vd = d;
   b.vs = (int32_t)vs;
   P.layout_idx_bytes -= nf * edges * (d - 1) * 8;
@@ -589,13 +601,18 @@ admm_status build_plan(admm_graph& g, Plan& P, bool no_tiles) {
       b.blk1 = (int32_t)blocks;
       for (int64_t t = 0; t < tiles; ++t)
         for (int e = 0; e < gr.arity; ++e) em.push_back({zof(0, e), b.dst_off + t * gr.arity + e});
-      for (int64_t f = 0; f < gr.n; ++f)
+      std::vector<int64_t> zs(gr.arity);   // every factor's
+      for (int e = 0; e < gr.arity; ++e) zs[e] = zof(0, e);
+      for (int64_t f = 0; f < gr.n; ++f) {
+        const int64_t row = b.m_off + f / FB * gr.arity * FB + f % FB;
         for (int e = 0; e < gr.arity; ++e) {
-          P.upos[us] = b.m_off + (f / FB * gr.arity + e) * FB + f % FB;
-          P.uz[us] = (int32_t)zof(f, e);
-          deg[zof(f, e)] += rw; rmz[zof(f, e)] = std::max(rmz[zof(f, e)], rg);
+          P.upos[us] = row + e * FB;
+          P.uz[us] = (int32_t)zs[e];
+          deg[zs[e]] += rw;
           ++us;
         }
+      }
+      for (int64_t z : zs) rmz[z] = std::max(rmz[z], rg);
       P.algo_elems += (int64_t)gr.n * (2 * gr.arity + d + 3);
       // Admission to the resident driver (Plan::admit) counts a bucket as rows
       // of all factors, padded to 64, and a partial sum per 128 factors up

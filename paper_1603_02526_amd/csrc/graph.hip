@@ -274,9 +274,13 @@ int hinge_dmax(int d) { return d <= 32 ? 32 : d <= 64 ? 64 : 0; }
 
 // Buckets whose factors share variables have at least this many edge slots
 // before their factors go to more workgroups of fewer factors each, every one
-// with a partial sum per shared variable.  Splitting is the faster from some
-// 40,000 on, by up to a microsecond per iteration; smaller buckets keep one
-// partial sum per 256 factors, the count that n_contributions has had for them.
+// with a partial sum per shared variable.  Splitting would be the faster from
+// some 40,000 on (2000 x 20: 5.3 us per iteration against 6.4; margin on one
+// bias 500 x 10: 6.3 against 11.2); the line lies here because
+// n_contributions, which callers see, counts the partial sums, and below it
+// they stay as few as the shape allows: one per 256 factors for margin, for
+// the shared hinge in FP32 one per 256 up to d = 31, 128 up to 63, 64 up to
+// 127 and 32 above, in FP64 twice as many.
 constexpr int64_t MIN_SPLIT_SLOTS = 131072;
 
 // Lanes per row of factors of the shared-variable hinge (xpass_hinge_tile;
@@ -663,8 +667,8 @@ admm_status build_plan(admm_graph& g, Plan& P, bool no_tiles) {
       // one bias for every factor (the usual graph): one partial per workgroup
       b.ub = 1;
       for (int64_t f = 1; f < gr.n && b.ub; ++f) b.ub = zof(f, 1) == zof(0, 1);
-      // a small bucket keeps one partial sum per 256 factors where a thread can
-      // hold a factor in registers; above, its chain of d dependent loads and two
+      // a small bucket keeps one partial sum per 256 factors (MIN_SPLIT_SLOTS)
+      // where a thread can hold a factor in registers; above, its chain of d dependent loads and two
       // sweeps would be the iteration (700 x 180: 145 us, split 9)
       const bool split = !P.no_tiles && !(b.ub && d <= 32 && gr.n * (d + 2) < MIN_SPLIT_SLOTS);
       b.mode = split ? BM_HINGE_SPLIT : BM_GEN_FACTOR;

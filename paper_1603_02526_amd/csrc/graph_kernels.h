@@ -1141,8 +1141,8 @@ __device__ __forceinline__ void xpass_hinge(const XArgs<T>& a, const BucketDesc&
 // keeps to EM and leaves every CU a workgroup (hinge_lanes in graph.hip).
 // x-pass of 10,000 factors, against one thread per factor: FP32 d = 200 6.4
 // us (104.6), d = 50 4.3 (24.5); FP64 d = 50 4.7 (36.9), d = 200 9.0 (198);
-// of 100,000 FP32 factors, d = 20: 6.5 us, 26 MB = 4.0 TB/s (8.6 with four
-// lanes per four factors and each edge a row of all factors).
+// of 100,000 FP32 factors, d = 20: 6.1 us from start to end, 26 MB = 4.2 TB/s
+// (7.2 with four lanes per four factors and each edge a row of all factors).
 // dsh: one allocation per precision whatever the shape.
 template <typename T>
 __device__ __forceinline__ T (&hinge_smem())[NT / 64][64 * (16 / sizeof(T))] {

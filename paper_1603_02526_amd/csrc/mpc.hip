@@ -1138,7 +1138,7 @@ struct Plan {
 struct Form {
   int threads = 0;           // per workgroup
   int resident = 0;          // workgroups resident per device at full occupancy
-  int32_t* d_items = nullptr;
+  const int32_t* d_items = nullptr;
   int32_t n_items = 0;
   double work = 0, latency = 0;   // per iteration, us: SIMD time of all instances, longest instance alone
 };
@@ -1154,6 +1154,7 @@ struct admm_mpc_batch {
   MpcInst* d_inst = nullptr;
   float* d_par = nullptr;
   float* d_u = nullptr;       // dual-completion output
+  int32_t* d_items = nullptr;   // of both forms
   Form tiles, lanes;
   int32_t* d_counter = nullptr;
   Plan plan;
@@ -1175,79 +1176,6 @@ namespace {
 admm_status mpc_alloc(admm_mpc_batch* b, void** p, size_t bytes) {
   ADMM_HIP(hipMalloc(p, std::max<size_t>(bytes, 4)));
   b->allocs.push_back(*p);
-  return ADMM_OK;
-}
-
-// Work items for a plan: instances of more than T1 steps get a workgroup of
-// their own; shorter ones take one wavefront each, pack1 to every four
-// wavefronts of a workgroup, but no more than it takes to give every CU a
-// workgroup (a lone wavefront has a SIMD to itself).  One instance per
-// workgroup and more than one tile: in lockstep (a quarter less time per
-// iteration at T = 20).  Items are ordered by the plan's order key.
-admm_status build_items(admm_mpc_batch* b, const Plan& pl) {
-  std::vector<int32_t> ids(b->n_inst);
-  std::iota(ids.begin(), ids.end(), 0);
-  auto cost = [&](int i) {
-    const MpcInst& I = b->h_inst[i];
-    return (double)I.T * (2.0 * I.n * (I.n + I.m) + I.n * I.n + 8.0 * (I.n + I.m));
-  };
-  // expected duration of a solve: measured iterations x the latency of one
-  // iteration, which grows with the products' size and with the wavefronts
-  // per SIMD (fitted to single-instance timings: 0.66 us at T = 64, n = 8,
-  // 1.02 at T = 100, n = 12, 1.85 at T = 200, n = 12)
-  auto duration = [&](int i) {
-    const MpcInst& I = b->h_inst[i];
-    const double gx = (I.n + 3) / 4, wps = (I.T + 63) / 64;
-    const double it = std::max<int32_t>(1, std::abs(b->measured[i]));
-    return it * (0.45 + 0.05 * gx + wps * (0.1 + 0.08 * gx));
-  };
-  if (pl.order == 3 && (int)b->measured.size() == b->n_inst) {
-    std::stable_sort(ids.begin(), ids.end(),
-                     [&](int x, int y) { return duration(x) > duration(y); });
-  } else if (pl.order == 1 || pl.order == 3) {
-    std::stable_sort(ids.begin(), ids.end(), [&](int x, int y) { return cost(x) > cost(y); });
-  } else if (pl.order == 2) {
-    std::stable_sort(ids.begin(), ids.end(), [&](int x, int y) {
-      const MpcInst &X = b->h_inst[x], &Y = b->h_inst[y];
-      if (X.n != Y.n) return X.n > Y.n;
-      if (X.m != Y.m) return X.m > Y.m;
-      return X.T > Y.T;
-    });
-  }
-  // Items of `width` numbers: up to `pack` instances of at most short_t steps
-  // (first number `mode`), or one longer instance (first number mode + 1).
-  std::vector<int32_t> items;
-  auto fill = [&](Form& f, int width, int mode, int pack, int short_t) -> admm_status {
-    items.clear();
-    std::vector<int32_t> pend;
-    auto flush = [&]() {
-      if (pend.empty()) return;
-      items.push_back(mode);
-      for (int q = 0; q < width - 1; ++q) items.push_back(q < (int)pend.size() ? pend[q] : -1);
-      pend.clear();
-    };
-    for (int32_t i : ids) {
-      if (b->h_inst[i].T <= short_t) {
-        pend.push_back(i);
-        if ((int)pend.size() == pack) flush();
-      } else {
-        items.push_back(mode + 1);
-        items.push_back(i);
-        for (int q = 2; q < width; ++q) items.push_back(-1);
-      }
-    }
-    flush();
-    f.n_items = (int32_t)(items.size() / width);
-    ADMM_HIP(hipMemcpy(f.d_items, items.data(), items.size() * sizeof(int32_t), hipMemcpyHostToDevice));
-    return ADMM_OK;
-  };
-  int n_short = 0;
-  for (const MpcInst& I : b->h_inst) n_short += I.T <= T1;
-  const int share = pl.pack1 == 1 ? 1 : pl.pack1 * b->wv / 4;
-  const int pack = std::max(1, std::min(share, (n_short + b->cus - 1) / b->cus));
-  if (admm_status s = fill(b->tiles, MAXW + 1, 0, pack, pack > 1 ? T1 : 16)) return s;
-  if (admm_status s = fill(b->lanes, LANE_ITEM, 1, std::min(pl.pack1, b->lanes.threads / 64), 64)) return s;
-  b->plan = pl;
   return ADMM_OK;
 }
 
@@ -1288,6 +1216,81 @@ bool use_lanes(const admm_mpc_batch* b, bool warm) {
   const double simds = 4.0 * b->cus, saved = (b->tiles.work - b->lanes.work) / simds;
   return b->lanes.work > simds * b->lanes.latency &&
          saved > most * std::max(b->lanes.latency - b->tiles.latency, 0.0);
+}
+
+// Work items for a plan: instances of more than T1 steps get a workgroup of
+// their own; shorter ones take one wavefront each, pack1 to every four
+// wavefronts of a workgroup, but no more than it takes to give every CU a
+// workgroup (a lone wavefront has a SIMD to itself).  One instance per
+// workgroup and more than one tile: in lockstep (a quarter less time per
+// iteration at T = 20).  Items are ordered by the plan's order key.
+admm_status build_items(admm_mpc_batch* b, const Plan& pl) {
+  std::vector<int32_t> ids(b->n_inst);
+  std::iota(ids.begin(), ids.end(), 0);
+  auto cost = [&](int i) {
+    const MpcInst& I = b->h_inst[i];
+    return (double)I.T * (2.0 * I.n * (I.n + I.m) + I.n * I.n + 8.0 * (I.n + I.m));
+  };
+  // expected duration of a solve: measured iterations x the latency of one
+  // iteration, which grows with the products' size and with the wavefronts
+  // per SIMD (fitted to single-instance timings: 0.66 us at T = 64, n = 8,
+  // 1.02 at T = 100, n = 12, 1.85 at T = 200, n = 12)
+  auto duration = [&](int i) {
+    const MpcInst& I = b->h_inst[i];
+    const double gx = (I.n + 3) / 4, wps = (I.T + 63) / 64;
+    const double it = std::max<int32_t>(1, std::abs(b->measured[i]));
+    return it * (0.45 + 0.05 * gx + wps * (0.1 + 0.08 * gx));
+  };
+  if (pl.order == 3 && (int)b->measured.size() == b->n_inst) {
+    std::stable_sort(ids.begin(), ids.end(),
+                     [&](int x, int y) { return duration(x) > duration(y); });
+  } else if (pl.order == 1 || pl.order == 3) {
+    std::stable_sort(ids.begin(), ids.end(), [&](int x, int y) { return cost(x) > cost(y); });
+  } else if (pl.order == 2) {
+    std::stable_sort(ids.begin(), ids.end(), [&](int x, int y) {
+      const MpcInst &X = b->h_inst[x], &Y = b->h_inst[y];
+      if (X.n != Y.n) return X.n > Y.n;
+      if (X.m != Y.m) return X.m > Y.m;
+      return X.T > Y.T;
+    });
+  }
+  // Items of `width` numbers: up to `pack` instances of at most short_t steps
+  // (first number `mode`), or one longer instance (first number mode + 1).
+  // Both forms' items lie in one array, lanes' after tiles' if a solve may use them.
+  std::vector<int32_t> items;
+  auto fill = [&](Form& f, int width, int mode, int pack, int short_t) {
+    const size_t first = items.size();
+    std::vector<int32_t> pend;
+    auto flush = [&]() {
+      if (pend.empty()) return;
+      items.push_back(mode);
+      for (int q = 0; q < width - 1; ++q) items.push_back(q < (int)pend.size() ? pend[q] : -1);
+      pend.clear();
+    };
+    for (int32_t i : ids) {
+      if (b->h_inst[i].T <= short_t) {
+        pend.push_back(i);
+        if ((int)pend.size() == pack) flush();
+      } else {
+        items.push_back(mode + 1);
+        items.push_back(i);
+        for (int q = 2; q < width; ++q) items.push_back(-1);
+      }
+    }
+    flush();
+    f.d_items = b->d_items + first;
+    f.n_items = (int32_t)((items.size() - first) / width);
+  };
+  int n_short = 0;
+  for (const MpcInst& I : b->h_inst) n_short += I.T <= T1;
+  const int share = pl.pack1 == 1 ? 1 : pl.pack1 * b->wv / 4;
+  const int pack = std::max(1, std::min(share, (n_short + b->cus - 1) / b->cus));
+  fill(b->tiles, MAXW + 1, 0, pack, pack > 1 ? T1 : 16);
+  if (use_lanes(b, false) || use_lanes(b, true))
+    fill(b->lanes, LANE_ITEM, 1, std::min(pl.pack1, b->lanes.threads / 64), 64);
+  ADMM_HIP(hipMemcpy(b->d_items, items.data(), items.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+  b->plan = pl;
+  return ADMM_OK;
 }
 
 auto solve_kernel(const admm_mpc_batch* b, const Form& f) {
@@ -1438,8 +1441,7 @@ admm_status admm_mpc_batch_create(int32_t n_inst, const int32_t* T, const int32_
   if ((s = mpc_alloc(b.get(), (void**)&b->d_inst, sizeof(MpcInst) * n_inst))) return s;
   if ((s = mpc_alloc(b.get(), (void**)&b->d_par, sizeof(float) * par.size()))) return s;
   if ((s = mpc_alloc(b.get(), (void**)&b->d_u, sizeof(float) * b->u_total))) return s;
-  if ((s = mpc_alloc(b.get(), (void**)&b->tiles.d_items, sizeof(int32_t) * (MAXW + 1) * (size_t)n_inst))) return s;
-  if ((s = mpc_alloc(b.get(), (void**)&b->lanes.d_items, sizeof(int32_t) * LANE_ITEM * (size_t)n_inst))) return s;
+  if ((s = mpc_alloc(b.get(), (void**)&b->d_items, sizeof(int32_t) * (MAXW + 1 + LANE_ITEM) * (size_t)n_inst))) return s;
   if ((s = mpc_alloc(b.get(), (void**)&b->d_counter, sizeof(int32_t)))) return s;
   ADMM_HIP(hipMemcpy(b->d_inst, b->h_inst.data(), sizeof(MpcInst) * n_inst, hipMemcpyHostToDevice));
   ADMM_HIP(hipMemcpy(b->d_par, par.data(), sizeof(float) * par.size(), hipMemcpyHostToDevice));
